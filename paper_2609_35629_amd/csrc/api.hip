@@ -315,30 +315,20 @@ santapp_status santapp_build_teams(const void* K, const void* V, int B, int Hkv,
     t->P = parent_size;
     t->R = reps_per_parent;
     t->M = static_cast<int>(M);
-    double* mind = nullptr;
-    int* owner = nullptr;
+    void* state = nullptr;
     hipError_t e = alloc_table(t);
-    auto alloc = [&](void** p, size_t bytes) {
-        if (e == hipSuccess) e = hipMalloc(p, bytes);
-    };
-    if (!build_packs_in_place(N, d, dtype, parent_size, reps_per_parent)) {
-        // running minimum and owner per token, for the general build kernel
-        alloc(reinterpret_cast<void**>(&mind), BH * N * sizeof(double));
-        alloc(reinterpret_cast<void**>(&owner), BH * N * sizeof(int));
-    }
+    const bool packed = build_packs_in_place(N, parent_size);
+    if (e == hipSuccess && !packed) e = hipMalloc(&state, BH * N * build_state_bytes());
     if (e != hipSuccess) {
-        release(mind);
-        release(owner);
+        release(state);
         free_teams(t);
         (void)hipGetLastError();
         return fail(SANTAPP_ENOMEM, "device allocation failed: %s", hipGetErrorString(e));
     }
     const char* what = "team build";
-    bool packed = false;
     e = launch_build_parents(K, V, dtype, static_cast<int>(BH), N, d, parent_size, reps_per_parent,
-                             t->M, mind, owner, t->team_begin, t->team_size, t->log_n,
-                             t->rep_token, t->perm, t->packed_K, t->packed_V, t->reps, t->team_count,
-                             &packed, s);
+                             t->M, state, t->team_begin, t->team_size, t->log_n,
+                             t->rep_token, t->perm, t->packed_K, t->packed_V, t->reps, t->team_count, s);
     if (e == hipSuccess && !packed) {
         what = "packing K";
         e = launch_gather_rows(K, t->packed_K, t->perm, static_cast<int>(BH), N, N, row, s);
@@ -354,14 +344,12 @@ santapp_status santapp_build_teams(const void* K, const void* V, int B, int Hkv,
     if (e != hipSuccess) {
         // a launch failed: nothing of this call is left queued that uses the
         // buffers (hipFree waits for the device)
-        release(mind);
-        release(owner);
+        release(state);
         free_teams(t);
         return hip_fail(e, what);
     }
     const santapp_status st = finish_table(t, s, out);  // waits for the build
-    release(mind);
-    release(owner);
+    release(state);
     return st;
 }
 
@@ -499,8 +487,7 @@ santapp_status santapp_build_teams_from_labels(const void* K, const void* V, int
     Carver sc;
     const size_t o_mem = sc.take(BH * N * sizeof(int)), o_pbeg = sc.take(BH * (Mp + 1) * sizeof(int));
     const size_t o_toff = sc.take(BH * (Mp + 1) * sizeof(int)), o_tcount = sc.take(BH * sizeof(int));
-    const size_t o_bad = sc.take(sizeof(int)), o_mind = sc.take(BH * N * sizeof(double));
-    const size_t o_owner = sc.take(BH * N * sizeof(int));
+    const size_t o_bad = sc.take(sizeof(int)), o_state = sc.take(BH * N * build_state_bytes());
     char* scratch = nullptr;
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&scratch), sc.off);
     if (e != hipSuccess) {
@@ -513,8 +500,6 @@ santapp_status santapp_build_teams_from_labels(const void* K, const void* V, int
     int* toff = reinterpret_cast<int*>(scratch + o_toff);
     int* tcount = reinterpret_cast<int*>(scratch + o_tcount);
     int* bad = reinterpret_cast<int*>(scratch + o_bad);
-    double* mind = reinterpret_cast<double*>(scratch + o_mind);
-    int* owner = reinterpret_cast<int*>(scratch + o_owner);
     const char* what = "parent lists";
     e = hipMemsetAsync(bad, 0, sizeof(int), s);
     if (e == hipSuccess)
@@ -561,7 +546,7 @@ santapp_status santapp_build_teams_from_labels(const void* K, const void* V, int
     if (e == hipSuccess) {
         what = "team build";
         e = launch_build_parent_lists(K, dtype, static_cast<int>(BH), N, d, Mp, reps_per_parent, M, members,
-                                      pbeg, toff, mind, owner, t->team_begin, t->team_size, t->log_n,
+                                      pbeg, toff, scratch + o_state, t->team_begin, t->team_size, t->log_n,
                                       t->rep_token, t->perm, s);
     }
     if (e == hipSuccess) {

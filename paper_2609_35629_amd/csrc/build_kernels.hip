@@ -3,14 +3,21 @@
 // parent partition"; packed team-contiguous copy of the prompt K/V as in the
 // appendix "Triton decode kernels").
 //
-// One workgroup builds one contiguous parent of one (sequence, KV head).  The
+// One workgroup builds one parent of one (sequence, KV head).  The
 // farthest-first rounds and the nearest-representative assignment share one
-// running minimum per member: after round u, mind[i] = min_{v<=u} |k_i-k_{j_v}|^2
-// and owner[i] is the first v attaining it, which is exactly the assignment
-// rule (ties to the earliest-chosen representative) once all r rounds ran.
-// Distances are fp64 sums in dimension order with no fused multiply-add, so
-// every comparison sees the value the definition gives.
+// running minimum per member: after round u, m[i] = min_{v<=u} |k_i-k_{j_v}|^2
+// and the owner of i is the first v attaining it, which is exactly the
+// assignment rule (ties to the earliest-chosen representative) once all r
+// rounds ran.
+//
+// The definition's distance is an fp64 sum over dimensions in index order
+// with no fused multiply-add, and every choice (nearest the mean, farthest,
+// owner) is the definition's bit for bit.  Few choices need that arithmetic:
+// the rounds run on an fp32 estimate |k|^2 + |c|^2 - 2 k.c whose error is
+// bounded, and only members whose estimates lie within twice the bound of the
+// best one are compared by the definition's distance.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "internal.h"
@@ -19,12 +26,23 @@ namespace santapp {
 
 namespace {
 
-constexpr int kBuildThreads = 256;
+constexpr int kBuildThreads = 1024;  // most threads of a build workgroup
 constexpr int kBuildWaves = kBuildThreads / kWave;
-// label-defined parents hold about N / M members each (k-means: about P),
-// one workgroup per parent: four times the threads for fewer rounds per
-// member sweep
-constexpr int kListBuildThreads = 1024;
+constexpr int kTie = 64;             // members one exact comparison takes
+constexpr int kRankBlock = kWave;    // representatives ranked per ballot block
+constexpr float kInf = __builtin_inff();
+
+// Bound on |estimate - the definition's distance| over a parent whose largest
+// squared norm is nmax: a lane's chain of at most eight products, the four
+// additions over the sixteen lanes and the final combination round at most 20
+// times per inner product, each by at most 2^-23 of sum |x_i c_i| <=
+// (|x|^2 + |c|^2) / 2 <= nmax; three inner products (one of them twice) and
+// the final additions stay below 100 x 2^-23 nmax.
+constexpr float kEstimate = 128.f * 0x1.0p-23f;
+// Parents whose largest squared norm lies outside this range (fp32 products
+// could overflow or vanish, or a key is not finite) are built by the
+// definition's arithmetic throughout.
+constexpr float kNormMin = 1e-30f, kNormMax = 1e30f;
 
 // (value, index) reductions with ties broken toward the lower index.
 struct ArgVal {
@@ -40,8 +58,8 @@ __device__ __forceinline__ ArgVal pick_max(ArgVal a, ArgVal b) {
     return (b.v > a.v || (b.v == a.v && b.i < a.i)) ? b : a;
 }
 
-template <bool kMax, int W = kBuildWaves>
-__device__ ArgVal block_arg(ArgVal x, ArgVal* s_red) {
+template <bool kMax>
+__device__ ArgVal block_arg(ArgVal x, ArgVal* s_red, int nw) {
     for (int off = kWave / 2; off > 0; off >>= 1) {
         ArgVal y;
         y.v = __shfl_xor(x.v, off);
@@ -51,7 +69,7 @@ __device__ ArgVal block_arg(ArgVal x, ArgVal* s_red) {
     if (lane_id() == 0) s_red[wave_id()] = x;
     __syncthreads();
     ArgVal r = s_red[0];
-    for (int w = 1; w < W; ++w) r = kMax ? pick_max(r, s_red[w]) : pick_min(r, s_red[w]);
+    for (int w = 1; w < nw; ++w) r = kMax ? pick_max(r, s_red[w]) : pick_min(r, s_red[w]);
     __syncthreads();
     return r;
 }
@@ -63,6 +81,7 @@ __device__ double sqdist_to(const T* __restrict__ row, const double* __restrict_
 #pragma clang fp contract(off)
     double acc = 0.0;
     constexpr int kPer = 16 / static_cast<int>(sizeof(T));
+#pragma unroll 4
     for (int j = 0; j < d; j += kPer) {
         const uint4 w = *reinterpret_cast<const uint4*>(row + j);
         float v[kPer];
@@ -88,591 +107,824 @@ __device__ double sqdist_to(const T* __restrict__ row, const double* __restrict_
     return acc;
 }
 
-// NT threads per workgroup.  LIST: the parent's members are the token
-// indices mem[0 .. n) (ascending)
-// of a label-defined partition; otherwise the contiguous span [pP, pP + n).
-template <typename T, bool LIST, int NT>
-__global__ __launch_bounds__(NT) void k_build_parent(
-    const T* __restrict__ K, int N, int d, int P, int R, int M, double* __restrict__ mind_all,
-    int* __restrict__ owner_all, int* __restrict__ team_begin, int* __restrict__ team_size,
-    double* __restrict__ log_n, int* __restrict__ rep_token, int* __restrict__ perm,
-    const int* __restrict__ members, const int* __restrict__ pbeg, const int* __restrict__ toff, int Mp,
-    int* __restrict__ team_count) {
-#pragma clang fp contract(off)
-    // contiguous parents: every pair has M teams
-    if (!LIST && blockIdx.x == 0 && threadIdx.x == 0) team_count[blockIdx.y] = M;
-    __shared__ double s_vec[kMaxHeadDim];
-    __shared__ ArgVal s_red[(NT / kWave)];
-    __shared__ int s_reps[kMaxReps];
-    __shared__ int s_cnt[kMaxReps];
-    __shared__ int s_off[kMaxReps];
-    __shared__ int s_wcnt[(NT / kWave)][kMaxReps];
-
-    const int p = blockIdx.x;
-    const int bh = blockIdx.y;
-    const int tid = threadIdx.x;
-    int start, n, team0;
-    if constexpr (LIST) {
-        start = pbeg[static_cast<size_t>(bh) * (Mp + 1) + p];
-        n = pbeg[static_cast<size_t>(bh) * (Mp + 1) + p + 1] - start;
-        team0 = toff[static_cast<size_t>(bh) * (Mp + 1) + p];
-        if (n == 0) return;  // empty parents are omitted (uniform over the workgroup)
-    } else {
-        start = p * P;
-        n = min(P, N - start);
-        team0 = p * min(R, P);  // every earlier parent is full-size
-    }
-    const int r = min(R, n);
-    const int* mem = LIST ? members + static_cast<size_t>(bh) * N + start : nullptr;
-    // token of member i, and its key row
-    auto tok = [&](int i) { return LIST ? mem[i] : start + i; };
-    const T* Kb = K + static_cast<size_t>(bh) * N * d;
-    auto row = [&](int i) { return Kb + static_cast<size_t>(tok(i)) * d; };
-    double* mind = mind_all + static_cast<size_t>(bh) * N + start;
-    int* owner = owner_all + static_cast<size_t>(bh) * N + start;
-
-    // parent mean, summed over members in token order
-    for (int j = tid; j < d; j += NT) {
-        double s = 0.0;
-        for (int i = 0; i < n; ++i) s = s + static_cast<double>(load_elem(row(i), j));
-        s_vec[j] = s / static_cast<double>(n);
-    }
-    __syncthreads();
-
-    // first representative: the member nearest the mean
-    ArgVal best{INFINITY, 0x7fffffff};
-    for (int i = tid; i < n; i += NT) {
-        ArgVal c{sqdist_to(row(i), s_vec, d), i};
-        best = pick_min(best, c);
-    }
-    best = block_arg<false, NT / kWave>(best, s_red);
-    // a reduction without a winner (NaN keys) falls back to member 0, so
-    // that every index stays inside the parent
-    int rep = best.i < n ? best.i : 0;
-
-    for (int u = 0; u < r; ++u) {
-        if (tid == 0) s_reps[u] = rep;
-        for (int j = tid; j < d; j += NT) s_vec[j] = static_cast<double>(load_elem(row(rep), j));
-        __syncthreads();
-        // fold the new representative into the running minimum; a chosen
-        // representative gets -1 so that it is never chosen again
-        ArgVal far{-INFINITY, 0x7fffffff};
-        for (int i = tid; i < n; i += NT) {
-            double m, dd = sqdist_to(row(i), s_vec, d);
-            int o;
-            if (u == 0) {
-                m = dd;
-                o = 0;
-            } else {
-                m = mind[i];
-                o = owner[i];
-                if (dd < m) {
-                    m = dd;
-                    o = u;
-                }
-            }
-            if (i == rep) {
-                m = -1.0;
-                o = u;
-            }
-            mind[i] = m;
-            owner[i] = o;
-            far = pick_max(far, ArgVal{m, i});
-        }
-        if (u + 1 < r) {
-            far = block_arg<true, NT / kWave>(far, s_red);
-            rep = far.i < n ? far.i : 0;
-        } else {
-            __syncthreads();
-        }
-    }
-
-    // team sizes and offsets inside the parent
-    for (int u = tid; u < r; u += NT) s_cnt[u] = 0;
-    __syncthreads();
-    for (int i = tid; i < n; i += NT) atomicAdd(&s_cnt[owner[i]], 1);
-    __syncthreads();
-    if (tid == 0) {
-        int acc = 0;
-        for (int u = 0; u < r; ++u) {
-            s_off[u] = acc;
-            acc += s_cnt[u];
-        }
-    }
-    __syncthreads();
-    const size_t tbase = static_cast<size_t>(bh) * M + team0;
-    for (int u = tid; u < r; u += NT) {
-        team_begin[tbase + u] = start + s_off[u];
-        team_size[tbase + u] = s_cnt[u];
-        log_n[tbase + u] = log(static_cast<double>(s_cnt[u]));
-        rep_token[tbase + u] = tok(s_reps[u]);
-    }
-
-    // packed position of each member: team offset + rank among the team's
-    // members in token order (ballots per representative, chunk by chunk)
-    int* pperm = perm + static_cast<size_t>(bh) * N + start;
-    const int w = wave_id();
-    const uint64_t lt = lanemask_lt();
-    for (int base = 0; base < n; base += NT) {
-        const int i = base + tid;
-        const int o = (i < n) ? owner[i] : -1;
-        int rank_in_wave = 0;
-        for (int u = 0; u < r; ++u) {
-            const uint64_t m = __ballot(o == u);
-            if (o == u) rank_in_wave = __popcll(m & lt);
-            if (lane_id() == 0) s_wcnt[w][u] = __popcll(m);
-        }
-        __syncthreads();
-        if (i < n) {
-            int pos = s_off[o] + rank_in_wave;
-            for (int v = 0; v < w; ++v) pos += s_wcnt[v][o];
-            pperm[pos] = tok(i);
-        }
-        __syncthreads();
-        for (int u = tid; u < r; u += NT) {
-            int add = 0;
-            for (int v = 0; v < (NT / kWave); ++v) add += s_wcnt[v][u];
-            s_off[u] += add;
-        }
-        __syncthreads();
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Register-resident variant of the same construction for parents of at most
-// kRegThreads members whose rows fit 64 registers (d * element size <= 256 B).
-// Thread i holds member i's key row in registers for the whole build, so each
-// round reads only the new representative (an LDS broadcast) instead of every
-// member's row from memory.  The arithmetic, its order and the tie rules are
-// those of k_build_parent, so both kernels produce identical tables.
-constexpr int kRegThreads = 512;
-constexpr int kRegWaves = kRegThreads / kWave;
-constexpr int kRankBlock = kWave;  // representatives ranked per ballot block
-
-// A member row as 32-bit words: packed bf16 pairs, or fp32 values.
+// The same between two rows in memory.
 template <typename T, int D>
-struct RegRow;
-
-template <int D>
-struct RegRow<bf16_t, D> {
-    static constexpr int kWords = D / 2;
-    uint32_t w[kWords];
-    __device__ __forceinline__ void load(const bf16_t* row) {
-        const uint4* p = reinterpret_cast<const uint4*>(row);
-#pragma unroll
-        for (int k = 0; k < kWords / 4; ++k) {
-            const uint4 v = p[k];
-            w[4 * k] = v.x;
-            w[4 * k + 1] = v.y;
-            w[4 * k + 2] = v.z;
-            w[4 * k + 3] = v.w;
-        }
-    }
-    __device__ __forceinline__ float elem(int j) const {
-        return (j & 1) ? bf16hi(w[j >> 1]) : bf16lo(w[j >> 1]);
-    }
-    // hides the words from code motion: widening the row to fp64 ahead of
-    // its use would need 4 D registers
-    __device__ __forceinline__ void opaque() {
-#pragma unroll
-        for (int k = 0; k < kWords; ++k) asm volatile("" : "+v"(w[k]));
-    }
-    // the same for the words of dimensions j0 .. j0 + 7
-    __device__ __forceinline__ void opaque8(int j0) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(w[j0 / 2 + k]));
-    }
-    __device__ __forceinline__ void store(bf16_t* row) const {
-        uint4* p = reinterpret_cast<uint4*>(row);
-#pragma unroll
-        for (int k = 0; k < kWords / 4; ++k) p[k] = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-    }
-    // the row as kWords / 4 chunks of 16 bytes, chunk c at position c ^ sw
-    __device__ __forceinline__ void store_swizzled(uint4* dst, int sw) const {
-#pragma unroll
-        for (int k = 0; k < kWords / 4; ++k) dst[k ^ sw] = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-    }
-    // element j of a row stored by store_swizzled
-    static __device__ __forceinline__ float swizzled_elem(const uint4* src, int j, int sw) {
-        const uint16_t* c = reinterpret_cast<const uint16_t*>(src + ((j >> 3) ^ sw));
-        return __uint_as_float(static_cast<uint32_t>(c[j & 7]) << 16);
-    }
-    // lane l < kWords widens the stored row's word l (dimensions 2l, 2l + 1)
-    // to fp64
-    static __device__ __forceinline__ void widen(const uint32_t* words, double* out, int lane) {
-        if (lane < kWords) {
-            const uint32_t x = words[lane];
-            *reinterpret_cast<double2*>(out + 2 * lane) =
-                make_double2(static_cast<double>(bf16lo(x)), static_cast<double>(bf16hi(x)));
-        }
-    }
-};
-
-template <int D>
-struct RegRow<float, D> {
-    static constexpr int kWords = D;
-    float w[kWords];
-    __device__ __forceinline__ void load(const float* row) {
-        const float4* p = reinterpret_cast<const float4*>(row);
-#pragma unroll
-        for (int k = 0; k < kWords / 4; ++k) {
-            const float4 v = p[k];
-            w[4 * k] = v.x;
-            w[4 * k + 1] = v.y;
-            w[4 * k + 2] = v.z;
-            w[4 * k + 3] = v.w;
-        }
-    }
-    __device__ __forceinline__ float elem(int j) const { return w[j]; }
-    __device__ __forceinline__ void opaque() {
-#pragma unroll
-        for (int k = 0; k < kWords; ++k) asm volatile("" : "+v"(w[k]));
-    }
-    __device__ __forceinline__ void opaque8(int j0) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) asm volatile("" : "+v"(w[j0 + k]));
-    }
-    __device__ __forceinline__ void store(float* row) const {
-        float4* p = reinterpret_cast<float4*>(row);
-#pragma unroll
-        for (int k = 0; k < kWords / 4; ++k) p[k] = make_float4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-    }
-    __device__ __forceinline__ void store_swizzled(uint4* dst, int sw) const {
-#pragma unroll
-        for (int k = 0; k < kWords / 4; ++k)
-            dst[k ^ sw] = make_uint4(__float_as_uint(w[4 * k]), __float_as_uint(w[4 * k + 1]),
-                                     __float_as_uint(w[4 * k + 2]), __float_as_uint(w[4 * k + 3]));
-    }
-    static __device__ __forceinline__ float swizzled_elem(const uint4* src, int j, int sw) {
-        return reinterpret_cast<const float*>(src + ((j >> 2) ^ sw))[j & 3];
-    }
-    // lane l < kWords widens the stored row's dimension l to fp64
-    static __device__ __forceinline__ void widen(const uint32_t* words, double* out, int lane) {
-        if (lane < kWords) out[lane] = static_cast<double>(__uint_as_float(words[lane]));
-    }
-};
-
-// |k - c|^2 with c an fp64 vector in LDS (read as broadcasts), summed in
-// dimension order without contraction.
-template <typename T, int D>
-__device__ __forceinline__ double reg_sqdist(const RegRow<T, D>& r, const double* c) {
+__device__ double sqdist_rows(const T* __restrict__ a, const T* __restrict__ c) {
 #pragma clang fp contract(off)
+    constexpr int kPer = 16 / static_cast<int>(sizeof(T));
     double acc = 0.0;
+#pragma unroll 4
+    for (int j = 0; j < D; j += kPer) {
+        const uint4 x = *reinterpret_cast<const uint4*>(a + j), y = *reinterpret_cast<const uint4*>(c + j);
+        const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
 #pragma unroll
-    for (int j = 0; j < D; j += 2) {
-        // LDS reads are kept in groups of four (eight dims): hoisting them
-        // all would need 256 registers for c
-        if (j % 8 == 0) asm volatile("" ::: "memory");
-        const double2 cc = *reinterpret_cast<const double2*>(c + j);
-        const double t0 = static_cast<double>(r.elem(j)) - cc.x;
-        acc = acc + t0 * t0;
-        const double t1 = static_cast<double>(r.elem(j + 1)) - cc.y;
-        acc = acc + t1 * t1;
+        for (int q = 0; q < 4; ++q) {
+            if constexpr (sizeof(T) == 2) {
+                const double t0 = static_cast<double>(bf16lo(xs[q])) - static_cast<double>(bf16lo(ys[q]));
+                acc = acc + t0 * t0;
+                const double t1 = static_cast<double>(bf16hi(xs[q])) - static_cast<double>(bf16hi(ys[q]));
+                acc = acc + t1 * t1;
+            } else {
+                const double t = static_cast<double>(__uint_as_float(xs[q])) - static_cast<double>(__uint_as_float(ys[q]));
+                acc = acc + t * t;
+            }
+        }
     }
     return acc;
 }
 
-// (value, index) extremum over the wave (wave-uniform): DPP row rotations
-// within each 16-lane row, then the four rows' results.  The order is total
-// (value, then the smaller index; NaN never reaches it), so any reduction
-// order gives the same winner.
-template <bool kMax>
-__device__ __forceinline__ ArgVal wave_arg(ArgVal x) {
-#define SANTAPP_ARGSTEP(CTRL)                                                  \
-    {                                                                          \
-        ArgVal y;                                                              \
-        y.v = dpp_f64<CTRL>(x.v);                                              \
-        y.i = __builtin_amdgcn_update_dpp(0, x.i, CTRL, 0xF, 0xF, false);     \
-        x = kMax ? pick_max(x, y) : pick_min(x, y);                            \
+// Completes x here: work on rows streamed through registers is not put off
+// (which would keep the rows alive).
+__device__ __forceinline__ void done(float& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void done(double& x) { asm volatile("" : "+v"(x)); }
+
+// One of sixteen lanes' share of a row: d / 16 consecutive elements.
+template <typename T, int D>
+struct Chunk {
+    static constexpr int E = D / 16;
+    static constexpr int W = E * static_cast<int>(sizeof(T)) / 4;  // 32-bit words
+    static_assert(W == 2 || W == 4 || W == 8, "8, 16 or 32 bytes per lane");
+    uint32_t w[W];
+
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int i = 0; i < W; ++i) w[i] = 0;
     }
-    SANTAPP_ARGSTEP(0x128)
-    SANTAPP_ARGSTEP(0x124)
-    SANTAPP_ARGSTEP(0x122)
-    SANTAPP_ARGSTEP(0x121)
-#undef SANTAPP_ARGSTEP
-    const uint64_t vb = static_cast<uint64_t>(__double_as_longlong(x.v));
-    ArgVal r{__longlong_as_double(static_cast<long long>(readlane(vb, 0))), readlane(x.i, 0)};
+    // hides the words from code motion (rows kept in registers would
+    // otherwise be kept a second time, widened)
+    __device__ __forceinline__ void opaque() {
 #pragma unroll
-    for (int row = 1; row < 4; ++row) {
-        const ArgVal y{__longlong_as_double(static_cast<long long>(readlane(vb, 16 * row))), readlane(x.i, 16 * row)};
-        r = kMax ? pick_max(r, y) : pick_min(r, y);
+        for (int i = 0; i < W; ++i) asm volatile("" : "+v"(w[i]));
     }
-    return r;
-}
-
-// (value, index) reduction over the workgroup's waves; s_red holds one
-// entry per wave.  The caller separates reuses of s_red by a barrier.
-template <bool kMax>
-__device__ __forceinline__ ArgVal reg_block_arg(ArgVal x, ArgVal* s_red, int nw) {
-    x = wave_arg<kMax>(x);
-    if (lane_id() == 0) s_red[wave_id()] = x;
-    __syncthreads();
-    ArgVal r = s_red[0];
+    __device__ __forceinline__ void load(const T* p) {
+        if constexpr (W == 2) {
+            const uint2 x = *reinterpret_cast<const uint2*>(p);
+            w[0] = x.x;
+            w[1] = x.y;
+        } else {
 #pragma unroll
-    for (int w = 1; w < kRegWaves; ++w)
-        if (w < nw) r = kMax ? pick_max(r, s_red[w]) : pick_min(r, s_red[w]);
-    return r;
-}
-
-// Thread t owns members t + k * blockDim.x, k < MPT, and is launched with
-// max(D, ceil(members / MPT) rounded up to a wave) threads.  Two members per
-// thread let one LDS read of the representative serve two distances.  The
-// kernel also writes the parent's rows of the packed copies: each member's
-// key from its registers and its value row, at its packed position, and the
-// representative key of each of its teams.
-template <typename T, int D, int MPT>
-__global__ __launch_bounds__(kRegThreads) void k_build_parent_regs(
-    const T* __restrict__ K, const T* __restrict__ V, int N, int P, int R, int M,
-    int* __restrict__ team_begin, int* __restrict__ team_size, double* __restrict__ log_n,
-    int* __restrict__ rep_token, int* __restrict__ perm, T* __restrict__ packed_K,
-    T* __restrict__ packed_V, T* __restrict__ reps, int* __restrict__ team_count) {
-#pragma clang fp contract(off)
-    __shared__ __align__(16) double s_mean[D];
-    __shared__ __align__(16) uint32_t s_raw[RegRow<T, D>::kWords];  // the new representative's words
-    __shared__ __align__(16) double s_cw[kRegWaves][D];  // each wave's fp64 copy of it
-    // one slot's rows (member t + k nt in row t), for the mean; 16-byte
-    // chunk c of row t sits at position c ^ (t mod chunks) so that the
-    // lanes' row stores spread over the banks
-    constexpr int kChunks = RegRow<T, D>::kWords / 4;
-    __shared__ __align__(16) uint4 s_rows[kRegThreads][kChunks];
-    __shared__ ArgVal s_red[2][kRegWaves];
-    __shared__ int s_reps[kMaxReps];
-    __shared__ int s_cnt[kMaxReps];
-    __shared__ int s_off[kMaxReps];
-    __shared__ int s_wsum[kRegWaves];
-    __shared__ int s_wcnt[MPT][kRegWaves][kRankBlock];
-
-    const int p = blockIdx.x;
-    const int bh = blockIdx.y;
-    const int tid = threadIdx.x;
-    const int nt = blockDim.x;
-    const int nw = nt / kWave;
-    const int w = wave_id(), lane = lane_id();
-    const int start = p * P;
-    const int n = min(P, N - start);
-    const int r = min(R, n);
-    const int team0 = p * min(R, P);  // every earlier parent is full-size
-    const T* Kc = K + (static_cast<size_t>(bh) * N + start) * D;
-    if (p == 0 && tid == 0) team_count[bh] = M;  // every pair has M teams
-
-    RegRow<T, D> row[MPT];
-    bool member[MPT];
-#pragma unroll
-    for (int k = 0; k < MPT; ++k) {
-        const int i = tid + k * nt;
-        member[k] = i < n;
-        if (member[k]) row[k].load(Kc + static_cast<size_t>(i) * D);
-    }
-
-    // parent mean, summed over members in token order: each slot's rows
-    // pass through LDS at once, and thread j < D adds dimension j of each
-    // staged row in turn, the reads 16 rows ahead of their (serial)
-    // additions
-    double msum = 0.0;
-#pragma unroll
-    for (int k = 0; k < MPT; ++k) {
-        const int cnt = min(nt, n - k * nt);  // members of slot k
-        if (cnt <= 0) break;
-        if (k > 0) __syncthreads();  // the previous slot's reads are done
-        row[k].opaque();
-        if (member[k]) row[k].store_swizzled(s_rows[tid], tid & (kChunks - 1));
-        __syncthreads();
-        if (tid < D) {
-            int i0 = 0;
-            for (; i0 + 16 <= cnt; i0 += 16) {
-                float x[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    x[i] = RegRow<T, D>::swizzled_elem(s_rows[i0 + i], tid, (i0 + i) & (kChunks - 1));
-#pragma unroll
-                for (int i = 0; i < 16; ++i) msum = msum + static_cast<double>(x[i]);
-                asm volatile("" : "+v"(msum)::"memory");  // one batch of reads in flight at a time
+            for (int i = 0; i < W; i += 4) {
+                const uint4 x = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(p) + i);
+                w[i] = x.x;
+                w[i + 1] = x.y;
+                w[i + 2] = x.z;
+                w[i + 3] = x.w;
             }
-            for (; i0 < cnt; ++i0)
-                msum = msum + static_cast<double>(RegRow<T, D>::swizzled_elem(s_rows[i0], tid, i0 & (kChunks - 1)));
         }
     }
-    if (tid < D) s_mean[tid] = msum / static_cast<double>(n);
-    __syncthreads();
-
-    // distances of this thread's members to the vector c in LDS: |k - c|^2
-    // summed in dimension order without contraction, one LDS read of c for
-    // all MPT members, eight dimensions per scheduling group (hoisting the
-    // reads or the widening of all dimensions would need 4 D registers)
-    auto distances = [&](const double* c, double (&dd)[MPT]) {
+    __device__ __forceinline__ void store(T* p) const {
+        if constexpr (W == 2) {
+            *reinterpret_cast<uint2*>(p) = make_uint2(w[0], w[1]);
+        } else {
 #pragma unroll
-        for (int k = 0; k < MPT; ++k) {
-            row[k].opaque();
-            dd[k] = 0.0;
+            for (int i = 0; i < W; i += 4)
+                *reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(p) + i) = make_uint4(w[i], w[i + 1], w[i + 2], w[i + 3]);
         }
+    }
+    __device__ __forceinline__ float elem(int e) const {
+        if constexpr (sizeof(T) == 2)
+            return (e & 1) ? bf16hi(w[e >> 1]) : bf16lo(w[e >> 1]);
+        else
+            return __uint_as_float(w[e]);
+    }
+    // this lane's part of the inner product of two rows
+    __device__ __forceinline__ float dot(const Chunk& o) const {
+        float acc = 0.f;
+        if constexpr (sizeof(T) == 2) {
+            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-        for (int j = 0; j < D; j += 2) {
-            if (j % 8 == 0) {
-                // the sums so far are complete before the group's LDS reads
-                // and widening (no group's work moves past another's)
+            for (int i = 0; i < W; ++i)
+                acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[i]),
+                                                      __builtin_bit_cast(bf16x2, o.w[i]), acc, false);
+        } else {
 #pragma unroll
-                for (int k = 0; k < MPT; ++k) {
-                    asm volatile("" : "+v"(dd[k])::"memory");
-                    row[k].opaque8(j);
+            for (int i = 0; i < W; ++i) acc = fmaf(__uint_as_float(w[i]), __uint_as_float(o.w[i]), acc);
+        }
+        return acc;
+    }
+    __device__ __forceinline__ float dot(const float (&c)[E]) const {
+        float acc = 0.f;
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc = fmaf(elem(e), c[e], acc);
+        return acc;
+    }
+};
+
+// Sixteen rows' partial sums per lane -> lane j of the sixteen holds row j's
+// total: four halving exchanges (partners l ^ 15, l ^ 7, l ^ 3, l ^ 1).
+__device__ __forceinline__ float transpose_sum16(const float (&v)[16]) {
+    const int l = lane_id();
+    float a[8], b[4], c[2];
+    const bool h3 = l & 8, h2 = l & 4, h1 = l & 2, h0 = l & 1;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a[k] = (h3 ? v[k + 8] : v[k]) + dpp_f32<0x140>(h3 ? v[k] : v[k + 8]);  // row_mirror
+#pragma unroll
+    for (int k = 0; k < 4; ++k) b[k] = (h2 ? a[k + 4] : a[k]) + dpp_f32<0x141>(h2 ? a[k] : a[k + 4]);  // row_half_mirror
+#pragma unroll
+    for (int k = 0; k < 2; ++k) c[k] = (h1 ? b[k + 2] : b[k]) + dpp_f32<0x1B>(h1 ? b[k] : b[k + 2]);   // quad [3,2,1,0]
+    return (h0 ? c[1] : c[0]) + dpp_f32<0xB1>(h0 ? c[0] : c[1]);                                      // quad [1,0,3,2]
+}
+
+// Maximum of a float over the wave (wave-uniform).
+__device__ __forceinline__ float wave_max_f32(float v) {
+    v = fmaxf(v, dpp_f32<0x128>(v));
+    v = fmaxf(v, dpp_f32<0x124>(v));
+    v = fmaxf(v, dpp_f32<0x122>(v));
+    v = fmaxf(v, dpp_f32<0x121>(v));
+    const int x = __float_as_int(v);
+    return fmaxf(fmaxf(__int_as_float(readlane(x, 0)), __int_as_float(readlane(x, 16))),
+                 fmaxf(__int_as_float(readlane(x, 32)), __int_as_float(readlane(x, 48))));
+}
+
+// A member's running minimum over the representatives so far: the three
+// smallest estimates and the representatives of the first two (own = first |
+// second << 16).  A chosen representative has m1 = -inf and owns itself.
+// While a parent is built by the definition's distances (m1, m2) hold the
+// bits of its fp64 minimum and own its owner.
+struct MemberState {
+    float m1, m2, m3;
+    uint32_t own;
+    float nx;  // the member's squared norm (kept here in memory only)
+    __device__ __forceinline__ void reset() {
+        m1 = m2 = m3 = kInf;
+        own = 0;
+    }
+    __device__ __forceinline__ void add(float a, uint32_t u) {
+        const bool first = a < m1, second = a < m2;
+        m3 = fminf(m3, fmaxf(m2, a));
+        m2 = fminf(m2, fmaxf(m1, a));
+        m1 = fminf(m1, a);
+        own = first ? (own << 16) | u : second ? (own & 0xffffu) | (u << 16) : own;
+    }
+    __device__ __forceinline__ void choose(uint32_t u) {
+        m1 = -kInf;
+        own = (own & 0xffff0000u) | u;
+    }
+    __device__ __forceinline__ double exact() const {
+        return __hiloint2double(__float_as_int(m2), __float_as_int(m1));
+    }
+    __device__ __forceinline__ void set_exact(double m, int o) {
+        m1 = __int_as_float(__double2loint(m));
+        m2 = __int_as_float(__double2hiint(m));
+        own = static_cast<uint32_t>(o);
+    }
+};
+
+// LDS of a build workgroup of nw waves and up to r representatives (bytes).
+struct BuildLds {
+    int part, vec, row, best, red, tie_i, tie_v, tie_o, reps, cnt, off, wcnt, misc, total;
+};
+__host__ __device__ inline BuildLds build_lds(int nw, int r, int d, int esz) {
+    BuildLds L{};
+    int o = 0;
+    auto take = [&](int bytes) {
+        const int at = o;
+        o += (bytes + 15) / 16 * 16;
+        return at;
+    };
+    L.part = take(nw * d * 8);  // the waves' mean sums; then the waves' farthest rows (2 nw rows)
+    L.row = L.part;
+    static_assert(2 * 4 <= 8, "two fp32 rows fit a row of doubles");
+    L.vec = take(d * 8);
+    L.best = take(2 * nw * 16);
+    L.red = take(nw * static_cast<int>(sizeof(ArgVal)));
+    L.tie_i = take(kTie * 4);
+    L.tie_v = take(kTie * 8);
+    L.tie_o = take(kTie * 4);
+    L.reps = take(r * 4);
+    L.cnt = take(r * 4);
+    L.off = take(r * 4);
+    L.wcnt = take(nw * (r < kRankBlock ? r : kRankBlock) * 4);
+    L.misc = take((nw + 4) * 4);
+    L.total = o;
+    return L;
+}
+
+// Thread t owns members t, t + nt, ... of its parent (nt = blockDim.x; ONE:
+// at most nt members, so one each, its state in registers, else in `state`).
+// Each sixteen lanes hold the rows of their sixteen members of a block of nt
+// together, one sixteenth of every row per lane, so that rows are read and
+// written whole and a round needs one sixteenth of the representative per
+// lane; the first block's first CACHE rows stay in registers for the whole
+// build, the rest are read again each round (from the L2).
+//
+// What bounds it: instruction issue in the rounds (per sixteen members of a
+// lane group 64 dot products of bf16 pairs, the exchange that hands each lane
+// its member's sum, about 100 instructions of state and maximum; one barrier),
+// and the rows' traffic before and after them.  32K tokens of bf16 d = 128 for
+// four KV heads, P = 1024, R = 16: 74 us, of which 38 us with R = 1, so 2.2 us
+// a round (fp64 distances of rows in registers took 6.7 us a round, 178 us in
+// all).  9001 tokens of fp32 d = 128: 117 us, most rows read again from the L2
+// every round (4.1 us a round; 620 us in fp64 with 256 threads).  P = 16, R = 4
+// at 32K: 64 us, one wave per parent (518 us).  K-means parents at 32K: 140 us
+// (782 us).
+// The thread index as a value of its own: what is derived from it here is not
+// kept in registers from (or for) another phase of the kernel.
+__device__ __forceinline__ int fresh_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+template <typename T, int D, bool LIST, bool ONE>
+__device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, int N, int R, int M, int bh, int start,
+                             int n, int team0, const int* __restrict__ mem, MemberState* __restrict__ state_all,
+                             int* __restrict__ team_begin, int* __restrict__ team_size, double* __restrict__ log_n,
+                             int* __restrict__ rep_token, int* __restrict__ perm, T* __restrict__ packed_K,
+                             T* __restrict__ packed_V, T* __restrict__ reps, char* lds) {
+    using C = Chunk<T, D>;
+    constexpr int E = C::E;
+    // rows kept in registers, and rows of the others in flight at once: what
+    // 128 registers a thread hold beside the sixteen sums
+    constexpr int CACHE = C::W == 2 ? 16 : C::W == 4 && ONE ? 16 : 4;
+    constexpr int BATCH = C::W == 2 ? 8 : C::W == 4 ? 4 : 2;
+    const int tid = threadIdx.x, nt = blockDim.x, nw = nt / kWave;
+    const int w = wave_id(), lane = lane_id(), sub = lane & 15, g16 = tid & ~15, lbase = lane & 48;
+    const int r = min(R, n);
+    const int nblk = ONE ? 1 : (n + nt - 1) / nt;
+    const BuildLds L = build_lds(nw, R, D, sizeof(T));
+    double* const s_part = reinterpret_cast<double*>(lds + L.part);
+    char* const s_row = lds + L.row;
+    double* const s_vec = reinterpret_cast<double*>(lds + L.vec);
+    float4* const s_best = reinterpret_cast<float4*>(lds + L.best);
+    ArgVal* const s_red = reinterpret_cast<ArgVal*>(lds + L.red);
+    int* const s_ti = reinterpret_cast<int*>(lds + L.tie_i);
+    unsigned long long* const s_tv = reinterpret_cast<unsigned long long*>(lds + L.tie_v);
+    int* const s_reps = reinterpret_cast<int*>(lds + L.reps);
+    int* const s_cnt = reinterpret_cast<int*>(lds + L.cnt);
+    int* const s_off = reinterpret_cast<int*>(lds + L.off);
+    int* const s_wcnt = reinterpret_cast<int*>(lds + L.wcnt);
+    int* const s_misc = reinterpret_cast<int*>(lds + L.misc);
+    const int wstride = min(R, kRankBlock);
+
+    const T* const Kb = K + static_cast<size_t>(bh) * N * D;
+    auto tok = [&](int i) { return LIST ? mem[i] : start + i; };
+    auto row = [&](int i) { return Kb + static_cast<size_t>(tok(i)) * D; };
+    MemberState* const state = ONE ? nullptr : state_all + static_cast<size_t>(bh) * N + start;
+
+    // the rows of this lane's sixteen members of block b
+    const int mytok = tid < n ? tok(tid) : start;
+    C cache[CACHE];
+#pragma unroll
+    for (int k = 0; k < CACHE; ++k) {
+        const int t = LIST ? __shfl(mytok, lbase + k) : start + g16 + k;
+        cache[k].clear();
+        if (g16 + k < n) cache[k].load(Kb + static_cast<size_t>(t) * D + sub * E);
+    }
+    // f(k, chunk) for the sixteen rows of block b (k a compile-time index;
+    // rows past the last member are zero)
+    auto rows_of = [&](int b, auto&& f) {
+        auto stream = [&](int i0, int tk, auto first) {
+            constexpr int kFirst = decltype(first)::value;
+#pragma unroll
+            for (int k0 = kFirst; k0 < 16; k0 += BATCH) {
+                // addresses are formed anew for each batch (kept over the
+                // rounds they would take two registers per row), and a batch
+                // is used before the next is requested
+                asm volatile("" : "+v"(i0), "+v"(tk));
+                C x[BATCH];
+#pragma unroll
+                for (int k = 0; k < BATCH; ++k) {
+                    const int t = LIST ? __shfl(tk, lbase + k0 + k) : start + i0 + k0 + k;
+                    x[k].clear();
+                    if (i0 + k0 + k < n) x[k].load(Kb + static_cast<size_t>(t) * D + sub * E);
+                }
+#pragma unroll
+                for (int k = 0; k < BATCH; ++k) {
+                    x[k].opaque();
+                    f(k0 + k, x[k]);
                 }
             }
-            const double2 cc = *reinterpret_cast<const double2*>(c + j);
+        };
+        if (ONE || b == 0) {
 #pragma unroll
-            for (int k = 0; k < MPT; ++k) {
-                const double t0 = static_cast<double>(row[k].elem(j)) - cc.x;
-                dd[k] = dd[k] + t0 * t0;
-                const double t1 = static_cast<double>(row[k].elem(j + 1)) - cc.y;
-                dd[k] = dd[k] + t1 * t1;
+            for (int k = 0; k < CACHE; ++k) {
+                cache[k].opaque();
+                f(k, cache[k]);
             }
+            if constexpr (CACHE < 16) stream(g16, mytok, std::integral_constant<int, CACHE>{});
+        } else {
+            stream(b * nt + g16, b * nt + tid < n ? tok(b * nt + tid) : start, std::integral_constant<int, 0>{});
         }
     };
 
-    // first representative: the member nearest the mean
-    double dd[MPT];
-    distances(s_mean, dd);
-    ArgVal best{INFINITY, 0x7fffffff};
+    // squared norms (one per member; of the first block kept), the largest,
+    // and the sums of each dimension over the lane's rows
+    float nx0 = 0.f, nmax = 0.f;
+    bool odd = false;  // a norm that is not finite
+    {
+        double sums[E];
 #pragma unroll
-    for (int k = 0; k < MPT; ++k)
-        if (member[k]) best = pick_min(best, ArgVal{dd[k], tid + k * nt});
-    int rep = reg_block_arg<false>(best, s_red[0], nw).i;
-    if (rep >= n) rep = 0;  // no winner (NaN keys): stay inside the parent
-
-    // farthest-first rounds with a running minimum; a chosen representative
-    // gets -1 so that it is never chosen again.  Round u uses buffer
-    // (u + 1) & 1 of s_red (the mean used buffer 0): a buffer is rewritten
-    // two rounds after it was read, past both barriers of the round between.
-    // The new representative's owner stores its raw words to s_raw, and
-    // after the barrier every wave widens them into its own fp64 copy
-    // (wave-private, so no second barrier); s_raw is rewritten only after
-    // the round's reduction barrier, which every wave reaches after its
-    // widening.
-    double m[MPT];
-    int o[MPT];
+        for (int e = 0; e < E; ++e) sums[e] = 0.0;
+        for (int b = 0; b < nblk; ++b) {
+            float pp[16];
+            rows_of(b, [&](int k, const C& x) {
+                pp[k] = x.dot(x);
+                done(pp[k]);
 #pragma unroll
-    for (int k = 0; k < MPT; ++k) {
-        m[k] = 0.0;
-        o[k] = 0;
+                for (int e = 0; e < E; ++e) {
+                    sums[e] += static_cast<double>(x.elem(e));
+                    done(sums[e]);
+                }
+            });
+            const float nx = transpose_sum16(pp);
+            if (ONE)
+                nx0 = nx;
+            else if (b * nt + tid < n)
+                state[b * nt + tid].nx = nx;
+            odd = odd || !(nx <= kNormMax);
+            nmax = fmaxf(nmax, nx);
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            double s = sums[e];
+            s += __shfl_xor(s, 16);
+            s += __shfl_xor(s, 32);
+            if (lane < 16) s_part[w * D + sub * E + e] = s;
+        }
     }
-    for (int u = 0; u < r; ++u) {
-        const int b = (u + 1) & 1;
-        const int rk = rep / nt;
-        if (tid == rep - rk * nt) {
-            s_reps[u] = rep;
+    nmax = wave_max_f32(__ballot(odd) ? kInf : nmax);
+    if (lane == 0) s_best[w].x = nmax;
+    __syncthreads();
+    for (int v = 0; v < nw; ++v) nmax = fmaxf(nmax, s_best[v].x);
+    for (int j = tid; j < D; j += nt) {
+        double s = 0.0;
+        for (int v = 0; v < nw; ++v) s += s_part[v * D + j];
+        s_vec[j] = s / static_cast<double>(n);
+    }
+    if (tid == 0) s_misc[0] = 0;
+    __syncthreads();
+    bool exact = !(nmax >= kNormMin && nmax <= kNormMax);  // uniform
+    const float err2 = 2.f * kEstimate * nmax;
+
+    MemberState st;
+    st.reset();
+    st.nx = nx0;
+    int rep = 0;
+
+    // The members listed in s_ti (cnt <= kTie of them, s_tv preset to ~0):
+    // their running minima over the first nv representatives by the
+    // definition's distances, into s_tv; a (member, representative) pair per
+    // thread.
+    auto tie_minima = [&](int cnt, int nv) {
+        for (int e = tid; e < cnt * nv; e += nt) {
+            const int c = e / nv, v = e - c * nv;
+            const double d2 = sqdist_rows<T, D>(row(s_ti[c]), row(s_reps[v]));
+            atomicMin(&s_tv[c], static_cast<unsigned long long>(__double_as_longlong(d2)));
+        }
+    };
+
+    if (!exact) {
+        // first representative: the member nearest the mean
+        const int tid = fresh_tid(), lane = tid & (kWave - 1), w = tid / kWave;
+        float mean[E];
+        float mm = 0.f;
 #pragma unroll
-            for (int k = 0; k < MPT; ++k)
-                if (k == rk) row[k].store(reinterpret_cast<T*>(s_raw));
+        for (int e = 0; e < E; ++e) {
+            mean[e] = static_cast<float>(s_vec[sub * E + e]);
+            mm = fmaf(mean[e], mean[e], mm);
+        }
+        mm = row16_sum(mm);
+        float near = kInf, near2 = kInf;  // this thread's two smallest
+        int ni = 0;
+        for (int b = 0; b < nblk; ++b) {
+            float pp[16];
+            rows_of(b, [&](int k, const C& x) {
+                pp[k] = x.dot(mean);
+                if (k >= CACHE || !ONE) done(pp[k]);
+            });
+            const float dt = transpose_sum16(pp);
+            const int i = b * nt + tid;
+            if (i < n) {
+                const float nx = ONE ? nx0 : state[i].nx;
+                const float a = nx + mm - 2.f * dt;
+                near2 = fminf(near2, fmaxf(near, a));
+                if (a < near) {
+                    near = a;
+                    ni = i;
+                }
+            }
+        }
+        {
+            const float wm = -wave_max_f32(-near);
+            const uint64_t in = __ballot(near <= wm + err2 && near < kInf);
+            const uint64_t in2 = __ballot(near2 <= wm + err2 && near2 < kInf);
+            const uint64_t at = __ballot(near == wm);
+            const int idx = readlane(ni, at ? __ffsll(static_cast<unsigned long long>(at)) - 1 : 0);
+            if (lane == 0)
+                s_best[w] = make_float4(wm, __int_as_float(idx), __int_as_float(__popcll(in) > 1 || in2 != 0 ? 1 : 0), 0.f);
         }
         __syncthreads();
-        double* cw = s_cw[w];
-        RegRow<T, D>::widen(s_raw, cw, lane);
-        distances(cw, dd);
-        ArgVal far{-INFINITY, 0x7fffffff};
+        const float4 eb = s_best[min(lane, nw - 1)];
+        const float T0 = -wave_max_f32(lane < nw ? -eb.x : -kInf);
+        const uint64_t nearw = __ballot(lane < nw && eb.x <= T0 + err2);
+        const int wsel = __ffsll(static_cast<unsigned long long>(nearw)) - 1;
+        const bool alone = __popcll(nearw) == 1 && readlane(__float_as_int(eb.z), wsel) == 0;
+        rep = readlane(__float_as_int(eb.y), wsel);
+        if (!alone) {
+            // several members: their distances to the fp64 mean.  That mean's
+            // sums run in another order than the definition's, so the winner
+            // has to be clear of the others by the difference this can make;
+            // otherwise (equal rows, as a rule) the definition's own mean
+            // decides.
+            for (int b = 0; b < nblk; ++b) {
+                // (the estimates again: only a thread's smallest was kept)
+                float pp[16];
+                rows_of(b, [&](int k, const C& x) {
+                pp[k] = x.dot(mean);
+                if (k >= CACHE || !ONE) done(pp[k]);
+            });
+                const float dt = transpose_sum16(pp);
+                const int i = b * nt + tid;
+                if (i < n && (ONE ? nx0 : state[i].nx) + mm - 2.f * dt <= T0 + err2) {
+                    const int at = atomicAdd(&s_misc[0], 1);
+                    if (at < kTie) s_ti[at] = i;
+                }
+            }
+            __syncthreads();
+            const int cnt = s_misc[0];
+            if (cnt > kTie) {
+                exact = true;  // uniform
+            } else {
+                if (tid < cnt) s_tv[tid] = static_cast<unsigned long long>(__double_as_longlong(sqdist_to(row(s_ti[tid]), s_vec, D)));
+                __syncthreads();
+                ArgVal win{INFINITY, 0x7fffffff};
+                for (int c = 0; c < cnt; ++c)
+                    win = pick_min(win, ArgVal{__longlong_as_double(static_cast<long long>(s_tv[c])), s_ti[c]});
+                const double slack = static_cast<double>(n + 256) * 0x1.0p-49 * static_cast<double>(nmax);
+                bool clear = true;
+                for (int c = 0; c < cnt; ++c)
+                    clear = clear && (s_ti[c] == win.i || __longlong_as_double(static_cast<long long>(s_tv[c])) > win.v + slack);
+                rep = win.i;
+                if (!clear) {  // uniform
+                    __syncthreads();
+                    for (int j = tid; j < D; j += nt) {
+                        double s = 0.0;
+                        int i = 0;
+                        for (; i + 16 <= n; i += 16) {
+                            float x[16];
 #pragma unroll
-        for (int k = 0; k < MPT; ++k) {
-            const int i = tid + k * nt;
-            if (member[k]) {
-                if (u == 0 || dd[k] < m[k]) {
-                    m[k] = dd[k];
-                    o[k] = u;
+                            for (int q = 0; q < 16; ++q) x[q] = load_elem(row(i + q), j);
+#pragma unroll
+                            for (int q = 0; q < 16; ++q) s = s + static_cast<double>(x[q]);
+                        }
+                        for (; i < n; ++i) s = s + static_cast<double>(load_elem(row(i), j));
+                        s_vec[j] = s / static_cast<double>(n);
+                    }
+                    __syncthreads();
+                    if (tid < cnt) s_tv[tid] = static_cast<unsigned long long>(__double_as_longlong(sqdist_to(row(s_ti[tid]), s_vec, D)));
+                    __syncthreads();
+                    win = ArgVal{INFINITY, 0x7fffffff};
+                    for (int c = 0; c < cnt; ++c)
+                        win = pick_min(win, ArgVal{__longlong_as_double(static_cast<long long>(s_tv[c])), s_ti[c]});
+                    rep = win.i;
+                }
+            }
+            __syncthreads();
+            if (tid == 0) s_misc[0] = 0;
+        }
+    }
+
+    if (!exact) {
+        // farthest-first rounds.  Every wave publishes its farthest member
+        // (and, with one member per thread, that member's row), and after the
+        // round's one barrier each wave finds the workgroup's.  s_best and
+        // s_row alternate between two sets: a set is rewritten two rounds
+        // after it was read, past the barrier of the round between.
+        const int tid = fresh_tid(), lane = tid & (kWave - 1), w = tid / kWave;
+        C rc;
+        rc.load(row(rep) + sub * E);
+        float nr = row16_sum(rc.dot(rc));
+        for (int u = 0; u < r; ++u) {
+            if (tid == 0) s_reps[u] = rep;
+            float far = -kInf, far2 = -kInf;
+            int fi = 0;
+            for (int b = 0; b < nblk; ++b) {
+                float pp[16];
+                rows_of(b, [&](int k, const C& x) {
+                    pp[k] = x.dot(rc);
+                    if (k >= CACHE || !ONE) done(pp[k]);
+                });
+                const float dt = transpose_sum16(pp);
+                const int i = b * nt + tid;
+                if (i < n) {
+                    MemberState s = ONE ? st : state[i];
+                    if (u == 0) s.reset();
+                    s.add((ONE ? nx0 : s.nx) + nr - 2.f * dt, static_cast<uint32_t>(u));
+                    if (i == rep) s.choose(static_cast<uint32_t>(u));
+                    if (ONE)
+                        st = s;
+                    else
+                        state[i] = s;
+                    far2 = fmaxf(far2, fminf(far, s.m1));
+                    if (s.m1 > far) {
+                        far = s.m1;
+                        fi = i;
+                    }
+                }
+            }
+            if (u + 1 == r) break;
+            const int set = ((u + 1) & 1) * nw;  // (the first representative used set 0)
+            const float wm = wave_max_f32(far);
+            const uint64_t in = __ballot(far >= wm - err2 && far > -kInf);
+            const uint64_t in2 = ONE ? 0 : __ballot(far2 >= wm - err2 && far2 > -kInf);
+            const uint64_t at = __ballot(far == wm);
+            const int lsel = __ffsll(static_cast<unsigned long long>(at)) - 1;
+            const int idx = readlane(fi, lsel);
+            if (lane == 0)
+                s_best[set + w] = make_float4(wm, __int_as_float(idx), __int_as_float(__popcll(in) > 1 || in2 != 0 ? 1 : 0),
+                                              __int_as_float(readlane(__float_as_int(nx0), lsel)));
+            if constexpr (ONE) {
+                if ((lane >> 4) == (lsel >> 4)) {
+                    const int kk = lsel & 15;  // wave-uniform
+                    T* const dst = reinterpret_cast<T*>(s_row + (set + w) * D * static_cast<int>(sizeof(T))) + sub * E;
+                    if (kk < CACHE) {
+#pragma unroll
+                        for (int hi = 0; hi < CACHE; hi += 4) {
+                            if ((kk & ~3) != hi) continue;
+#pragma unroll
+                            for (int k = hi; k < hi + 4; ++k)
+                                if (k == kk) cache[k].store(dst);
+                        }
+                    } else if (idx < n) {
+                        C x;
+                        x.load(row(idx) + sub * E);
+                        x.store(dst);
+                    }
+                }
+            }
+            __syncthreads();
+            const float4 eb = s_best[set + min(lane, nw - 1)];
+            const float T0 = wave_max_f32(lane < nw ? eb.x : -kInf);
+            const uint64_t farw = __ballot(lane < nw && eb.x >= T0 - err2);
+            const int wsel = __ffsll(static_cast<unsigned long long>(farw)) - 1;
+            const bool alone = __popcll(farw) == 1 && readlane(__float_as_int(eb.z), wsel) == 0;
+            rep = readlane(__float_as_int(eb.y), wsel);
+            if (alone) {
+                if constexpr (ONE) {
+                    rc.load(reinterpret_cast<const T*>(s_row + (set + wsel) * D * static_cast<int>(sizeof(T))) + sub * E);
+                    nr = __int_as_float(readlane(__float_as_int(eb.w), wsel));
+                } else {
+                    rc.load(row(rep) + sub * E);
+                    nr = row16_sum(rc.dot(rc));
+                }
+                continue;
+            }
+            // several members within the bound: the definition's minima
+            for (int b = 0; b < nblk; ++b) {
+                const int i = b * nt + tid;
+                if (i < n) {
+                    const float m1 = ONE ? st.m1 : state[i].m1;
+                    if (m1 >= T0 - err2 && m1 > -kInf) {
+                        const int at = atomicAdd(&s_misc[0], 1);
+                        if (at < kTie) {
+                            s_ti[at] = i;
+                            s_tv[at] = ~0ull;
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+            const int cnt = s_misc[0];
+            if (cnt > kTie) {
+                exact = true;  // uniform
+                break;
+            }
+            tie_minima(cnt, u + 1);
+            __syncthreads();
+            ArgVal win{-INFINITY, 0x7fffffff};
+            for (int c = 0; c < cnt; ++c)
+                win = pick_max(win, ArgVal{__longlong_as_double(static_cast<long long>(s_tv[c])), s_ti[c]});
+            rep = win.i < n ? win.i : 0;
+            rc.load(row(rep) + sub * E);
+            nr = row16_sum(rc.dot(rc));
+            __syncthreads();  // s_ti and s_tv are rewritten by a later round
+            if (tid == 0) s_misc[0] = 0;
+        }
+    }
+    if (!exact) {
+        // owners the estimates leave open: the definition's distances to the
+        // two nearest representatives (to all where a third is as near)
+        const int tid = fresh_tid();
+        __syncthreads();
+        for (int b = 0; b < nblk; ++b) {
+            const int i = b * nt + tid;
+            if (i >= n) continue;
+            MemberState s = ONE ? st : state[i];
+            if (s.m1 > -kInf && s.m2 - s.m1 <= err2) {
+                int o = static_cast<int>(s.own & 0xffffu);
+                if (s.m3 - s.m1 <= err2) {
+                    double m = INFINITY;
+                    for (int v = 0; v < r; ++v) {
+                        const double d2 = sqdist_rows<T, D>(row(i), row(s_reps[v]));
+                        if (d2 < m) {
+                            m = d2;
+                            o = v;
+                        }
+                    }
+                } else {
+                    const int o1 = min(o, static_cast<int>(s.own >> 16)), o2 = max(o, static_cast<int>(s.own >> 16));
+                    const double d1 = sqdist_rows<T, D>(row(i), row(s_reps[o1]));
+                    const double d2 = sqdist_rows<T, D>(row(i), row(s_reps[o2]));
+                    o = d2 < d1 ? o2 : o1;
+                }
+                if (ONE)
+                    st.own = static_cast<uint32_t>(o);
+                else
+                    state[i].own = static_cast<uint32_t>(o);
+            }
+        }
+    } else {
+        // the definition's arithmetic throughout
+        const int tid = fresh_tid();
+        __syncthreads();
+        for (int j = tid; j < D; j += nt) {
+            double s = 0.0;
+            for (int i = 0; i < n; ++i) s = s + static_cast<double>(load_elem(row(i), j));
+            s_vec[j] = s / static_cast<double>(n);
+        }
+        __syncthreads();
+        ArgVal best{INFINITY, 0x7fffffff};
+        for (int i = tid; i < n; i += nt) best = pick_min(best, ArgVal{sqdist_to(row(i), s_vec, D), i});
+        best = block_arg<false>(best, s_red, nw);
+        // a reduction without a winner (NaN keys) falls back to member 0, so
+        // that every index stays inside the parent
+        rep = best.i < n ? best.i : 0;
+        for (int u = 0; u < r; ++u) {
+            if (tid == 0) s_reps[u] = rep;
+            for (int j = tid; j < D; j += nt) s_vec[j] = static_cast<double>(load_elem(row(rep), j));
+            __syncthreads();
+            // fold the new representative into the running minimum; a chosen
+            // representative gets -1 so that it is never chosen again
+            ArgVal far{-INFINITY, 0x7fffffff};
+            for (int b = 0; b < nblk; ++b) {
+                const int i = b * nt + tid;
+                if (i >= n) continue;
+                const double dd = sqdist_to(row(i), s_vec, D);
+                double m = dd;
+                int o = u;
+                if (u > 0) {
+                    const MemberState s = ONE ? st : state[i];
+                    m = s.exact();
+                    o = static_cast<int>(s.own);
+                    if (dd < m) {
+                        m = dd;
+                        o = u;
+                    }
                 }
                 if (i == rep) {
-                    m[k] = -1.0;
-                    o[k] = u;
+                    m = -1.0;
+                    o = u;
                 }
-                far = pick_max(far, ArgVal{m[k], i});
+                if (ONE)
+                    st.set_exact(m, o);
+                else
+                    state[i].set_exact(m, o);
+                far = pick_max(far, ArgVal{m, i});
+            }
+            if (u + 1 < r) {
+                far = block_arg<true>(far, s_red, nw);
+                rep = far.i < n ? far.i : 0;
             }
         }
-        if (u + 1 < r) {
-            rep = reg_block_arg<true>(far, s_red[b], nw).i;
-            if (rep >= n) rep = 0;
+    }
+    {
+        const int tid = fresh_tid();
+        const int lane = tid & (kWave - 1), w = tid / kWave, sub = tid & 15, g16 = tid & ~15, lbase = lane & 48;
+        auto owner = [&](int i) { return static_cast<int>((ONE ? st.own : state[i].own) & 0xffffu); };
+
+        // team sizes and offsets inside the parent
+        __syncthreads();
+        for (int u = tid; u < r; u += nt) s_cnt[u] = 0;
+        __syncthreads();
+        for (int i = tid; i < n; i += nt) atomicAdd(&s_cnt[owner(i)], 1);
+        __syncthreads();
+        for (int base = 0; base < r; base += nt) {
+            const int u = base + tid;
+            const int c = u < r ? s_cnt[u] : 0;
+            const int inc = wave_incl_scan(c);
+            if (lane == kWave - 1) s_misc[4 + w] = inc;
+            __syncthreads();
+            int pre = base > 0 ? s_off[base - 1] + s_cnt[base - 1] : 0;
+            for (int v = 0; v < w; ++v) pre += s_misc[4 + v];
+            if (u < r) s_off[u] = pre + inc - c;
+            __syncthreads();
         }
-    }
-    __syncthreads();
-
-    // team sizes and their exclusive scan (r <= blockDim.x: one team per
-    // thread)
-    for (int u = tid; u < r; u += nt) s_cnt[u] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < MPT; ++k)
-        if (member[k]) atomicAdd(&s_cnt[o[k]], 1);
-    __syncthreads();
-    for (int base = 0; base < r; base += nt) {
-        const int u = base + tid;
-        const int c = u < r ? s_cnt[u] : 0;
-        const int inc = wave_incl_scan(c);
-        if (lane == kWave - 1) s_wsum[w] = inc;
+        const size_t tbase = static_cast<size_t>(bh) * M + team0;
+        for (int u = tid; u < r; u += nt) {
+            team_begin[tbase + u] = start + s_off[u];
+            team_size[tbase + u] = s_cnt[u];
+            log_n[tbase + u] = log(static_cast<double>(s_cnt[u]));
+            rep_token[tbase + u] = tok(s_reps[u]);
+        }
         __syncthreads();
-        int pre = base > 0 ? s_off[base - 1] + s_cnt[base - 1] : 0;
-        for (int v = 0; v < w; ++v) pre += s_wsum[v];
-        if (u < r) s_off[u] = pre + inc - c;
-        __syncthreads();
-    }
-    const size_t tbase = static_cast<size_t>(bh) * M + team0;
-    for (int u = tid; u < r; u += nt) {
-        team_begin[tbase + u] = start + s_off[u];
-        team_size[tbase + u] = s_cnt[u];
-        log_n[tbase + u] = log(static_cast<double>(s_cnt[u]));
-        rep_token[tbase + u] = start + s_reps[u];
-    }
 
-    // packed position of each member: its team's offset plus its rank among
-    // the team's members in token order (slot k of wave v holds members
-    // k nt + 64 v ..), per block of 64 representatives with one ballot per
-    // representative, slot and wave
-    int* pperm = perm + static_cast<size_t>(bh) * N + start;
-    const uint64_t lt = lanemask_lt();
-    int pos[MPT];
-#pragma unroll
-    for (int k = 0; k < MPT; ++k) pos[k] = 0;
-    for (int ub = 0; ub < r; ub += kRankBlock) {
-        const int nb = min(kRankBlock, r - ub);
-        int rank_in_wave[MPT];
-#pragma unroll
-        for (int k = 0; k < MPT; ++k) {
-            const int ok = member[k] ? o[k] : -1;
-            rank_in_wave[k] = 0;
-            for (int q = 0; q < nb; ++q) {
-                const uint64_t bm = __ballot(ok == ub + q);
-                if (ok == ub + q) rank_in_wave[k] = __popcll(bm & lt);
-                if (lane == 0) s_wcnt[k][w][q] = __popcll(bm);
+        // packed position of each member: its team's offset plus its rank among
+        // the team's members in token order, per block of nt members and of 64
+        // representatives, one ballot per representative and wave
+        int* const pperm = perm + static_cast<size_t>(bh) * N + start;
+        const uint64_t lt = lanemask_lt();
+        int pos = 0;
+        for (int b = 0; b < nblk; ++b) {
+            const int i = b * nt + tid;
+            const int o = i < n ? owner(i) : -1;
+            for (int ub = 0; ub < r; ub += kRankBlock) {
+                const int nb = min(kRankBlock, r - ub);
+                int rank = 0;
+                for (int q = 0; q < nb; ++q) {
+                    const uint64_t bm = __ballot(o == ub + q);
+                    if (o == ub + q) rank = __popcll(bm & lt);
+                    if (lane == 0) s_wcnt[w * wstride + q] = __popcll(bm);
+                }
+                __syncthreads();
+                if (o >= ub && o < ub + nb) {
+                    int ps = s_off[o] + rank;
+                    for (int v = 0; v < w; ++v) ps += s_wcnt[v * wstride + o - ub];
+                    pperm[ps] = tok(i);
+                    pos = ps;
+                }
+                __syncthreads();
+                if (!ONE) {  // the next block's members follow
+                    for (int q = tid; q < nb; q += nt) {
+                        int add = 0;
+                        for (int v = 0; v < nw; ++v) add += s_wcnt[v * wstride + q];
+                        s_off[ub + q] += add;
+                    }
+                    __syncthreads();
+                }
             }
         }
-        __syncthreads();
+
+        // packed copies of a contiguous parent of one block: whole rows, sixteen
+        // lanes each, keys from the registers that hold them
+        if constexpr (ONE && !LIST) {
+            const size_t prow0 = static_cast<size_t>(bh) * N + start;
+            auto dst = [&](T* base, int k) { return base + (prow0 + __shfl(pos, lbase + k)) * D + sub * E; };
 #pragma unroll
-        for (int k = 0; k < MPT; ++k) {
-            const int ok = member[k] ? o[k] : -1;
-            if (ok >= ub && ok < ub + nb) {
-                int ps = s_off[ok] + rank_in_wave[k];
-                for (int kk = 0; kk < k; ++kk)
-                    for (int v = 0; v < nw; ++v) ps += s_wcnt[kk][v][ok - ub];
-                for (int v = 0; v < w; ++v) ps += s_wcnt[k][v][ok - ub];
-                pperm[ps] = start + tid + k * nt;
-                pos[k] = ps;
+            for (int k = 0; k < CACHE; ++k) {
+                T* const to = dst(packed_K, k);
+                if (g16 + k < n) cache[k].store(to);
+            }
+            // rows k0 .. 15 of src
+            auto copy = [&](const T* src, T* to, int k0) {
+#pragma unroll 1
+                for (; k0 < 16; k0 += 4) {
+                    C x[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (g16 + k0 + k < n) x[k].load(src + (prow0 + g16 + k0 + k) * D + sub * E);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        T* const p = dst(to, k0 + k);
+                        if (g16 + k0 + k < n) x[k].store(p);
+                    }
+                }
+            };
+            copy(K, packed_K, CACHE);
+            copy(V, packed_V, 0);
+            for (int e = tid; e < r * 16; e += nt) {
+                const int u = e >> 4, c = e & 15;
+                C x;
+                x.load(row(s_reps[u]) + c * E);
+                x.store(reps + (tbase + u) * D + c * E);
             }
         }
-        __syncthreads();
     }
+}
 
-    // packed copies: key rows from registers, value rows copied, and each
-    // team's representative key (its member's row, re-read from memory)
-    const size_t prow0 = static_cast<size_t>(bh) * N + start;
-#pragma unroll
-    for (int k = 0; k < MPT; ++k) {
-        if (member[k]) {
-            const size_t prow = prow0 + pos[k];
-            row[k].store(packed_K + prow * D);
-            const uint4* src = reinterpret_cast<const uint4*>(V + (prow0 + tid + k * nt) * D);
-            uint4* dst = reinterpret_cast<uint4*>(packed_V + prow * D);
-#pragma unroll
-            for (int c = 0; c < kChunks; ++c) dst[c] = src[c];
-        }
-    }
-    for (int c = tid; c < r * kChunks; c += nt) {
-        const int u = c / kChunks, q = c - u * kChunks;
-        reinterpret_cast<uint4*>(reps + (tbase + u) * D)[q] =
-            reinterpret_cast<const uint4*>(Kc + static_cast<size_t>(s_reps[u]) * D)[q];
-    }
+// Contiguous parents [pP, min(pP + P, N)); every pair has M teams.
+template <typename T, int D, bool ONE>
+__global__ __launch_bounds__(kBuildThreads) void k_build_contiguous(
+    const T* __restrict__ K, const T* __restrict__ V, int N, int P, int R, int M, MemberState* __restrict__ state,
+    int* __restrict__ team_begin, int* __restrict__ team_size, double* __restrict__ log_n,
+    int* __restrict__ rep_token, int* __restrict__ perm, T* __restrict__ packed_K, T* __restrict__ packed_V,
+    T* __restrict__ reps, int* __restrict__ team_count) {
+    extern __shared__ __align__(16) char s_build[];
+    const int p = blockIdx.x, bh = blockIdx.y, start = p * P;
+    if (p == 0 && threadIdx.x == 0) team_count[bh] = M;
+    build_parent<T, D, false, ONE>(K, V, N, R, M, bh, start, min(P, N - start), p * min(R, P), nullptr, state, team_begin,
+                                   team_size, log_n, rep_token, perm, packed_K, packed_V, reps, s_build);
+}
+
+// Label-defined parents: the members are the token indices mem[0 .. n)
+// (ascending) of the pair's member lists.
+template <typename T, int D>
+__global__ __launch_bounds__(kBuildThreads) void k_build_lists(
+    const T* __restrict__ K, int N, int R, int M, MemberState* __restrict__ state, int* __restrict__ team_begin,
+    int* __restrict__ team_size, double* __restrict__ log_n, int* __restrict__ rep_token, int* __restrict__ perm,
+    const int* __restrict__ members, const int* __restrict__ pbeg, const int* __restrict__ toff, int Mp) {
+    extern __shared__ __align__(16) char s_build[];
+    const int p = blockIdx.x, bh = blockIdx.y;
+    const size_t at = static_cast<size_t>(bh) * (Mp + 1) + p;
+    const int start = pbeg[at], n = pbeg[at + 1] - start;
+    if (n <= 0) return;  // empty parents are omitted (uniform over the workgroup)
+    const int* const mem = members + static_cast<size_t>(bh) * N + start;
+    if (n <= static_cast<int>(blockDim.x))  // uniform
+        build_parent<T, D, true, true>(K, nullptr, N, R, M, bh, start, n, toff[at], mem, state, team_begin, team_size,
+                                       log_n, rep_token, perm, nullptr, nullptr, nullptr, s_build);
+    else
+        build_parent<T, D, true, false>(K, nullptr, N, R, M, bh, start, n, toff[at], mem, state, team_begin, team_size,
+                                        log_n, rep_token, perm, nullptr, nullptr, nullptr, s_build);
 }
 
 // Row gather into team order: packed[bh][pos] = src[bh][perm[bh][pos]], and the
@@ -695,67 +947,58 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint4* __restrict__ s
 
 }  // namespace
 
-bool build_packs_in_place(int N, int d, santapp_dtype dtype, int P, int R) {
-    const int members = std::min(P, N);
-    return members <= 2 * kRegThreads && R <= kMaxReps &&
-           ((dtype == SANTAPP_BF16 && (d == 128 || d == 64)) || (dtype == SANTAPP_FP32 && d == 64));
-}
+size_t build_state_bytes() { return sizeof(MemberState); }
+
+// A parent of at most kBuildThreads members is one member per thread: its
+// state stays in registers and the workgroup writes the packed rows itself.
+bool build_packs_in_place(int N, int P) { return std::min(P, N) <= kBuildThreads; }
 
 hipError_t launch_build_parents(const void* K, const void* V, santapp_dtype dtype, int BH, int N,
-                                int d, int P, int R, int M, double* mind, int* owner,
+                                int d, int P, int R, int M, void* state,
                                 int* team_begin, int* team_size, double* log_n, int* rep_token,
                                 int* perm, void* packed_K, void* packed_V, void* reps, int* team_count,
-                                bool* packed, hipStream_t s) {
-    *packed = false;
+                                hipStream_t s) {
     const dim3 grid((N + P - 1) / P, BH);
-    // register-resident kernel where a parent fits 2 kRegThreads members and
-    // a row 64 registers (two members per thread above kRegThreads); the
-    // general kernel otherwise.  At least one thread per dimension: they sum
-    // the parent mean.
     const int members = std::min(P, N);
-    if (build_packs_in_place(N, d, dtype, P, R)) {
-        const int mpt = members > kRegThreads ? 2 : 1;
-        const int threads = std::max(d, ((members + mpt - 1) / mpt + kWave - 1) / kWave * kWave);
-#define SANTAPP_REGS(TT, DD)                                                                       \
-    do {                                                                                          \
-        auto kern = mpt == 1 ? k_build_parent_regs<TT, DD, 1> : k_build_parent_regs<TT, DD, 2>;  \
-        kern<<<grid, threads, 0, s>>>(static_cast<const TT*>(K), static_cast<const TT*>(V), N, P, R, \
-                                      M, team_begin, team_size, log_n, rep_token, perm,           \
-                                      static_cast<TT*>(packed_K), static_cast<TT*>(packed_V),    \
-                                      static_cast<TT*>(reps), team_count);                        \
-        *packed = true;                                                                           \
-        return hipGetLastError();                                                                 \
+    const int threads = std::min(kBuildThreads, (members + kWave - 1) / kWave * kWave);
+    const bool one = build_packs_in_place(N, P);
+    const int lds = build_lds(threads / kWave, R, d, dtype == SANTAPP_BF16 ? 2 : 4).total;
+#define SANTAPP_BUILD(TT, DD)                                                                        \
+    do {                                                                                            \
+        auto kern = one ? k_build_contiguous<TT, DD, true> : k_build_contiguous<TT, DD, false>;    \
+        kern<<<grid, threads, lds, s>>>(static_cast<const TT*>(K), static_cast<const TT*>(V), N, P, R, M, \
+                                        static_cast<MemberState*>(state), team_begin, team_size, log_n,   \
+                                        rep_token, perm, static_cast<TT*>(packed_K),               \
+                                        static_cast<TT*>(packed_V), static_cast<TT*>(reps), team_count);  \
+        return hipGetLastError();                                                                   \
     } while (0)
-        if (dtype == SANTAPP_BF16 && d == 128) SANTAPP_REGS(bf16_t, 128);
-        if (dtype == SANTAPP_BF16 && d == 64) SANTAPP_REGS(bf16_t, 64);
-        if (dtype == SANTAPP_FP32 && d == 64) SANTAPP_REGS(float, 64);
-#undef SANTAPP_REGS
-    }
-    if (dtype == SANTAPP_BF16)
-        k_build_parent<bf16_t, false, kBuildThreads><<<grid, kBuildThreads, 0, s>>>(
-            static_cast<const bf16_t*>(K), N, d, P, R, M, mind, owner, team_begin, team_size,
-            log_n, rep_token, perm, nullptr, nullptr, nullptr, 0, team_count);
-    else
-        k_build_parent<float, false, kBuildThreads><<<grid, kBuildThreads, 0, s>>>(
-            static_cast<const float*>(K), N, d, P, R, M, mind, owner, team_begin, team_size,
-            log_n, rep_token, perm, nullptr, nullptr, nullptr, 0, team_count);
-    return hipGetLastError();
+    if (dtype == SANTAPP_BF16 && d == 128) SANTAPP_BUILD(bf16_t, 128);
+    if (dtype == SANTAPP_BF16 && d == 64) SANTAPP_BUILD(bf16_t, 64);
+    if (dtype == SANTAPP_FP32 && d == 128) SANTAPP_BUILD(float, 128);
+    if (dtype == SANTAPP_FP32 && d == 64) SANTAPP_BUILD(float, 64);
+#undef SANTAPP_BUILD
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_build_parent_lists(const void* K, santapp_dtype dtype, int BH, int N, int d, int Mp,
                                      int R, int M, const int* members, const int* pbeg, const int* toff,
-                                     double* mind, int* owner, int* team_begin, int* team_size,
+                                     void* state, int* team_begin, int* team_size,
                                      double* log_n, int* rep_token, int* perm, hipStream_t s) {
     const dim3 grid(Mp, BH);
-    if (dtype == SANTAPP_BF16)
-        k_build_parent<bf16_t, true, kListBuildThreads><<<grid, kListBuildThreads, 0, s>>>(
-            static_cast<const bf16_t*>(K), N, d, 0, R, M, mind, owner, team_begin, team_size, log_n,
-            rep_token, perm, members, pbeg, toff, Mp, nullptr);
-    else
-        k_build_parent<float, true, kListBuildThreads><<<grid, kListBuildThreads, 0, s>>>(
-            static_cast<const float*>(K), N, d, 0, R, M, mind, owner, team_begin, team_size, log_n,
-            rep_token, perm, members, pbeg, toff, Mp, nullptr);
-    return hipGetLastError();
+    const int lds = build_lds(kBuildWaves, R, d, dtype == SANTAPP_BF16 ? 2 : 4).total;
+#define SANTAPP_LISTS(TT, DD)                                                                         \
+    do {                                                                                             \
+        k_build_lists<TT, DD><<<grid, kBuildThreads, lds, s>>>(                                     \
+            static_cast<const TT*>(K), N, R, M, static_cast<MemberState*>(state), team_begin, team_size, log_n, \
+            rep_token, perm, members, pbeg, toff, Mp);                                              \
+        return hipGetLastError();                                                                    \
+    } while (0)
+    if (dtype == SANTAPP_BF16 && d == 128) SANTAPP_LISTS(bf16_t, 128);
+    if (dtype == SANTAPP_BF16 && d == 64) SANTAPP_LISTS(bf16_t, 64);
+    if (dtype == SANTAPP_FP32 && d == 128) SANTAPP_LISTS(float, 128);
+    if (dtype == SANTAPP_FP32 && d == 64) SANTAPP_LISTS(float, 64);
+#undef SANTAPP_LISTS
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_gather_rows(const void* src, void* dst, const int* index, int BH, int rows_out,

@@ -116,19 +116,21 @@ DecodeLayout dense_layout(int B, int Hq, int Hkv, int N, int T, int d, int cus, 
 
 __host__ __device__ inline int chunk_count(int rows) { return (rows + kUnitRows - 1) / kUnitRows; }
 
-// Whether launch_build_parents takes the register-resident kernel (which
-// needs no per-token scratch and writes the packed copies itself).
-bool build_packs_in_place(int N, int d, santapp_dtype dtype, int P, int R);
+// Whether launch_build_parents writes the packed copies itself and needs no
+// member state.
+bool build_packs_in_place(int N, int P);
 
-// Team table of every parent, and team_count[bh] = M.  Where the
-// register-resident kernel runs it also writes the packed copies (packed_K,
-// packed_V, reps) and sets *packed; otherwise the caller gathers them from
-// perm and rep_token.
+// Bytes of member state per token of the team build.
+size_t build_state_bytes();
+
+// Team table of every contiguous parent, and team_count[bh] = M.  Where
+// build_packs_in_place, the packed copies too (state may be null); otherwise
+// the caller gathers them from perm and rep_token.
 hipError_t launch_build_parents(const void* K, const void* V, santapp_dtype dtype, int BH, int N,
-                                int d, int P, int R, int M, double* mind, int* owner,
+                                int d, int P, int R, int M, void* state,
                                 int* team_begin, int* team_size, double* log_n, int* rep_token,
                                 int* perm, void* packed_K, void* packed_V, void* reps, int* team_count,
-                                bool* packed, hipStream_t s);
+                                hipStream_t s);
 
 hipError_t launch_gather_rows(const void* src, void* dst, const int* index, int BH, int rows_out,
                               int rows_in, size_t row_bytes, hipStream_t s);
@@ -138,7 +140,7 @@ hipError_t launch_gather_rows(const void* src, void* dst, const int* index, int 
 // toff[bh (Mp+1) + u]; team_begin is a position in that member order.
 hipError_t launch_build_parent_lists(const void* K, santapp_dtype dtype, int BH, int N, int d, int Mp,
                                      int R, int M, const int* members, const int* pbeg, const int* toff,
-                                     double* mind, int* owner, int* team_begin, int* team_size,
+                                     void* state, int* team_begin, int* team_size,
                                      double* log_n, int* rep_token, int* perm, hipStream_t s);
 
 // k-means state of one (b, kv): smoothed batch inertia and its minimum, the
