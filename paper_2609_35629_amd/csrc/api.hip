@@ -29,6 +29,7 @@ struct santapp_teams {
     int* perm;
     int* team_count;  // [B*Hkv] teams of each pair (M for contiguous parents)
     void* block;      // the one device allocation every array above is carved from
+    size_t block_bytes;
     // cap[x]: the most attention chunks any x distinct teams of one (b, kv)
     // need (sum of their x largest chunk counts, maximum over (b, kv))
     std::vector<int> cap;
@@ -98,15 +99,138 @@ long long team_count(int N, int P, int R) {
     return (np - 1) * std::min<long long>(R, P) + std::min<long long>(R, last);
 }
 
-// Release device memory on clean-up paths, where a failure to free cannot be
-// reported any better than the error already being returned.
-void release(void* p) {
-    if (p) (void)hipFree(p);
+// Device blocks kept for the next table or preparation scratch of a similar
+// size.  A hipMalloc and a hipFree of a 68 MiB table take 40 and 260 us (and
+// at times a millisecond), more than the 75 us kernel that builds it.
+//   - A block is only given out again once nothing can still use it: release()
+//     waits for the whole device first, as hipFree does, so that a table may be
+//     destroyed under the same conditions as before; release_idle() is for
+//     scratch whose only stream the caller has waited for.
+//   - Bounded: at most kBlocks blocks and kBytes bytes over all devices; what
+//     does not fit is freed, the oldest first, and all of it is freed when an
+//     allocation fails.
+//   - Any thread may call; a block goes back to the device it came from.
+class BlockPool {
+   public:
+    // A block of at least `bytes` on the current device; its size in *got.
+    hipError_t acquire(void** p, size_t bytes, size_t* got) {
+        bytes = (bytes + kGrain - 1) / kGrain * kGrain;
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            int best = -1;
+            for (int i = 0; i < n_; ++i)
+                if (b_[i].dev == dev && b_[i].bytes >= bytes && b_[i].bytes <= bytes + bytes / 4 &&
+                    (best < 0 || b_[i].bytes < b_[best].bytes))
+                    best = i;
+            if (best >= 0) {
+                const Block x = take(best);
+                *p = x.p;
+                *got = x.bytes;
+                return hipSuccess;
+            }
+        }
+        e = hipMalloc(p, bytes);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            drop_all();
+            e = hipMalloc(p, bytes);
+        }
+        *got = bytes;
+        return e;
+    }
+
+    // Back to the pool once the device that holds p is idle.
+    void release(void* p, size_t bytes) {
+        if (!p) return;
+        int dev = 0, cur = 0;
+        hipPointerAttribute_t at;
+        bool idle = hipPointerGetAttributes(&at, p) == hipSuccess && hipGetDevice(&cur) == hipSuccess;
+        if (idle) {
+            dev = at.device;
+            if (dev != cur) idle = hipSetDevice(dev) == hipSuccess;
+            // hipFree's own wait for the device, on a block of no size to
+            // speak of (hipDeviceSynchronize would end a graph capture that
+            // another stream has in progress in relaxed mode; hipFree does not)
+            void* small = nullptr;
+            idle = idle && hipMalloc(&small, 256) == hipSuccess && hipFree(small) == hipSuccess;
+            if (dev != cur) (void)hipSetDevice(cur);
+        }
+        if (idle) {
+            keep(p, bytes, dev);
+        } else {
+            (void)hipGetLastError();
+            (void)hipFree(p);
+        }
+    }
+
+    // The same for a block of the current device that nothing uses any more.
+    void release_idle(void* p, size_t bytes) {
+        int dev = 0;
+        if (!p) return;
+        if (hipGetDevice(&dev) == hipSuccess)
+            keep(p, bytes, dev);
+        else
+            (void)hipFree(p);
+    }
+
+   private:
+    static constexpr int kBlocks = 16;
+    static constexpr size_t kBytes = size_t(1) << 30, kGrain = size_t(1) << 16;
+    struct Block {
+        void* p;
+        size_t bytes;
+        int dev;
+    };
+    std::mutex mu_;
+    Block b_[kBlocks];  // oldest first
+    int n_ = 0;
+    size_t held_ = 0;
+
+    Block take(int i) {
+        const Block x = b_[i];
+        for (int j = i + 1; j < n_; ++j) b_[j - 1] = b_[j];
+        --n_;
+        held_ -= x.bytes;
+        return x;
+    }
+    void keep(void* p, size_t bytes, int dev) {
+        Block out[kBlocks + 1];
+        int nout = 0;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            while (n_ > 0 && (n_ == kBlocks || held_ + bytes > kBytes)) out[nout++] = take(0);
+            if (bytes <= kBytes) {
+                b_[n_++] = Block{p, bytes, dev};
+                held_ += bytes;
+            } else {
+                out[nout++] = Block{p, bytes, dev};
+            }
+        }
+        for (int i = 0; i < nout; ++i) (void)hipFree(out[i].p);
+    }
+    void drop_all() {
+        Block out[kBlocks];
+        int nout = 0;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            while (n_ > 0) out[nout++] = take(0);
+        }
+        for (int i = 0; i < nout; ++i) (void)hipFree(out[i].p);
+    }
+};
+
+// Never destroyed: tables may outlive this library's static objects.
+BlockPool& pool() {
+    static BlockPool* const p = new BlockPool;
+    return *p;
 }
 
 void free_teams(santapp_teams* t) {
     if (!t) return;
-    release(t->block);
+    pool().release(t->block, t->block_bytes);
     delete t;
 }
 
@@ -147,9 +271,10 @@ hipError_t alloc_table(santapp_teams* t) {
     const size_t ob = c.take(BH * M * sizeof(int)), os = c.take(BH * M * sizeof(int));
     const size_t ol = c.take(BH * M * sizeof(double)), ot = c.take(BH * M * sizeof(int));
     const size_t op = c.take(BH * N * sizeof(int)), oc = c.take(BH * sizeof(int));
-    char* b = nullptr;
-    const hipError_t e = hipMalloc(reinterpret_cast<void**>(&b), c.off);
+    void* p = nullptr;
+    const hipError_t e = pool().acquire(&p, c.off, &t->block_bytes);
     if (e != hipSuccess) return e;
+    char* const b = static_cast<char*>(p);
     t->block = b;
     t->packed_K = b + oK;
     t->packed_V = b + oV;
@@ -316,11 +441,11 @@ santapp_status santapp_build_teams(const void* K, const void* V, int B, int Hkv,
     t->R = reps_per_parent;
     t->M = static_cast<int>(M);
     void* state = nullptr;
+    size_t state_bytes = 0;
     hipError_t e = alloc_table(t);
     const bool packed = build_packs_in_place(N, parent_size);
-    if (e == hipSuccess && !packed) e = hipMalloc(&state, BH * N * build_state_bytes());
+    if (e == hipSuccess && !packed) e = pool().acquire(&state, BH * N * build_state_bytes(), &state_bytes);
     if (e != hipSuccess) {
-        release(state);
         free_teams(t);
         (void)hipGetLastError();
         return fail(SANTAPP_ENOMEM, "device allocation failed: %s", hipGetErrorString(e));
@@ -342,14 +467,17 @@ santapp_status santapp_build_teams(const void* K, const void* V, int B, int Hkv,
         e = launch_gather_rows(K, t->reps, t->rep_token, static_cast<int>(BH), t->M, N, row, s);
     }
     if (e != hipSuccess) {
-        // a launch failed: nothing of this call is left queued that uses the
-        // buffers (hipFree waits for the device)
-        release(state);
+        // a launch failed: an earlier one of this call may still run, so the
+        // buffers go back through a wait for the device
+        pool().release(state, state_bytes);
         free_teams(t);
         return hip_fail(e, what);
     }
     const santapp_status st = finish_table(t, s, out);  // waits for the build
-    release(state);
+    if (st == SANTAPP_OK)
+        pool().release_idle(state, state_bytes);
+    else
+        pool().release(state, state_bytes);
     return st;
 }
 
@@ -413,8 +541,10 @@ santapp_status santapp_kmeans_parents(const void* K, int B, int Hkv, int N, int 
     if (s0 > N) s0 = N;
     const KmLayout L = kmeans_layout(static_cast<int>(BH), N, d, M, theta->batch_size, s0);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    char* ws = nullptr;
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(&ws), L.total);
+    void* block = nullptr;
+    size_t block_bytes = 0;
+    hipError_t e = pool().acquire(&block, L.total, &block_bytes);
+    char* const ws = static_cast<char*>(block);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SANTAPP_ENOMEM, "k-means scratch (%zu bytes): %s", L.total, hipGetErrorString(e));
@@ -450,8 +580,11 @@ santapp_status santapp_kmeans_parents(const void* K, int B, int Hkv, int N, int 
         e = hipMemcpyAsync(st.data(), ws + L.state, BH * sizeof(KmState), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
     }
-    release(ws);
-    if (e != hipSuccess) return hip_fail(e, what);
+    if (e != hipSuccess) {
+        pool().release(block, block_bytes);
+        return hip_fail(e, what);
+    }
+    pool().release_idle(block, block_bytes);  // the stream has been waited for
     if (num_parents) *num_parents = M;
     if (steps)
         for (size_t i = 0; i < BH; ++i) steps[i] = st[i].steps;
@@ -488,13 +621,15 @@ santapp_status santapp_build_teams_from_labels(const void* K, const void* V, int
     const size_t o_mem = sc.take(BH * N * sizeof(int)), o_pbeg = sc.take(BH * (Mp + 1) * sizeof(int));
     const size_t o_toff = sc.take(BH * (Mp + 1) * sizeof(int)), o_tcount = sc.take(BH * sizeof(int));
     const size_t o_bad = sc.take(sizeof(int)), o_state = sc.take(BH * N * build_state_bytes());
-    char* scratch = nullptr;
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(&scratch), sc.off);
+    void* block = nullptr;
+    size_t block_bytes = 0;
+    hipError_t e = pool().acquire(&block, sc.off, &block_bytes);
+    char* const scratch = static_cast<char*>(block);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SANTAPP_ENOMEM, "device allocation failed: %s", hipGetErrorString(e));
     }
-    auto cleanup = [&]() { release(scratch); };
+    auto cleanup = [&]() { pool().release(block, block_bytes); };
     int* members = reinterpret_cast<int*>(scratch + o_mem);
     int* pbeg = reinterpret_cast<int*>(scratch + o_pbeg);
     int* toff = reinterpret_cast<int*>(scratch + o_toff);
@@ -567,7 +702,10 @@ santapp_status santapp_build_teams_from_labels(const void* K, const void* V, int
         return hip_fail(e, what);
     }
     const santapp_status st = finish_table(t, s, out);  // waits for the build
-    cleanup();
+    if (st == SANTAPP_OK)
+        pool().release_idle(block, block_bytes);
+    else
+        cleanup();
     return st;
 }
 
