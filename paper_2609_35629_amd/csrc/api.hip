@@ -745,19 +745,18 @@ santapp_status santapp_teams_set_route_keys(santapp_teams* t, santapp_route_key 
 
 namespace {
 
-// KL workspace: phi, Y (unused by the diagnostic, written by the routing
-// kernel) and the per-team sums, each [B, Hq, M].
+// KL workspace: phi [B, Hq, M] and the sums of each stretch of packed rows
+// [B, Hq, kl_chunks(N)].
 struct KlLayout {
-    size_t phi, Y, part, total;
+    size_t phi, part, total;
 };
 
-KlLayout kl_layout(int B, int Hq, int M) {
-    const size_t n = static_cast<size_t>(B) * Hq * M;
+KlLayout kl_layout(int B, int Hq, int N, int M) {
+    const size_t n = static_cast<size_t>(B) * Hq;
     KlLayout L;
     L.phi = 0;
-    L.Y = align_up(L.phi + n * sizeof(double));
-    L.part = align_up(L.Y + n * sizeof(double));
-    L.total = align_up(L.part + n * kl_part_bytes());
+    L.part = align_up(L.phi + n * M * sizeof(double));
+    L.total = align_up(L.part + n * kl_chunks(N) * kl_part_bytes());
     return L;
 }
 
@@ -766,7 +765,7 @@ KlLayout kl_layout(int B, int Hq, int M) {
 santapp_status santapp_routing_kl_workspace_bytes(const santapp_teams* t, int Hq, size_t* bytes) {
     if (!t || !bytes) return fail(SANTAPP_EINVAL, "NULL argument");
     if (Hq < 1 || Hq % t->Hkv != 0) return fail(SANTAPP_EINVAL, "Hq must be a positive multiple of Hkv");
-    *bytes = kl_layout(t->B, Hq, t->M).total;
+    *bytes = kl_layout(t->B, Hq, t->N, t->M).total;
     return ok();
 }
 
@@ -778,7 +777,7 @@ santapp_status santapp_routing_kl(const santapp_teams* t, const float* q, int Hq
     if (Hq / t->Hkv > kMaxGroup) return fail(SANTAPP_ELIMIT, "%d query heads per KV head exceed %d", Hq / t->Hkv, kMaxGroup);
     if (!(scale >= 0.0) || !isfinite(scale)) return fail(SANTAPP_EINVAL, "scale must be finite and >= 0");
     if (scale == 0.0) scale = 1.0 / sqrt(static_cast<double>(t->d));
-    const KlLayout L = kl_layout(t->B, Hq, t->M);
+    const KlLayout L = kl_layout(t->B, Hq, t->N, t->M);
     if (!workspace || ws_bytes < L.total)
         return fail(SANTAPP_EWORKSPACE, "workspace of %zu bytes needed (got %zu)", L.total, ws_bytes);
     if (!aligned16(q) || !aligned16(kl) || !aligned16(workspace))
@@ -798,12 +797,11 @@ santapp_status santapp_routing_kl(const santapp_teams* t, const float* q, int Hq
     R.M = t->M;
     R.dtype = t->dtype;
     R.scale = scale;
-    hipError_t e = launch_route_phi(R, phi, reinterpret_cast<double*>(ws + L.Y), s);
+    hipError_t e = launch_route_phi(R, phi, s);
     if (e != hipSuccess) return hip_fail(e, "routing kernel");
     KlArgs A{};
     A.packed_K = t->packed_K;
     A.team_begin = t->team_begin;
-    A.team_size = t->team_size;
     A.log_n = t->log_n;
     A.q = q;
     A.phi = phi;

@@ -4,8 +4,9 @@
 //
 // k_team_centroid   the team mean as routing key (centroid-guided sampling)
 // k_team_repkey     the representative's key again (the table's default)
-// k_kl_team         per (query head, team): max, sum of e^(s - max) and of
-//                   e^(s - max) s over the team's prompt rows, fp64
+// k_kl_rows         per (query head, 256 packed rows): max, sum of e^(s - max),
+//                   of e^(s - max) s and of e^(s - max) r, fp64 (s the row's
+//                   score, r its team's routing score)
 // k_kl_merge        per query head: KL(p || q) from those sums and the
 //                   routing logits phi
 #include "common.h"
@@ -35,29 +36,58 @@ __device__ __forceinline__ void store_mean(bf16_t* p, double v) { p->bits = f64_
 __device__ __forceinline__ void store_mean(float* p, double v) { *p = static_cast<float>(v); }
 
 // Team means: thread j sums dimension j over the team's rows in packed
-// order (ascending token index), then divides by n_g.
+// order (ascending token index), then divides by n_g.  The order of the sum
+// is the definition's, so a team is one serial chain, and the largest team
+// bounds the launch (700 rows at the 32K prompt): 64 rows at a time are read
+// whole and passed through LDS, the next 64 in flight while these are added
+// (reading a column per thread, 8 rows at a time, took 37 us; 31 us now).
 template <typename T, int D>
 __global__ __launch_bounds__(D) void k_team_centroid(const T* __restrict__ packed_K,
                                                      const int* __restrict__ team_begin,
                                                      const int* __restrict__ team_size, int N, int M,
                                                      T* __restrict__ reps) {
 #pragma clang fp contract(off)
+    constexpr int kRows = 64;
+    constexpr int kChunks = D * static_cast<int>(sizeof(T)) / 16;  // 16-byte chunks of a row
+    constexpr int kPerPass = D / kChunks;                          // rows one load of the workgroup covers
+    constexpr int kLoads = kRows / kPerPass;
+    __shared__ __align__(16) T s_rows[kRows][D];
     const int g = blockIdx.x, bh = blockIdx.y, j = threadIdx.x;
     const size_t t = static_cast<size_t>(bh) * M + g;
     const int begin = team_begin[t], n = team_size[t];
-    const T* col = packed_K + (static_cast<size_t>(bh) * N + begin) * D + j;
-    double s = 0.0;
-    int i = 0;
-    for (; i + 8 <= n; i += 8) {  // eight loads in flight, then the adds in order
-        float v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = load_elem(col, static_cast<size_t>(i + k) * D);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) s = s + static_cast<double>(v[k]);
+    if (n <= 0) {  // an absent team keeps a zero key; its log n excludes it
+        store_mean(reps + t * D + j, 0.0);
+        return;
     }
-    for (; i < n; ++i) s = s + static_cast<double>(load_elem(col, static_cast<size_t>(i) * D));
-    // an absent team (no rows) keeps a zero key; its log n excludes it
-    store_mean(reps + t * D + j, n > 0 ? s / static_cast<double>(n) : 0.0);
+    const T* const first = packed_K + (static_cast<size_t>(bh) * N + begin) * D;
+    const int lr = j / kChunks, lc = j % kChunks;
+    // chunk lc of row i (rows past the team's last repeat it)
+    auto chunk = [&](int i) {
+        return reinterpret_cast<const u32x4_t*>(first + static_cast<size_t>(min(i, n - 1)) * D)[lc];
+    };
+    u32x4_t x[kLoads];
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k) x[k] = chunk(k * kPerPass + lr);
+    double s = 0.0;
+    for (int i0 = 0; i0 < n; i0 += kRows) {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) reinterpret_cast<u32x4_t*>(s_rows[k * kPerPass + lr])[lc] = x[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) x[k] = chunk(i0 + kRows + k * kPerPass + lr);
+        const int cnt = min(kRows, n - i0);
+        int i = 0;
+        for (; i + 16 <= cnt; i += 16) {
+            float v[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) v[k] = load_elem(&s_rows[i + k][0], j);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) s = s + static_cast<double>(v[k]);
+        }
+        for (; i < cnt; ++i) s = s + static_cast<double>(load_elem(&s_rows[i][0], j));
+    }
+    store_mean(reps + t * D + j, s / static_cast<double>(n));
 }
 
 // The representative's key: its packed row is found among the team's rows
@@ -87,101 +117,175 @@ __global__ __launch_bounds__(kWave) void k_team_repkey(const T* __restrict__ pac
 }
 
 struct KlPart {
-    double m;  // max score of the team's rows
+    double m;  // max score of the rows
     double z;  // sum of e^(s - m)
     double s;  // sum of e^(s - m) s
+    double r;  // sum of e^(s - m) r
 };
 
-// Add score x to a running (max, sum e^(s-max), sum e^(s-max) s).
-__device__ __forceinline__ void kl_push(double& m, double& z, double& sm, double x) {
-    if (x > m) {
-        const double c = exp(m - x);
-        z = z * c + 1.0;
-        sm = sm * c + x;
-        m = x;
-    } else {
-        const double e = exp(x - m);
-        z += e;
-        sm += e * x;
+// D / 4 consecutive elements of a row, one of four lanes' share of it.
+template <typename T, int D>
+struct Quarter {
+    static constexpr int E = D / 4;
+    static constexpr int V = E * static_cast<int>(sizeof(T)) / 16;
+    uint4 v[V];
+    __device__ __forceinline__ void load(const T* p) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[i] = reinterpret_cast<const uint4*>(p)[i];
     }
-}
-
-__device__ __forceinline__ void kl_combine(double& m, double& z, double& s, double m2, double z2, double s2) {
-    const double mm = fmax(m, m2);
-    if (mm == -INFINITY) return;
-    const double c1 = exp(m - mm), c2 = exp(m2 - mm);
-    z = z * c1 + z2 * c2;
-    s = s * c1 + s2 * c2;
-    m = mm;
-}
-
-// Eight consecutive elements of a row (16 bytes of bf16, 32 of fp32).
-__device__ __forceinline__ void load8(const bf16_t* p, float (&v)[8]) {
-    const uint4 w = *reinterpret_cast<const uint4*>(p);
-    const uint32_t x[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        v[2 * k] = bf16lo(x[k]);
-        v[2 * k + 1] = bf16hi(x[k]);
+    __device__ __forceinline__ float elem(int e) const {
+        constexpr int kPer = 16 / static_cast<int>(sizeof(T));
+        const uint4 x = v[e / kPer];
+        const int q = (e % kPer) * static_cast<int>(sizeof(T)) / 4;
+        const uint32_t w = q == 0 ? x.x : q == 1 ? x.y : q == 2 ? x.z : x.w;
+        if constexpr (sizeof(T) == 2)
+            return (e & 1) ? bf16hi(w) : bf16lo(w);
+        else
+            return __uint_as_float(w);
     }
-}
-
-__device__ __forceinline__ void load8(const float* p, float (&v)[8]) {
-    const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-}
-
-// One wave per (b, kv, team): lane l takes the team's rows l, l + 64, ...,
-// scores them for the G query heads of kv in fp64 and keeps each head's
-// running sums; the wave then combines its lanes.
-template <typename T, int D, int G>
-__global__ __launch_bounds__(kWave) void k_kl_team(const T* __restrict__ packed_K,
-                                                   const int* __restrict__ team_begin,
-                                                   const int* __restrict__ team_size,
-                                                   const float* __restrict__ q, int N, int M, int Hkv,
-                                                   int Hq, double scale, KlPart* __restrict__ part) {
-    __shared__ double s_q[G][D];
-    const int g = blockIdx.x, bh = blockIdx.y, lane = lane_id();
-    const int b = bh / Hkv, kv = bh - b * Hkv;
-    const float* qb = q + (static_cast<size_t>(b) * Hq + kv * G) * D;
-    for (int i = lane; i < G * D; i += kWave) s_q[i / D][i % D] = static_cast<double>(qb[i]);
-    __syncthreads();
-    const size_t t = static_cast<size_t>(bh) * M + g;
-    const int begin = team_begin[t], n = team_size[t];
-    double m[G], z[G], sm[G];
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-        m[h] = -INFINITY;
-        z[h] = 0.0;
-        sm[h] = 0.0;
-    }
-    for (int r = lane; r < n; r += kWave) {
-        const T* row = packed_K + (static_cast<size_t>(bh) * N + begin + r) * D;
-        double acc[G];
-#pragma unroll
-        for (int h = 0; h < G; ++h) acc[h] = 0.0;
-#pragma unroll 1
-        for (int j = 0; j < D; j += 8) {  // rolled: unrolling hoists every query read from LDS
-            float v[8];
-            load8(row + j, v);
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-#pragma unroll
-                for (int h = 0; h < G; ++h) acc[h] = fma(s_q[h][j + e], static_cast<double>(v[e]), acc[h]);
-        }
-#pragma unroll
-        for (int h = 0; h < G; ++h) kl_push(m[h], z[h], sm[h], scale * acc[h]);
-    }
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-        for (int off = kWave / 2; off > 0; off >>= 1)
-            kl_combine(m[h], z[h], sm[h], __shfl_xor(m[h], off), __shfl_xor(z[h], off), __shfl_xor(sm[h], off));
-        if (lane == 0) part[(static_cast<size_t>(b) * Hq + kv * G + h) * M + g] = KlPart{m[h], z[h], sm[h]};
-    }
-}
+};
 
 constexpr int kKlThreads = 256;
+constexpr int kKlWaves = kKlThreads / kWave;
+
+// The last team whose first row is at or before `row` (team_begin ascends and
+// starts at 0): the wave samples 64 teams of the range left at a time.
+__device__ __forceinline__ int team_of_row(const int* __restrict__ begin, int M, int row) {
+    int lo = 0, hi = M;
+    while (hi - lo > 1) {  // uniform
+        const int step = (hi - lo + kWave - 1) / kWave;
+        const int i = lo + lane_id() * step;
+        const uint64_t at = __ballot(i < hi && begin[min(i, M - 1)] <= row);
+        lo += (static_cast<int>(__popcll(at)) - 1) * step;
+        hi = min(hi, lo + step);
+        if (step == 1) break;
+    }
+    return lo;
+}
+
+// A wave takes 64 packed rows, whatever teams they belong to (a wave per team
+// waited for the largest team: 160 us at the 32K prompt, whose largest has
+// 700 rows; 21 us now).  The scores of 16 rows and the G <= 8 heads
+// are one 16 x 16 tile of v_mfma_f64_16x16x4_f64 (A: head i on lanes 16 c + i,
+// B: row j on lanes 16 c + j, each lane group c holding dims [c D / 4,
+// (c + 1) D / 4)); register q of the result is head 4 q + c of row j, so
+// registers 0 and 1 hold every head.  All rows are requested before the teams
+// are looked up.
+template <typename T, int D, int G>
+__global__ __launch_bounds__(kKlThreads) void k_kl_rows(const T* __restrict__ packed_K,
+                                                        const int* __restrict__ team_begin,
+                                                        const double* __restrict__ log_n,
+                                                        const float* __restrict__ q,
+                                                        const double* __restrict__ phi, int N, int M, int Hkv,
+                                                        int Hq, double scale, KlPart* __restrict__ part) {
+    using Q = Quarter<T, D>;
+    typedef double f64x4 __attribute__((ext_vector_type(4)));
+    __shared__ int s_team[kKlWaves][kWave];
+    __shared__ KlPart s_part[kKlWaves][8];
+    const int bh = blockIdx.y, lane = lane_id(), w = wave_id();
+    const int b = bh / Hkv, kv = bh - b * Hkv;
+    const int c = lane >> 4, j = lane & 15;
+    const int row0 = blockIdx.x * kKlThreads + w * kWave;
+    const T* const Kp = packed_K + static_cast<size_t>(bh) * N * D + c * Q::E;
+    Q rows[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) rows[t].load(Kp + static_cast<size_t>(min(row0 + 16 * t + j, N - 1)) * D);
+    float qv[Q::E];
+    {
+        const float* const qh = q + (static_cast<size_t>(b) * Hq + kv * G + min(j, G - 1)) * D + c * Q::E;
+#pragma unroll
+        for (int e = 0; e < Q::E; e += 4) {
+            const float4 x = *reinterpret_cast<const float4*>(qh + e);
+            qv[e] = x.x;
+            qv[e + 1] = x.y;
+            qv[e + 2] = x.z;
+            qv[e + 3] = x.w;
+        }
+    }
+
+    // the team of each of the wave's rows: marked at the teams' first rows,
+    // then a running maximum
+    const int* const begin = team_begin + static_cast<size_t>(bh) * M;
+    const int last = min(row0 + kWave, N) - 1;
+    int team = 0;
+    if (row0 < N) {  // uniform
+        const int g0 = team_of_row(begin, M, row0);
+        s_team[w][lane] = g0;
+        for (int g = g0 + 1 + lane;; g += kWave) {
+            const int first = g < M ? begin[g] : N;
+            if (first <= last) atomicMax(&s_team[w][first - row0], g);
+            if (__ballot(first <= last) != ~0ull) break;
+        }
+        team = s_team[w][lane];
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int o = __shfl_up(team, off);
+            if (lane >= off) team = max(team, o);
+        }
+    }
+    const double* const ln = log_n + static_cast<size_t>(bh) * M;
+    const size_t hq0 = static_cast<size_t>(b) * Hq + kv * G;
+    double rr[4][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int g = __shfl(team, 16 * t + j);
+        const double l = ln[g];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) rr[t][k] = phi[(hq0 + min(4 * k + c, G - 1)) * M + g] - l;
+    }
+
+    double sc[4][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < Q::E; ++e)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(qv[e]), static_cast<double>(rows[t].elem(e)),
+                                                       acc, 0, 0, 0);
+        sc[t][0] = scale * acc[0];
+        sc[t][1] = scale * acc[1];
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        double m = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (row0 + 16 * t + j < N) m = fmax(m, sc[t][k]);
+        m = fmax(m, dpp_f64<0x128>(m));
+        m = fmax(m, dpp_f64<0x124>(m));
+        m = fmax(m, dpp_f64<0x122>(m));
+        m = fmax(m, dpp_f64<0x121>(m));
+        double z = 0.0, s = 0.0, r = 0.0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (row0 + 16 * t + j < N) {
+                const double e = exp(sc[t][k] - m);
+                z += e;
+                s = fma(e, sc[t][k], s);
+                r = fma(e, rr[t][k], r);
+            }
+        }
+        z = row16_sum(z);
+        s = row16_sum(s);
+        r = row16_sum(r);
+        if (j == 0) s_part[w][4 * k + c] = KlPart{m, z, s, r};
+    }
+    __syncthreads();
+    const int h = threadIdx.x;
+    if (h < G) {
+        KlPart p{-INFINITY, 0.0, 0.0, 0.0};
+        for (int v = 0; v < kKlWaves; ++v) p.m = fmax(p.m, s_part[v][h].m);
+        for (int v = 0; v < kKlWaves; ++v) {
+            const KlPart x = s_part[v][h];
+            if (x.z == 0.0) continue;  // a wave past the last row
+            const double f = exp(x.m - p.m);
+            p.z += x.z * f;
+            p.s += x.s * f;
+            p.r += x.r * f;
+        }
+        part[(hq0 + h) * gridDim.x + blockIdx.x] = p;
+    }
+}
 
 template <bool kMax>
 __device__ double kl_block_reduce(double v, double* s_red) {
@@ -200,30 +304,25 @@ __device__ double kl_block_reduce(double v, double* s_red) {
 // KL(p || q) = E_p[s] - E_p[r] - LSE(s) + LSE(phi), with r_g = phi_g - log n_g
 // the routing score of team g (log q_i = r_g(i) - LSE(phi)).
 __global__ __launch_bounds__(kKlThreads) void k_kl_merge(const double* __restrict__ phi,
-                                                         const KlPart* __restrict__ part,
-                                                         const double* __restrict__ log_n, int M,
-                                                         int Hkv, int Hq, double* __restrict__ kl) {
+                                                         const KlPart* __restrict__ part, int M,
+                                                         int chunks, double* __restrict__ kl) {
     __shared__ double s_red[kKlThreads / kWave];
     const int bhq = blockIdx.x, tid = threadIdx.x;
-    const int b = bhq / Hq, hq = bhq - b * Hq, G = Hq / Hkv;
-    const int bh = b * Hkv + hq / G;
     const double* ph = phi + static_cast<size_t>(bhq) * M;
-    const KlPart* pt = part + static_cast<size_t>(bhq) * M;
-    const double* ln = log_n + static_cast<size_t>(bh) * M;
+    const KlPart* pt = part + static_cast<size_t>(bhq) * chunks;
     double pmax = -INFINITY, mmax = -INFINITY;
-    for (int g = tid; g < M; g += kKlThreads) {
-        pmax = fmax(pmax, ph[g]);
-        mmax = fmax(mmax, pt[g].m);
-    }
+    for (int g = tid; g < M; g += kKlThreads) pmax = fmax(pmax, ph[g]);
+    for (int i = tid; i < chunks; i += kKlThreads) mmax = fmax(mmax, pt[i].m);
     pmax = kl_block_reduce<true>(pmax, s_red);
     mmax = kl_block_reduce<true>(mmax, s_red);
     double ep = 0.0, Z = 0.0, S = 0.0, Rr = 0.0;
-    for (int g = tid; g < M; g += kKlThreads) {
-        ep += exp(ph[g] - pmax);
-        const double c = exp(pt[g].m - mmax);
-        Z += pt[g].z * c;
-        S += pt[g].s * c;
-        Rr += (ph[g] - ln[g]) * pt[g].z * c;
+    for (int g = tid; g < M; g += kKlThreads) ep += exp(ph[g] - pmax);
+    for (int i = tid; i < chunks; i += kKlThreads) {
+        const KlPart x = pt[i];
+        const double c = exp(x.m - mmax);
+        Z += x.z * c;
+        S += x.s * c;
+        Rr += x.r * c;
     }
     ep = kl_block_reduce<false>(ep, s_red);
     Z = kl_block_reduce<false>(Z, s_red);
@@ -249,12 +348,12 @@ hipError_t route_keys_d(const void* packed_K, const int* team_begin, const int* 
 template <typename T, int D>
 hipError_t kl_d(const KlArgs& a, hipStream_t s) {
     KlPart* part = static_cast<KlPart*>(a.part);
-    const dim3 grid(a.M, a.B * a.Hkv);
-#define SANTAPP_KL(GG)                                                                                \
-    case GG:                                                                                          \
-        k_kl_team<T, D, GG><<<grid, kWave, 0, s>>>(static_cast<const T*>(a.packed_K), a.team_begin,  \
-                                                   a.team_size, a.q, a.N, a.M, a.Hkv, a.Hq, a.scale, \
-                                                   part);                                             \
+    const dim3 grid(kl_chunks(a.N), a.B * a.Hkv);
+#define SANTAPP_KL(GG)                                                                                  \
+    case GG:                                                                                            \
+        k_kl_rows<T, D, GG><<<grid, kKlThreads, 0, s>>>(static_cast<const T*>(a.packed_K), a.team_begin, \
+                                                        a.log_n, a.q, a.phi, a.N, a.M, a.Hkv, a.Hq,     \
+                                                        a.scale, part);                                 \
         break
     switch (a.Hq / a.Hkv) {
         SANTAPP_KL(1); SANTAPP_KL(2); SANTAPP_KL(3); SANTAPP_KL(4);
@@ -264,13 +363,15 @@ hipError_t kl_d(const KlArgs& a, hipStream_t s) {
 #undef SANTAPP_KL
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_kl_merge<<<a.B * a.Hq, kKlThreads, 0, s>>>(a.phi, part, a.log_n, a.M, a.Hkv, a.Hq, a.kl);
+    k_kl_merge<<<a.B * a.Hq, kKlThreads, 0, s>>>(a.phi, part, a.M, kl_chunks(a.N), a.kl);
     return hipGetLastError();
 }
 
 }  // namespace
 
 size_t kl_part_bytes() { return sizeof(KlPart); }
+
+int kl_chunks(int N) { return (N + kKlThreads - 1) / kKlThreads; }
 
 hipError_t launch_route_keys(const void* packed_K, const int* team_begin, const int* team_size,
                              const int* rep_token, const int* perm, int BH, int N, int M, int d,

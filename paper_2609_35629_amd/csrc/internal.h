@@ -180,8 +180,7 @@ hipError_t launch_parent_lists(const int* labels, int BH, int N, int Mp, int R, 
 hipError_t launch_pad_teams(const int* team_count, int BH, int M, int N, int* team_begin, int* team_size,
                             double* log_n, int* rep_token, hipStream_t s);
 
-// Routing logits of the KL diagnostic (k_route): phi and Y for every
-// (b, h, team).
+// Routing logits of the KL diagnostic (k_route): phi of every (b, h, team).
 struct RouteArgs {
     const void* reps;       // [BH, M, d]
     const double* log_n;    // [BH, M]
@@ -189,10 +188,9 @@ struct RouteArgs {
     int B, Hkv, Hq, G, d, M;
     santapp_dtype dtype;
     double scale;
-    uint64_t seed, step;
 };
 
-hipError_t launch_route_phi(const RouteArgs& a, double* phi, double* Y, hipStream_t s);
+hipError_t launch_route_phi(const RouteArgs& a, double* phi, hipStream_t s);
 
 // Routing keys of a table: the team means (centroid) or the representatives'
 // keys, written to reps [BH, M, d].
@@ -203,11 +201,10 @@ hipError_t launch_route_keys(const void* packed_K, const int* team_begin, const 
 struct KlArgs {
     const void* packed_K;    // [BH, N, d]
     const int* team_begin;   // [BH, M]
-    const int* team_size;    // [BH, M]
     const double* log_n;     // [BH, M]
     const float* q;          // [B, Hq, d]
     const double* phi;       // [B, Hq, M] routing logits
-    void* part;              // [B, Hq, M] per-team sums (kl_part_bytes() each)
+    void* part;              // [B, Hq, kl_chunks(N)] sums (kl_part_bytes() each)
     double* kl;              // [B, Hq]
     int B, Hkv, Hq, N, M, d;
     santapp_dtype dtype;
@@ -215,8 +212,9 @@ struct KlArgs {
 };
 
 size_t kl_part_bytes();
+int kl_chunks(int N);
 
-// Per-team sums over the prompt rows, then KL(p || q) per query head.
+// Sums over the prompt rows, then KL(p || q) per query head.
 hipError_t launch_routing_kl(const KlArgs& a, hipStream_t s);
 
 // One decode step (sampled, or dense when `dense`): everything the kernels

@@ -126,3 +126,45 @@ def test_decode_with_centroid_keys():
     assert not cmp.unexcused
     assert cmp.max_phi_rel < 1e-10
     assert cmp.rel_l2.max() <= 1e-2
+
+
+@pytest.mark.parametrize("dtype,d,Hq,Hkv,N,P,R", [
+    ("bf16", 128, 3, 1, 257, 17, 3), ("bf16", 64, 16, 2, 1023, 64, 64), ("fp32", 128, 8, 1, 1000, 300, 5),
+    ("fp32", 64, 5, 1, 63, 100, 1), ("bf16", 128, 2, 2, 1, 4, 2), ("bf16", 64, 1, 1, 5000, 1, 1),
+])
+def test_routing_kl_ragged_shapes(dtype, d, Hq, Hkv, N, P, R):
+    # rows past the last 256, teams across its bounds and many teams in it
+    wl = datagen.WORKLOADS["qwen8k" if dtype == "bf16" else "tiny"].with_(
+        name="kl", d=d, N=N, P=P, R=R, Hq=Hq, Hkv=Hkv, T=0)
+    log(f"[gpu] routing KL {dtype} d={d} Hq={Hq} Hkv={Hkv} N={N} P={P} R={R}")
+    b = datagen.generate(wl)
+    db = dev_batch(b)
+    ot = oracle_teams(b)
+    teams = sp.build_teams(db.K, db.V, P, R)
+    for kind in ("representative", "centroid"):
+        sp.set_route_keys(teams, kind)
+        kl = sp.routing_kl(teams, db.q).cpu().numpy()
+        keys = _oracle_keys(b, ot, kind)
+        _check_keys(teams, b, keys)
+        for h in range(Hq):
+            kv = h // wl.G
+            ref = oracle.routing_kl(b.q[0, h], b.f64(b.K[0, kv]), ot[0][kv], keys[0][kv], wl.scale)
+            assert abs(kl[0, h] - ref) <= 1e-9 + 1e-9 * abs(ref), (kind, h, kl[0, h], ref)
+
+
+def test_routing_kl_absent_teams():
+    # pairs of unequal team counts: the absent teams' log n excludes them
+    wl = datagen.WORKLOADS["qwen8k"].with_(name="kl-lists", N=700, Hq=4, Hkv=2, T=0)
+    b = datagen.generate(wl)
+    db = dev_batch(b)
+    lab = np.random.default_rng(1).integers(0, 9, size=(1, 2, 700)).astype(np.int32)
+    lab[0, 1] = np.minimum(lab[0, 1], 3)
+    log("[gpu] routing KL with absent teams")
+    teams = sp.build_teams_from_labels(db.K, db.V, torch.from_numpy(lab).cuda(), 9, 4)
+    kl = sp.routing_kl(teams, db.q).cpu().numpy()
+    for h in range(4):
+        kv = h // 2
+        x = b.f64(b.K[0, kv])
+        t = oracle.build_teams_from_labels(x, lab[0, kv], 4)
+        ref = oracle.routing_kl(b.q[0, h], x, t, oracle.routing_keys(x, t, "representative", wl.dtype), wl.scale)
+        assert abs(kl[0, h] - ref) <= 1e-9 + 1e-9 * abs(ref), (h, kl[0, h], ref)
