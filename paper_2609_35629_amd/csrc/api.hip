@@ -322,6 +322,18 @@ void step_regions(DecodeLayout& L, size_t BH, int G, int M, int d, bool dense, s
     L.part = take(BH * L.maxwp * G * static_cast<size_t>(step_state_bytes(d)));
 }
 
+// A 64-bit value that no earlier call had and that memory holds only by a
+// chance of 2^-64: a counter through an invertible mixing of its bits
+// (Steele, Lea, Flood: SplitMix64).
+uint64_t call_token() {
+    static std::atomic<uint64_t> calls{0x5bf03635u};
+    uint64_t z = (calls.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull;
+    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+    z ^= z >> 31;
+    return z != 0 ? z : 1;
+}
+
 bool fused_wanted() { return launch_mode() == LaunchMode::kFused; }
 
 }  // namespace
@@ -340,8 +352,12 @@ int step_wgs(int cus, long long BH) {
     return static_cast<int>(BH * std::min<long long>(kStepMaxWgs, cus / BH));
 }
 
+bool fused_step(santapp_dtype dt, const DecodeLayout& L) {
+    return !L.step && dt == SANTAPP_BF16 && fused_wanted() && L.nwg % 8 == 0;
+}
+
 DecodeLayout decode_layout(int B, int Hq, int Hkv, int T, int d, int M, int Kp, const int* cap, int cus,
-                           santapp_dtype dt) {
+                           santapp_dtype dt, size_t ws_bytes) {
     DecodeLayout L;
     const size_t BH = static_cast<size_t>(B) * Hkv, BQ = static_cast<size_t>(B) * Hq;
     const int G = Hq / Hkv;
@@ -365,6 +381,18 @@ DecodeLayout decode_layout(int B, int Hq, int Hkv, int T, int d, int M, int Kp, 
     L.lc = c.take(BQ * M * sizeof(float));
     L.part = c.take(BH * L.maxwp * G * state_stride(d) * sizeof(float));
     L.total = c.off;
+    if (M > kDecodeThreads && !fused_step(dt, L)) {
+        DecodeLayout X = L;
+        X.keys = true;
+        X.kstride = (M + 3) / 4 * 4;
+        const size_t n = BQ * X.kstride;
+        X.yu = c.take(n * sizeof(uint32_t));
+        X.yk = c.take(n * sizeof(uint64_t));
+        X.phi = c.take(n * sizeof(double));
+        X.tokens = c.take(BH * key_blocks(M) * sizeof(uint64_t));
+        X.total = c.off;
+        if (X.total <= ws_bytes) return X;
+    }
     return L;
 }
 
@@ -847,7 +875,7 @@ santapp_status santapp_decode_launch_info(const santapp_teams* t, int Hq, int T,
     const DecodeLayout L = dense ? dense_layout(t->B, Hq, t->Hkv, t->N, T, t->d, t->cus, t->dtype)
                                  : decode_layout(t->B, Hq, t->Hkv, T, t->d, t->M, Kp, t->cap.data(), t->cus,
                                                  t->dtype);
-    const bool fused = !L.step && t->dtype == SANTAPP_BF16 && fused_wanted() && L.nwg % 8 == 0;
+    const bool fused = fused_step(t->dtype, L);
     *kernels = L.step || fused ? 1 : (dense ? 2 : 3);
     *workgroups = L.nwg;
     return ok();
@@ -898,7 +926,7 @@ santapp_status santapp_decode(const santapp_teams* t, const float* q, const void
     if (!dense && t->M > kMaxTeams) return fail(SANTAPP_ELIMIT, "%d teams per KV head exceed %d", t->M, kMaxTeams);
     const DecodeLayout L = dense ? dense_layout(t->B, Hq, t->Hkv, t->N, T, t->d, t->cus, t->dtype)
                                  : decode_layout(t->B, Hq, t->Hkv, T, t->d, t->M, Kp, t->cap.data(), t->cus,
-                                                 t->dtype);
+                                                 t->dtype, ws_bytes);
     if (!workspace || ws_bytes < L.total)
         return fail(SANTAPP_EWORKSPACE, "workspace of %zu bytes needed (got %zu)", L.total, ws_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -930,6 +958,7 @@ santapp_status santapp_decode(const santapp_teams* t, const float* q, const void
     A.scale_log2 = static_cast<float>(scale * 1.4426950408889634);
     A.seed = seed;
     A.step = step;
+    if (L.keys) A.token = call_token();
     A.lay = L;
     A.ws = static_cast<char*>(workspace);
     if (dbg) {
@@ -945,7 +974,7 @@ santapp_status santapp_decode(const santapp_teams* t, const float* q, const void
         A.ev_start = static_cast<hipEvent_t>(dbg->events[1]);
         A.ev_stop = static_cast<hipEvent_t>(dbg->events[2]);
     }
-    A.fused = t->dtype == SANTAPP_BF16 && fused_wanted() && L.nwg % 8 == 0;
+    A.fused = fused_step(t->dtype, L);
 
     hipError_t e;
     auto mark = [&](int i) -> hipError_t {
@@ -1011,6 +1040,8 @@ santapp_status santapp_decode_static(const santapp_teams* t, const float* q, con
     if (!t) return fail(SANTAPP_EINVAL, "teams is NULL");
     size_t need = 0;
     if (santapp_status st = santapp_decode_workspace_bytes(t, Hq, T, K, &need)) return st;
+    if (need > kStaticScratchBytes && K < t->M)  // the least that a sampled step takes
+        need = decode_layout(t->B, Hq, t->Hkv, T, t->d, t->M, K, t->cap.data(), t->cus, t->dtype, kStaticScratchBytes).total;
     if (need > kStaticScratchBytes)
         return fail(SANTAPP_ELIMIT, "this step needs %zu bytes of scratch; the static scratch holds %zu "
                     "(use santapp_decode with a workspace)", need, kStaticScratchBytes);
@@ -1064,7 +1095,7 @@ santapp_status santapp_dense_decode(const float* q, const void* K, const void* V
     A.scale_log2 = static_cast<float>(scale * 1.4426950408889634);
     A.lay = L;
     A.ws = static_cast<char*>(workspace);
-    A.fused = dtype == SANTAPP_BF16 && fused_wanted() && L.nwg % 8 == 0;
+    A.fused = fused_step(dtype, L);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (dbg) {  // the stage events only
         A.ev_start = static_cast<hipEvent_t>(dbg->events[1]);

@@ -117,6 +117,28 @@ struct RepChunk<float, 4> {
     }
 };
 
+// D / 4 consecutive elements of a row, one of four lanes' share of it.
+template <typename T, int D>
+struct Quarter {
+    static constexpr int E = D / 4;
+    static constexpr int V = E * static_cast<int>(sizeof(T)) / 16;
+    uint4 v[V];
+    __device__ __forceinline__ void load(const T* p) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[i] = reinterpret_cast<const uint4*>(p)[i];
+    }
+    __device__ __forceinline__ float elem(int e) const {
+        constexpr int kPer = 16 / static_cast<int>(sizeof(T));
+        const uint4 x = v[e / kPer];
+        const int q = (e % kPer) * static_cast<int>(sizeof(T)) / 4;
+        const uint32_t w = q == 0 ? x.x : q == 1 ? x.y : q == 2 ? x.z : x.w;
+        if constexpr (sizeof(T) == 2)
+            return (e & 1) ? bf16hi(w) : bf16lo(w);
+        else
+            return __uint_as_float(w);
+    }
+};
+
 // ---------------------------------------------------------------------------
 // Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11).  One round maps
 // (x0,x1,x2,x3) to (hi(M1 x2)^x1^k0, lo(M1 x2), hi(M0 x0)^x3^k1, lo(M0 x0));
@@ -182,6 +204,12 @@ __device__ __forceinline__ double gumbel_of_word(uint64_t w) {
 __device__ __forceinline__ uint64_t order_key(double y) {
     const uint64_t b = static_cast<uint64_t>(__double_as_longlong(y));
     return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
+
+// The same for a float.
+__device__ __forceinline__ uint32_t order_key(float y) {
+    const uint32_t b = __float_as_uint(y);
+    return (b >> 31) ? ~b : (b | 0x80000000u);
 }
 
 __device__ __forceinline__ double key_value(uint64_t k) {

@@ -840,6 +840,445 @@ __device__ void sample_head(const DecodeArgs& a, const Views& v, int p, int j, c
     __syncthreads();  // the LDS is reused by the next task
 }
 
+// ---------------------------------------------------------------------------
+// Sampling of larger tables (split launches): one launch routes all teams of
+// all pairs, and the last workgroup of a pair to finish selects for its heads.
+// ---------------------------------------------------------------------------
+struct KeyViews {
+    uint32_t* yu;      // [B Hq, kstride] order key of the perturbed score rounded to fp32
+    uint64_t* yk;      // [B Hq, kstride] its order key
+    double* phi;       // [B Hq, kstride]
+    uint64_t* arrive;  // [BH, workgroups of a pair] the call's token, once its scores are out
+};
+
+__device__ __forceinline__ KeyViews key_views(const DecodeArgs& a) {
+    return KeyViews{reinterpret_cast<uint32_t*>(a.ws + a.lay.yu), reinterpret_cast<uint64_t*>(a.ws + a.lay.yk),
+                    reinterpret_cast<double*>(a.ws + a.lay.phi), reinterpret_cast<uint64_t*>(a.ws + a.lay.tokens)};
+}
+
+// Maximum of an unsigned value over the wave (wave-uniform).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#define SANTAPP_MAXSTEP(CTRL) \
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, false)));
+    SANTAPP_MAXSTEP(0x128)
+    SANTAPP_MAXSTEP(0x124)
+    SANTAPP_MAXSTEP(0x122)
+    SANTAPP_MAXSTEP(0x121)
+#undef SANTAPP_MAXSTEP
+    const int x = static_cast<int>(v);
+    return max(max(static_cast<uint32_t>(readlane(x, 0)), static_cast<uint32_t>(readlane(x, 16))),
+               max(static_cast<uint32_t>(readlane(x, 32)), static_cast<uint32_t>(readlane(x, 48))));
+}
+
+// The value of rank `want` (0-based, descending) among x[0 .. R) of all lanes,
+// its lowest `drop` bits cleared (so at most that value): bit by bit below the
+// nonzero values' common prefix, counting the values at or above each
+// candidate.  0 when there are not that many nonzero values.  Wave-uniform.
+template <int R>
+__device__ __forceinline__ uint32_t wave_kth(const uint32_t (&x)[R], int want, int drop) {
+    auto at_least = [&](uint32_t c) __attribute__((always_inline)) {
+        int n = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) n += static_cast<int>(__popcll(__ballot(x[r] >= c)));
+        return n;
+    };
+    if (at_least(1u) <= want) return 0;
+    uint32_t hi = 0, lo = 0;  // the largest value, and the complement of the smallest nonzero one
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        hi = max(hi, x[r]);
+        lo = max(lo, x[r] != 0 ? ~x[r] : 0);
+    }
+    hi = wave_max_u32(hi);
+    lo = ~wave_max_u32(lo);
+    const int bits = hi == lo ? 0 : 32 - __clz(static_cast<int>(hi ^ lo));
+    uint32_t t = bits == 32 ? 0 : (hi >> bits) << bits;
+    for (int bit = bits - 1; bit >= drop; --bit) {
+        const uint32_t c = t | (1u << bit);
+        if (at_least(c) > want) t = c;
+    }
+    return drop > 0 ? (t >> drop) << drop : t;
+}
+
+constexpr int kTopList = 256;
+constexpr int kRouteTeamsWg = kKeyTeamsWg;  // teams of a routing workgroup
+static_assert(kRouteTeamsWg == 16 * kWaves, "sixteen teams a wave");
+
+// LDS of the sampling launch: the workgroup's Philox words, or per head of the
+// selection the upper halves of its teams' fp32 keys, the sampled teams' bits
+// and a list of teams.
+struct KeyLds {
+    int keys, bits, list, total;
+};
+__host__ __device__ inline KeyLds key_lds(int M, int G) {
+    const int Mr = (M + 511) / 512 * 512;  // the lists are scanned 512 teams at a time
+    KeyLds L;
+    L.keys = 0;
+    L.bits = L.keys + G * Mr * 2;
+    L.list = L.bits + G * (Mr / 32) * 4;
+    L.total = L.list + G * kTopList * 2;
+    const int words = G * kRouteTeamsWg * 8;
+    if (L.total < words) L.total = words;
+    return L;
+}
+
+// The selection of query head h = wave of pair p: tau, the perturbed score of
+// rank K, and the K teams above it (equal scores: the lower team).
+//   - The K-th largest of 256 maxima (four a lane, the low half of their fp32
+//     keys dropped) bounds tau from below; the teams at or above it, a few more
+//     than K, are listed in team order and ranked by their exact keys.
+//   - More than kTopList of them (K near or past 256): the fp32 key of rank K
+//     over all teams; the teams above it are taken, those equal to it listed.
+//   - More than kTopList of those (absent teams): their exact keys' differing
+//     bits are fixed one by one, from memory.
+// Every launch runs this code once, so its time is round trips and instruction
+// fetches: all keys are requested at once, and the loops over them stay rolled
+// (with the list's loop unrolled over keys in registers the launch took 31 us
+// instead of 24 us at 8192 teams).
+template <int KQ>
+__device__ void key_select(const DecodeArgs& a, const Views& v, int p, char* lds) {
+    const int lane = lane_id(), h = wave_id(), M = a.M, Kp = a.Kp;
+    const int b = p / a.Hkv, kv = p - b * a.Hkv;
+    const size_t bq = static_cast<size_t>(b) * a.Hq + kv * a.G + h, row = bq * a.lay.kstride;
+    const KeyViews kw = key_views(a);
+    // the scores come from other workgroups of this launch: coherent loads
+    const uint32_t ks = static_cast<uint32_t>(a.lay.kstride);
+    const __amdgpu_buffer_rsrc_t ru = coherent_rsrc(kw.yu + row, 4u * ks), rk = coherent_rsrc(kw.yk + row, 8u * ks),
+                                 rp = coherent_rsrc(kw.phi + row, 8u * ks);
+    auto key_of = [&](int g) __attribute__((always_inline)) {
+        const u32x2v w = load8_coherent(rk, 8u * static_cast<uint32_t>(g));
+        return (static_cast<uint64_t>(w.y) << 32) | w.x;
+    };
+    auto phi_of = [&](int g) __attribute__((always_inline)) {
+        const u32x2v w = load8_coherent(rp, 8u * static_cast<uint32_t>(g));
+        return __hiloint2double(static_cast<int>(w.y), static_cast<int>(w.x));
+    };
+    const KeyLds L = key_lds(M, a.G);
+    const int Mr = (M + 511) / 512 * 512, words = Mr / 32;
+    uint16_t* const yh = reinterpret_cast<uint16_t*>(lds + L.keys) + static_cast<size_t>(h) * Mr;
+    uint32_t* const bits = reinterpret_cast<uint32_t*>(lds + L.bits) + h * words;
+    uint16_t* const s_list = reinterpret_cast<uint16_t*>(lds + L.list) + h * kTopList;
+    for (int i = lane; i < words; i += kWave) bits[i] = 0;
+    const uint64_t lt = lanemask_lt();
+    auto take = [&](int g) __attribute__((always_inline)) { atomicOr(&bits[g >> 5], 1u << (g & 31)); };
+    // keys of teams g .. g + 3 (0 past the table)
+    auto load4 = [&](int g) __attribute__((always_inline)) {
+        u32x4v w = load16_coherent(ru, 4u * static_cast<uint32_t>(g));  // 0 past the row
+        w.x = g < M ? w.x : 0;
+        w.y = g + 1 < M ? w.y : 0;
+        w.z = g + 2 < M ? w.z : 0;
+        w.w = g + 3 < M ? w.w : 0;
+        return w;
+    };
+    uint32_t gm[4] = {0, 0, 0, 0};
+    {
+        u32x4v w[KQ];
+#pragma unroll
+        for (int i = 0; i < KQ; ++i) w[i] = load4(4 * (64 * i + lane));
+#pragma unroll
+        for (int i = 0; i < KQ; ++i) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) gm[e] = max(gm[e], w[i][e]);
+            const int g = 4 * (64 * i + lane);
+            if (g < Mr)
+                *reinterpret_cast<uint2*>(yh + g) =
+                    make_uint2((w[i].x >> 16) | (w[i].y & 0xffff0000u), (w[i].z >> 16) | (w[i].w & 0xffff0000u));
+        }
+    }
+    lds_order();
+    int n = kTopList + 1, want = Kp;
+    uint32_t t = 0;   // the listed teams' least key, or their key
+    bool up = false;  // teams were taken without a look at their exact keys
+    if (Kp < 4 * kWave) {  // uniform
+        // the teams whose upper half is at or above the bound's, in team order
+        const uint32_t t16 = wave_kth<4>(gm, Kp, 16) >> 16;
+        n = 0;
+#pragma unroll 1
+        for (int g0 = 0; g0 < Mr; g0 += 8 * kWave) {
+            const int g = g0 + 8 * lane;
+            const uint4 w = *reinterpret_cast<const uint4*>(yh + g);
+            const uint32_t y[4] = {w.x, w.y, w.z, w.w};
+            uint32_t in = 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) in |= ((y[e >> 1] >> (16 * (e & 1))) & 0xffffu) >= t16 && g + e < M ? 1u << e : 0u;
+            if (__ballot(in != 0) == 0) continue;  // uniform
+            const int mine = static_cast<int>(__popc(in)), inc = wave_incl_scan(mine);
+            int at = n + inc - mine;
+            for (; in != 0; in &= in - 1, ++at)
+                if (at < kTopList) s_list[at] = static_cast<uint16_t>(g + __ffs(static_cast<int>(in)) - 1);
+            n += readlane(inc, kWave - 1);
+        }
+    }
+    if (n > kTopList) {  // uniform
+        // f(g, keys of teams g .. g + 3)
+        auto each4 = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll 1
+            for (int g0 = 0; g0 < M; g0 += 32 * kWave) {
+                u32x4v w[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) w[i] = load4(g0 + 4 * (64 * i + lane));
+#pragma unroll
+                for (int i = 0; i < 8; ++i) f(g0 + 4 * (64 * i + lane), w[i]);
+            }
+        };
+        for (int bit = 31; bit >= 0; --bit) {
+            const uint32_t c = t | (1u << bit);
+            int cnt = 0;
+            each4([&](int, const u32x4v& w) __attribute__((always_inline)) {
+                cnt += (w.x >= c ? 1 : 0) + (w.y >= c ? 1 : 0) + (w.z >= c ? 1 : 0) + (w.w >= c ? 1 : 0);
+            });
+            if (wave_sum(cnt) > Kp) t = c;
+        }
+        up = true;
+        n = 0;
+        each4([&](int g, const u32x4v& w) __attribute__((always_inline)) {
+            bool in[4];
+            int above = 0, mine = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (w[e] > t) {  // past the table the key is 0
+                    take(g + e);
+                    ++above;
+                }
+                in[e] = g + e < M && w[e] == t;
+                mine += in[e] ? 1 : 0;
+            }
+            want -= wave_sum(above);
+            if (__ballot(mine != 0) == 0) return;  // uniform
+            const int inc = wave_incl_scan(mine);
+            int at = n + inc - mine;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (in[e]) {
+                    if (at < kTopList) s_list[at] = static_cast<uint16_t>(g + e);
+                    ++at;
+                }
+            }
+            n += readlane(inc, kWave - 1);
+        });
+    }
+    lds_order();
+    // rank `want` among the listed teams, by their exact keys
+    uint64_t tkey;
+    if (n <= kWave) {  // uniform: one a lane, ranked directly
+        const bool in = lane < n;
+        const int g = in ? s_list[lane] : 0;
+        const uint64_t k = in ? key_of(g) : 0;
+        const double ph = in ? phi_of(g) : 0.0;
+        int gt = 0, before = 0;  // greater keys; equal ones at lower teams
+        for (int i = 0; i < n; ++i) {
+            const uint64_t o = readlane(k, i);
+            gt += o > k ? 1 : 0;
+            before += o == k && i < lane ? 1 : 0;
+        }
+        const uint64_t at = __ballot(in && gt + before == want);
+        tkey = readlane(k, __ffsll(static_cast<unsigned long long>(at)) - 1);
+        if (in && gt + before < want) {
+            take(g);
+            if (!up) v.lc[bq * M + g] = log_inclusion(static_cast<float>(ph - key_value(tkey)));
+        }
+    } else if (n <= kTopList) {
+        constexpr int R = kTopList / kWave;
+        uint32_t hi[R], lo[R], same[R];
+        int g[R];
+        double ph[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = r * kWave + lane;
+            g[r] = i < n ? s_list[i] : 0;
+            const uint64_t k = i < n ? key_of(g[r]) : 0;
+            ph[r] = i < n ? phi_of(g[r]) : 0.0;
+            hi[r] = static_cast<uint32_t>(k >> 32);
+            lo[r] = static_cast<uint32_t>(k);
+        }
+        const uint32_t th = wave_kth<R>(hi, want, 0);
+        int need = want;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool in = r * kWave + lane < n;
+            need -= static_cast<int>(__popcll(__ballot(in && hi[r] > th)));
+            same[r] = in && hi[r] == th ? lo[r] : 0;
+        }
+        const uint32_t tl = wave_kth<R>(same, need, 0);
+        tkey = (static_cast<uint64_t>(th) << 32) | tl;
+        // then the first `need` of the keys equal to tau's
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            need -= static_cast<int>(__popcll(__ballot(r * kWave + lane < n && hi[r] == th && lo[r] > tl)));
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool in = r * kWave + lane < n;
+            const bool eq = in && hi[r] == th && lo[r] == tl;
+            const uint64_t be = __ballot(eq);
+            if (in && (hi[r] > th || (hi[r] == th && lo[r] > tl) || (eq && static_cast<int>(__popcll(be & lt)) < need))) {
+                take(g[r]);
+                if (!up) v.lc[bq * M + g[r]] = log_inclusion(static_cast<float>(ph[r] - key_value(tkey)));
+            }
+            need -= static_cast<int>(__popcll(be));
+        }
+    } else {
+        // the listed teams' keys in team order, 64 teams at a time
+        up = true;
+        auto each = [&](auto&& f) __attribute__((always_inline)) {
+            for (int g0 = 0; g0 < M; g0 += kWave) {
+                const int g = min(g0 + lane, M - 1);
+                f(g, g0 + lane < M && load_u32_coherent(kw.yu + row + g) == t, key_of(g));
+            }
+        };
+        uint64_t kand = ~0ull, kor = 0;
+        each([&](int, bool in, uint64_t k) {
+            if (in) {
+                kand &= k;
+                kor |= k;
+            }
+        });
+        kand = wave_and64(kand);
+        kor = wave_or64(kor);
+        tkey = kand;
+        for (uint64_t diff = kand ^ kor; diff != 0;) {
+            const uint64_t bit = 1ull << (63 - __clzll(static_cast<long long>(diff)));
+            const uint64_t c = tkey | bit;
+            int cnt = 0;
+            each([&](int, bool in, uint64_t k) { cnt += static_cast<int>(__popcll(__ballot(in && k >= c))); });
+            if (cnt > want) tkey = c;
+            diff &= ~bit;
+        }
+        int need = want;
+        each([&](int, bool in, uint64_t k) { need -= static_cast<int>(__popcll(__ballot(in && k > tkey))); });
+        each([&](int g, bool in, uint64_t k) {
+            const uint64_t be = __ballot(in && k == tkey);
+            if (in && (k > tkey || (k == tkey && static_cast<int>(__popcll(be & lt)) < need))) take(g);
+            need -= static_cast<int>(__popcll(be));
+        });
+    }
+    lds_order();
+    // the sample words, and log c of the teams that have none yet
+    const double tau = key_value(tkey);
+    for (int i = lane; i < a.lay.swords; i += kWave) {
+        const uint64_t w = (static_cast<uint64_t>(bits[2 * i + 1]) << 32) | bits[2 * i];
+        v.sbits[bq * a.lay.swords + i] = w;
+        if (up) {
+            for (uint64_t x = w; x != 0; x &= x - 1) {
+                const int g = 64 * i + __ffsll(static_cast<unsigned long long>(x)) - 1;
+                v.lc[bq * M + g] = log_inclusion(static_cast<float>(phi_of(g) - tau));
+            }
+        }
+    }
+    if (lane == 0 && a.dbg_tau) a.dbg_tau[bq] = tau;
+    if (a.dbg_sel || a.dbg_logc) {  // the sample in ascending team order
+        int rank = 0;
+        for (int g0 = 0; g0 < M; g0 += kWave) {
+            const int g = min(g0 + lane, M - 1);
+            const bool in = g0 + lane < M && ((bits[g >> 5] >> (g & 31)) & 1u);
+            const uint64_t bal = __ballot(in);
+            const int r = rank + static_cast<int>(__popcll(bal & lt));
+            if (in && r < Kp) {
+                if (a.dbg_sel) a.dbg_sel[bq * Kp + r] = g;
+                if (a.dbg_logc) a.dbg_logc[bq * Kp + r] = log_inclusion(static_cast<float>(phi_of(g) - tau));
+            }
+            rank += static_cast<int>(__popcll(bal));
+        }
+    }
+}
+
+// A workgroup takes kRouteTeamsWg teams of a pair, a wave 16 of them: phi of
+// every head (16 x 16 tiles of v_mfma_f64_16x16x4_f64: A head i on lanes
+// 16 c + i, B team j on lanes 16 c + j, lane group c holding dims [c D / 4,
+// (c + 1) D / 4); result register q of lane 16 c + j is head 4 q + c of team
+// j), the workgroup's Philox blocks one a thread, and on the result's lanes the
+// Gumbel variates and keys.  The pair's last workgroup (dispatched after the
+// others, which wait for nothing) waits until all have left the call's token,
+// clears the tokens for the next call (a replayed graph brings the same one)
+// and selects, one wave per head.  What a workspace held before cannot be
+// taken for the 64-bit token, so it needs no state between calls.
+//
+// One workgroup per query head, which read its pair's keys at 25 GB/s and had
+// the whole table's noise to draw, took 84 us at 8192 teams (four pairs of
+// seven heads) and 25 us at 2048 (sixteen pairs); this takes 24 and 18 us.  At 512
+// teams and fewer the former (8 us, one launch less deep) is as fast.
+template <typename T, int D, int KQ>
+__global__ __launch_bounds__(kThreads, 1) void k_route_select(DecodeArgs a) {
+    using Q = Quarter<T, D>;
+    typedef double f64x4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) char s_keys[];
+    uint64_t(*const s_word)[kRouteTeamsWg] = reinterpret_cast<uint64_t(*)[kRouteTeamsWg]>(s_keys);
+    __shared__ int s_ok;
+    const int tid = threadIdx.x, lane = lane_id(), c = lane >> 4, j = lane & 15;
+    const int p = blockIdx.y, b = p / a.Hkv, kv = p - b * a.Hkv, G = a.G, M = a.M;
+    const int g0 = blockIdx.x * kRouteTeamsWg, t = wave_id() * 16 + j;
+    const int g = min(g0 + t, M - 1);
+    const size_t tg = static_cast<size_t>(p) * M + g;
+    Q row;
+    row.load(static_cast<const T*>(a.reps) + tg * D + c * Q::E);
+    const float* const qh = a.q + (static_cast<size_t>(b) * a.Hq + kv * G + min(j, G - 1)) * D + c * Q::E;
+    float qv[Q::E];
+#pragma unroll
+    for (int e = 0; e < Q::E; e += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(qh + e);
+        qv[e] = x.x;
+        qv[e + 1] = x.y;
+        qv[e + 2] = x.z;
+        qv[e + 3] = x.w;
+    }
+    const double ln = a.log_n[tg];
+    // the Philox block at counter (g / 4, h, b, step), key (seed, 0), holds the
+    // words of teams 4 (g / 4) .. + 3
+    constexpr int kBlocks = kRouteTeamsWg / 4;
+    for (int i = tid; i < G * kBlocks; i += kThreads) {
+        const int h = i / kBlocks, q = i - h * kBlocks;
+        const u64x4 r = philox4x64_10(static_cast<uint64_t>(g0 / 4 + q), static_cast<uint64_t>(kv * G + h),
+                                      static_cast<uint64_t>(b), a.step, a.seed, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s_word[h][4 * q + e] = r.v[e];
+    }
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < Q::E; ++e)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(qv[e]), static_cast<double>(row.elem(e)), acc, 0, 0, 0);
+    __syncthreads();
+    const KeyViews kw = key_views(a);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int h = 4 * k + c;
+        if (h < G && g0 + t < M) {
+            const size_t bq = static_cast<size_t>(b) * a.Hq + kv * G + h, o = bq * a.lay.kstride + g;
+            const double phi = ln + a.scale * acc[k], y = phi + gumbel_of_word(s_word[h][t]);
+            store_u32_coherent(kw.yu + o, order_key(static_cast<float>(y)));
+            store_u64_coherent(kw.yk + o, order_key(y));
+            store_u64_coherent(kw.phi + o, static_cast<unsigned long long>(__double_as_longlong(phi)));
+            if (a.dbg_phi) a.dbg_phi[bq * M + g] = phi;
+            if (a.dbg_Y) a.dbg_Y[bq * M + g] = y;
+        }
+    }
+    drain_and_sync();
+    uint64_t* const arrive = kw.arrive + static_cast<size_t>(p) * gridDim.x;
+    if (tid == 0) store_u64_coherent(arrive + blockIdx.x, a.token);
+    if (blockIdx.x + 1 != gridDim.x) return;  // uniform
+    if (tid < kWave) {
+        bool here = false;
+        for (int it = 0; it < kSpinLimit; ++it) {
+            here = true;
+            for (int i = lane; i < static_cast<int>(gridDim.x); i += kWave)
+                here = here && load_u64_coherent(arrive + i) == a.token;
+            if (__ballot(!here) == 0) break;  // uniform
+            __builtin_amdgcn_s_sleep(2);
+        }
+        const uint64_t missing = __ballot(!here);
+        for (int i = lane; i < static_cast<int>(gridDim.x); i += kWave) store_u64_coherent(arrive + i, 0);
+        if (lane == 0) s_ok = missing == 0 ? 1 : 0;
+    }
+    __syncthreads();
+    const Views v = views_of(a);
+    if (wave_id() >= G) return;
+    if (s_ok != 0) {
+        key_select<KQ>(a, v, p, s_keys);
+    } else {  // a wait that ran out: the head's output becomes NaN
+        const size_t bq = static_cast<size_t>(b) * a.Hq + kv * G + wave_id();
+        for (int i = lane; i < a.lay.swords; i += kWave) v.sbits[bq * a.lay.swords + i] = i == 0 ? 1 : 0;
+        if (lane == 0) v.lc[bq * M] = __builtin_nanf("");
+    }
+}
+
 // Scores of one 16-row tile.  Lane l = 16 c + j feeds row j of the tile and
 // holds head 4 c + r of row j in accumulator register r (M rows 8 .. 15 repeat
 // heads 0 .. 7, so lane groups 2 and 3 repeat the states of groups 0 and 1).
@@ -1169,6 +1608,67 @@ __device__ __forceinline__ bool walk_units(const DecodeArgs& a, const Views& v, 
     if (FUSED) run(0, nsuf, by_index, true);
     const int tid = threadIdx.x, M = a.M;
     const size_t tb0 = static_cast<size_t>(p) * M;
+    if constexpr (!FUSED && PT > 1) {
+        // Larger tables: the union's teams are listed first (PT teams of the
+        // table per thread), then planned one a thread, so that only they read
+        // their size and begin and a pass is as full as the union allows.
+        // 8192 teams, K = 32: 12.6 us; sizes and begins of every team, sixteen a
+        // thread, 27 us.
+        static_assert(PT <= 32 && 64 % PT == 0, "a thread's teams lie in one sample word");
+        const int b = p / a.Hkv, kv = p - b * a.Hkv, g0 = tid * PT;
+        uint32_t f[kMaxGroup], any = 0;
+#pragma unroll
+        for (int h = 0; h < kMaxGroup; ++h) {
+            f[h] = 0;
+            if (h < a.G && g0 < M) {
+                const size_t hq = static_cast<size_t>(b) * a.Hq + kv * a.G + h;
+                f[h] = static_cast<uint32_t>(v.sbits[hq * a.lay.swords + (g0 >> 6)] >> (g0 & 63)) &
+                       static_cast<uint32_t>((1ull << PT) - 1);
+            }
+            any |= f[h];
+        }
+        const int mine[1] = {static_cast<int>(__popc(any))};
+        int slot[1], total[1];
+        block_scan<1>(mine, slot, total, P.w);
+        // the listed teams (team | heads << 16) lie where the records will be:
+        // they are read before plan_records' first barrier
+        int* const s_team = reinterpret_cast<int*>(P.rec);
+        int run_u = nsuf, run_rows = 0, base = 0;
+        do {
+            int at = slot[0] - base;
+            for (uint32_t x = any; x != 0; x &= x - 1) {
+                const int k = __ffs(static_cast<int>(x)) - 1;
+                if (at >= 0 && at < kPlanRecs) {
+                    int m = 0;
+#pragma unroll
+                    for (int h = 0; h < kMaxGroup; ++h) m |= static_cast<int>((f[h] >> k) & 1u) << h;
+                    s_team[at] = (g0 + k) | (m << 16);
+                }
+                ++at;
+            }
+            __syncthreads();
+            const bool in = base + tid < total[0];
+            const int e = in ? s_team[tid] : 0, g = e & 0xffff;
+            int hm[1] = {e >> 16}, sz[1] = {0}, bg[1] = {0};
+            if (in) {
+                sz[0] = a.team_size[tb0 + g];
+                bg[0] = a.team_begin[tb0 + g];
+            }
+            const int3 t = plan_records<1>(g, M, hm, sz, bg, P, a.dbg_urows != nullptr);
+            const int lo = base == 0 ? 0 : run_u, first = run_u;
+            run(lo, run_u + t.y,
+                [&](int u) { return u < first ? by_index(u) : plan_unit<T>(a, P, p, u - first, t.x, t.y); }, false);
+            run_u += t.y;
+            run_rows += t.z;
+            base += kPlanRecs;
+            if (base < total[0]) __syncthreads();  // the records are rewritten by the next pass
+        } while (base < total[0]);
+        if (iw == 0 && tid == 0) {
+            if (a.dbg_uteams) a.dbg_uteams[p] = total[0];
+            if (a.dbg_urows) a.dbg_urows[p] = run_rows;
+        }
+        return true;
+    }
     int sz[PT], bg[PT];
     auto fetch = [&](int base) {
 #pragma unroll
@@ -2762,17 +3262,17 @@ __device__ __forceinline__ void attend_pair(const DecodeArgs& a, const Views& v,
 }
 
 // Phase B and C for every pair this workgroup serves: pair w mod BH (or the
-// pairs w, w + grid, ... when there are more pairs than workgroups).  The
-// plan passes cover HK teams per thread when the heads' union fits one
-// pass's records (G K <= kPlanRecs), else one team per thread.
+// pairs w, w + grid, ... when there are more pairs than workgroups).  In the
+// fused launch the plan passes cover HK teams per thread when the heads' union
+// fits one pass's records (G K <= kPlanRecs), else one team per thread.
 template <typename T, int D, int HK, bool DENSE, bool FUSED>
 __device__ __forceinline__ void attend_all(const DecodeArgs& a, const Views& v, char* t0, char* t1, char* misc) {
     const int w = blockIdx.x, nwg = gridDim.x;
     const int BH = a.B * a.Hkv;
     auto one = [&](int p, int iw, int nwp) {
-        if (HK > 1 && !DENSE && static_cast<long long>(a.G) * a.Kp <= kPlanRecs)
+        if (HK > 1 && !DENSE && (!FUSED || static_cast<long long>(a.G) * a.Kp <= kPlanRecs))
             attend_pair<T, D, DENSE, FUSED, HK>(a, v, p, iw, nwp, t0, t1, misc);
-        else
+        else if constexpr (HK == 1 || DENSE || FUSED)
             attend_pair<T, D, DENSE, FUSED, 1>(a, v, p, iw, nwp, t0, t1, misc);
     };
     if (BH <= nwg) {
@@ -2862,7 +3362,15 @@ hipError_t decode_sampled(const DecodeArgs& a, hipStream_t s) {
         return hipErrorInvalidValue;
     }
     const int tasks = 8 * ((BH + 7) / 8) * a.G;
-    hipError_t e = launch_one(a, k_decode<T, D, HK, kSample, false>, tasks, false, s);
+    hipError_t e;
+    if (a.lay.keys) {
+        if constexpr (HK == 1) return hipErrorInvalidValue;
+        else hipLaunchKernelGGL((k_route_select<T, D, 2 * HK>), dim3(key_blocks(a.M), BH), dim3(kThreads),
+                                key_lds(a.M, a.G).total, s, a);
+        e = hipGetLastError();
+    } else {
+        e = launch_one(a, k_decode<T, D, HK, kSample, false>, tasks, false, s);
+    }
     if (e == hipSuccess) e = launch_one(a, k_decode<T, D, HK, kAttend, false>, a.lay.nwg, true, s);
     if (e == hipSuccess) e = launch_merge<D>(a, s);
     return e;

@@ -123,28 +123,6 @@ struct KlPart {
     double r;  // sum of e^(s - m) r
 };
 
-// D / 4 consecutive elements of a row, one of four lanes' share of it.
-template <typename T, int D>
-struct Quarter {
-    static constexpr int E = D / 4;
-    static constexpr int V = E * static_cast<int>(sizeof(T)) / 16;
-    uint4 v[V];
-    __device__ __forceinline__ void load(const T* p) {
-#pragma unroll
-        for (int i = 0; i < V; ++i) v[i] = reinterpret_cast<const uint4*>(p)[i];
-    }
-    __device__ __forceinline__ float elem(int e) const {
-        constexpr int kPer = 16 / static_cast<int>(sizeof(T));
-        const uint4 x = v[e / kPer];
-        const int q = (e % kPer) * static_cast<int>(sizeof(T)) / 4;
-        const uint32_t w = q == 0 ? x.x : q == 1 ? x.y : q == 2 ? x.z : x.w;
-        if constexpr (sizeof(T) == 2)
-            return (e & 1) ? bf16hi(w) : bf16lo(w);
-        else
-            return __uint_as_float(w);
-    }
-};
-
 constexpr int kKlThreads = 256;
 constexpr int kKlWaves = kKlThreads / kWave;
 

@@ -51,11 +51,19 @@ __host__ __device__ inline int state_stride(int d) { return d + 4; }
 // call publishes carries the tag epoch + 1, so words left by earlier calls are
 // never taken for this call's; the workspace must be zero before its first
 // use and needs no reset between calls.
+//
+// Split launches of more than 512 teams (`keys`) add per (query head, team) the
+// order key of the perturbed score in fp32 (`yu`) and fp64 (`yk`) and phi
+// (`phi`), rows of kstride teams, and a word per workgroup of the sampling
+// launch (`tokens`) that a workgroup sets to the call's token; nothing of these
+// outlives the sampling launch.
 struct DecodeLayout {
     int nwg = 0, maxwp = 0, swords = 0;
-    bool step = false;
+    bool step = false, keys = false;
     size_t ctr = 0, sbits = 0, lc = 0, part = 0, total = 0;
     size_t epoch = 0, xk = 0;
+    int kstride = 0;
+    size_t yu = 0, yk = 0, phi = 0, tokens = 0;
 };
 
 // Bytes of one published state of the single-launch step: d / 2 + 1 chunks
@@ -71,6 +79,11 @@ bool step_mode(santapp_dtype dt, int d, long long BH, int M, int Kp, bool dense,
 // kStepMaxWgs, one per compute unit at most; a multiple of eight per pair where
 // the compute units allow it, so that each pair spans all eight XCDs.
 int step_wgs(int cus, long long BH);
+
+// Teams of a workgroup of the sampling launch that keeps scores in memory, and
+// its workgroups per (b, kv) pair.
+constexpr int kKeyTeamsWg = 128;
+constexpr int key_blocks(int M) { return (M + kKeyTeamsWg - 1) / kKeyTeamsWg; }
 
 // Workgroup w of an attention grid of nwg workgroups serving BH (b, kv)
 // pairs (BH <= nwg): its pair p, its index iw among the pair's workgroups and
@@ -109,9 +122,13 @@ __host__ __device__ inline int pair_wgs(int p, int nwg, int BH) {
 int decode_wgs(int cus, long long BH, long long units_per_pair);
 
 // cap: host table with cap[x] = most units any x distinct teams of one
-// (b, kv) can need (x = 0 .. M).
+// (b, kv) can need (x = 0 .. M).  ws_bytes: the workspace at hand (SIZE_MAX:
+// as much as the step likes); a workspace too small for the scores of every
+// (head, team) takes the sampling kernel that keeps them on chip.
 DecodeLayout decode_layout(int B, int Hq, int Hkv, int T, int d, int M, int Kp, const int* cap, int cus,
-                           santapp_dtype dt);
+                           santapp_dtype dt, size_t ws_bytes = SIZE_MAX);
+// Whether SANTAPP_DECODE_LAUNCH asks for the fused launch and this step has one.
+bool fused_step(santapp_dtype dt, const DecodeLayout& L);
 DecodeLayout dense_layout(int B, int Hq, int Hkv, int N, int T, int d, int cus, santapp_dtype dt);
 
 __host__ __device__ inline int chunk_count(int rows) { return (rows + kUnitRows - 1) / kUnitRows; }
@@ -237,6 +254,7 @@ struct DecodeArgs {
     double scale;            // softmax scale (routing in fp64)
     float scale_log2;        // scale log2(e) (attention logits, base-2 exponentials)
     uint64_t seed, step;
+    uint64_t token;          // of this call (lay.keys)
     DecodeLayout lay;
     char* ws;                // workspace base
     // optional diagnostics (device pointers, each may be null)
