@@ -296,34 +296,138 @@ __global__ __launch_bounds__(kPickThreads) void k_kpp_pick(
     if (tid < L) cand[bh * L + tid] = s_first[tid];
 }
 
-// Nearest center of 64 points per workgroup against center tiles of 32 in
-// LDS.  Thread (pg, cg) = (tid / 16, tid % 16) scores points 4 pg .. 4 pg + 3
-// against tile centers 2 cg, 2 cg + 1; rows are padded to D + 1 doubles so
-// that the 16 center rows and the 4 point rows a wave reads per dimension sit
-// in distinct banks.
+// |x - c|^2 of a staged point (fp32, exact values) and a center, the
+// definition's way: fp64 in dimension order, no fused multiply-add.
+template <int D>
+__device__ __forceinline__ double point_dist(const float* x, const double* __restrict__ c) {
+#pragma clang fp contract(off)
+    double acc = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < D; k += 32) {  // 32 dimensions in flight
+        double2 v[16];
+        float xs[32];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v[q] = reinterpret_cast<const double2*>(c + k)[q];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float4 y = reinterpret_cast<const float4*>(x + k)[q];
+            xs[4 * q] = y.x;
+            xs[4 * q + 1] = y.y;
+            xs[4 * q + 2] = y.z;
+            xs[4 * q + 3] = y.w;
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const double t0 = static_cast<double>(xs[2 * q]) - v[q].x;
+            acc = acc + t0 * t0;
+            const double t1 = static_cast<double>(xs[2 * q + 1]) - v[q].y;
+            acc = acc + t1 * t1;
+        }
+    }
+    return acc;
+}
+
+// A point's three smallest estimated distances and the centers of the first
+// two.
+struct Near3 {
+    float d1, d2, d3;
+    int u1, u2;
+    __device__ __forceinline__ void add(float d, int u) {
+        const bool first = d < d1, second = d < d2;
+        d3 = fminf(d3, fmaxf(d2, d));
+        d2 = fminf(d2, fmaxf(d1, d));
+        d1 = fminf(d1, d);
+        u2 = first ? u1 : second ? u : u2;
+        u1 = first ? u : u1;
+    }
+    // with the lane CTRL (a DPP row rotation) away
+    template <int CTRL>
+    __device__ __forceinline__ void merge() {
+        const float o1 = dpp_f32<CTRL>(d1), o2 = dpp_f32<CTRL>(d2), o3 = dpp_f32<CTRL>(d3);
+        const int w1 = __builtin_amdgcn_update_dpp(0, u1, CTRL, 0xF, 0xF, false);
+        const int w2 = __builtin_amdgcn_update_dpp(0, u2, CTRL, 0xF, 0xF, false);
+        add(o1, w1);
+        add(o2, w2);
+        d3 = fminf(d3, o3);
+    }
+};
+
+// Maximum of a float over the wave (wave-uniform).
+__device__ __forceinline__ float wave_fmax(float v) {
+    v = fmaxf(v, dpp_f32<0x128>(v));
+    v = fmaxf(v, dpp_f32<0x124>(v));
+    v = fmaxf(v, dpp_f32<0x122>(v));
+    v = fmaxf(v, dpp_f32<0x121>(v));
+    const int x = __float_as_int(v);
+    return fmaxf(fmaxf(__int_as_float(readlane(x, 0)), __int_as_float(readlane(x, 16))),
+                 fmaxf(__int_as_float(readlane(x, 32)), __int_as_float(readlane(x, 48))));
+}
+
+// Nearest center of 64 points per workgroup.  The centers are compared on fp32
+// estimates |c|^2 - 2 x.c, center tiles of 32 in LDS: a wave's 16 points
+// against 16 centers as one tile of v_mfma_f32_16x16x4_f32 (A point i on lanes
+// 16 c + i, B center j on lanes 16 c + j, lane group c holding dims [c D / 4,
+// (c + 1) D / 4); register r of lane 16 c + j is point 4 c + r, center j).  The
+// definition's fp64 distance is then formed for the nearest center (the batch
+// inertia sums it) and, where the estimates of the two nearest lie within the
+// error bound, for the second; a point with a third that close, or whose
+// estimates left fp32's range, is compared with every center that way.
+//
+// Error bound: an inner product rounds at most five times per product step and
+// D / 4 <= 32 steps, each by at most 2^-23 of |x| |c|; with the norms' own
+// sums and the centers' rounding an estimate is off by less than 700 x 2^-24
+// (|x| |c| + |c|^2).
+//
+// With fp64 distances to all centers a step took 23.2 us (32 centers, 4096
+// points, four pairs, d = 128, bf16) and the labels of 32K tokens 82 us; now
+// 15.2 and 41 us, one workgroup per CU and a chain of latencies: the draw, the
+// rows, the estimates, one fp64 distance, the sort by center and the sums.
 template <typename T, int D, bool FINAL>
 __global__ __launch_bounds__(kAsgThreads) void k_km_assign(
     const T* __restrict__ K, int N, int M, int batch, int step, uint64_t seed,
     const double* __restrict__ cent, const KmState* __restrict__ state, int* __restrict__ labels,
     double* __restrict__ bpart, int* __restrict__ bcnt, double* __restrict__ binert) {
 #pragma clang fp contract(off)
-    __shared__ float s_x[kAsgPts][D + 1];  // exact key values
-    __shared__ double s_c[kAsgCen][D + 1];
+    constexpr int S = D + 4;  // row stride: whole 16-byte reads, rows spread over the banks
+    __shared__ __align__(16) float s_x[kAsgPts][S];  // exact key values
+    __shared__ __align__(16) float s_c[kAsgCen][S];  // centers rounded to fp32
+    __shared__ __align__(16) double s_cd[FINAL ? 1 : kAsgCen][D + 2];  // the first tile's centers as they are
     __shared__ int s_tok[kAsgPts];
     __shared__ int s_lab[kAsgPts];
     __shared__ double s_e[kAsgPts];
     __shared__ int s_ord[kAsgPts];
+    __shared__ Near3 s_near[kAsgPts];
+    __shared__ double s_second[kAsgPts];
+    __shared__ float s_err[kAsgThreads / kWave];  // twice a wave's error bound; negative: all zero
+    __shared__ int s_full, s_list[kAsgPts];
     const int bh = blockIdx.y, tid = threadIdx.x;
     if (!FINAL && state[bh].stop) return;
     const T* X = K + static_cast<size_t>(bh) * N * D;
     const int npts = FINAL ? N : batch;
     const int p0 = blockIdx.x * kAsgPts;
+    const double* cb = cent + static_cast<size_t>(bh) * M * D;
+    // a tile's centers (rows past the last center read center 0 and are not
+    // compared), the first tile's requested before the points are drawn
+    static_assert(kAsgCen * D % (4 * kAsgThreads) == 0, "whole tile quads per thread");
+    constexpr int kQuads = kAsgCen * D / (4 * kAsgThreads);
+    double2 cv0[kQuads], cv1[kQuads];
+    auto load_tile = [&](int ct) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < kQuads; ++q) {
+            const int e = q * kAsgThreads + tid, u = e / (D / 4), k = 4 * (e % (D / 4));
+            const double2* src = reinterpret_cast<const double2*>(cb + static_cast<size_t>(ct + u < M ? ct + u : 0) * D + k);
+            cv0[q] = src[0];
+            cv1[q] = src[1];
+        }
+    };
+    load_tile(0);
     if (tid < kAsgPts) {
         const int j = p0 + tid;
         int tok = -1;
         if (j < npts) tok = FINAL ? j : draw_index(km_word(seed, static_cast<uint64_t>(j), 3, static_cast<uint64_t>(step)), N);
         s_tok[tid] = tok;
     }
+    if (tid == 0) s_full = 0;
     __syncthreads();
     // point rows, 16 bytes per load: every load of a thread is independent
     {
@@ -344,90 +448,149 @@ __global__ __launch_bounds__(kAsgThreads) void k_km_assign(
             const int p = e / (D / kPer), k0 = (e % (D / kPer)) * kPer;
             const bool ok = s_tok[p] >= 0;
 #pragma unroll
-            for (int r = 0; r < kPer; ++r) s_x[p][k0 + r] = ok ? v[q][r] : 0.f;
+            for (int r = 0; r < kPer; r += 4) {
+                const float4 y = ok ? make_float4(v[q][r], v[q][r + 1], v[q][r + 2], v[q][r + 3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+                *reinterpret_cast<float4*>(&s_x[p][k0 + r]) = y;
+            }
         }
     }
-    const int pg = tid >> 4, cg = tid & 15;
-    double bd[4];
-    int bu[4];
+    constexpr int kVec = D / 16;  // 16-byte pieces of a lane's quarter row
+    const int lane = lane_id(), wv = wave_id(), cgrp = lane >> 4, j16 = lane & 15;
+    float4 xf[kVec];
+    float xn2 = 0.f, xabs = 0.f, cn2 = 0.f, cabs = 0.f;  // largest squared norms and magnitudes
+    Near3 nr[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        bd[i] = INFINITY;
-        bu[i] = 0x7fffffff;
-    }
-    const double* cb = cent + static_cast<size_t>(bh) * M * D;
+    for (int i = 0; i < 4; ++i) nr[i] = Near3{INFINITY, INFINITY, INFINITY, 0x7fffffff, 0x7fffffff};
+    auto quarter = [&](const float* row, float4 (&v)[kVec], float& n2, float& mx) __attribute__((always_inline)) {
+        n2 = 0.f;
+        mx = 0.f;
+#pragma unroll
+        for (int q = 0; q < kVec; ++q) {
+            v[q] = reinterpret_cast<const float4*>(row + cgrp * (D / 4))[q];
+            n2 = fmaf(v[q].x, v[q].x, fmaf(v[q].y, v[q].y, fmaf(v[q].z, v[q].z, fmaf(v[q].w, v[q].w, n2))));
+            mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v[q].x), fabsf(v[q].y)), fmaxf(fabsf(v[q].z), fabsf(v[q].w))));
+        }
+        n2 += __shfl_xor(n2, 16);
+        n2 += __shfl_xor(n2, 32);
+    };
     for (int ct = 0; ct < M; ct += kAsgCen) {
-        __syncthreads();  // the previous tile is no longer read
+        if (ct > 0) {
+            load_tile(ct);
+            __syncthreads();  // the previous tile is no longer read
+        }
         const int nct = min(kAsgCen, M - ct);
-        {
-            // the tile's values, all loads in flight before the LDS stores
-            // (rows past the last center read center 0 and store zero)
-            static_assert(kAsgCen * D % kAsgThreads == 0, "whole tile elements per thread");
-            constexpr int kPer = kAsgCen * D / kAsgThreads;
-            double v[kPer];
 #pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                const int e = q * kAsgThreads + tid, u = e / D, k = e % D;
-                v[q] = cb[static_cast<size_t>(u < nct ? ct + u : 0) * D + k];
-            }
-#pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                const int e = q * kAsgThreads + tid, u = e / D, k = e % D;
-                s_c[u][k] = u < nct ? v[q] : 0.0;
+        for (int q = 0; q < kQuads; ++q) {
+            const int e = q * kAsgThreads + tid, u = e / (D / 4), k = 4 * (e % (D / 4));
+            *reinterpret_cast<float4*>(&s_c[u][k]) = make_float4(static_cast<float>(cv0[q].x), static_cast<float>(cv0[q].y),
+                                                                 static_cast<float>(cv1[q].x), static_cast<float>(cv1[q].y));
+            if (!FINAL && ct == 0) {
+                *reinterpret_cast<double2*>(&s_cd[FINAL ? 0 : u][k]) = cv0[q];
+                *reinterpret_cast<double2*>(&s_cd[FINAL ? 0 : u][k + 2]) = cv1[q];
             }
         }
         __syncthreads();
-        double acc[4][2];
+        if (ct == 0) quarter(s_x[16 * wv + j16], xf, xn2, xabs);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i][0] = acc[i][1] = 0.0;
-#pragma unroll 4
-        for (int k = 0; k < D; ++k) {
-            double xv[4], cv[2];
+        for (int t = 0; t < kAsgCen / 16; ++t) {
+            float4 cf[kVec];
+            float n2, mx;
+            quarter(s_c[16 * t + j16], cf, n2, mx);
+            f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) xv[i] = static_cast<double>(s_x[4 * pg + i][k]);
-#pragma unroll
-            for (int e = 0; e < 2; ++e) cv[e] = s_c[2 * cg + e][k];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const double t = xv[i] - cv[e];
-                    acc[i][e] = acc[i][e] + t * t;
-                }
+            for (int q = 0; q < kVec; ++q) {
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[q].x, cf[q].x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[q].y, cf[q].y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[q].z, cf[q].z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[q].w, cf[q].w, acc, 0, 0, 0);
             }
-        }
+            if (16 * t + j16 < nct) {
+                cn2 = fmaxf(cn2, n2);
+                cabs = fmaxf(cabs, mx);
+                if (!(n2 < INFINITY)) cn2 = INFINITY;  // NaN too
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int u = ct + 2 * cg + e;
-            if (2 * cg + e < nct) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (acc[i][e] < bd[i] || (acc[i][e] == bd[i] && u < bu[i])) {
-                        bd[i] = acc[i][e];
-                        bu[i] = u;
-                    }
+                for (int r = 0; r < 4; ++r) nr[r].add(fmaf(-2.f, acc[r], n2), ct + 16 * t + j16);
             }
         }
     }
-    // the 16 center groups of a point: lowest distance, then lowest index
+    // the 16 lanes that share a point's centers
 #pragma unroll
-    for (int off = 8; off > 0; off >>= 1) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const double od = __shfl_xor(bd[i], off);
-            const int ou = __shfl_xor(bu[i], off);
-            if (od < bd[i] || (od == bd[i] && ou < bu[i])) {
-                bd[i] = od;
-                bu[i] = ou;
+    for (int r = 0; r < 4; ++r) {
+        nr[r].merge<0x128>();
+        nr[r].merge<0x124>();
+        nr[r].merge<0x122>();
+        nr[r].merge<0x121>();
+        if (j16 == r) s_near[16 * wv + 4 * cgrp + r] = nr[r];
+    }
+    {
+        const bool odd = __ballot(!(xn2 < INFINITY)) != 0;
+        const float x2 = odd ? INFINITY : wave_fmax(xn2), c2 = wave_fmax(cn2);
+        const bool zero = !odd && c2 < INFINITY && wave_fmax(fmaxf(xabs, cabs)) == 0.f;  // every distance is 0
+        const float size = __fsqrt_rn(x2) * __fsqrt_rn(c2) + c2;
+        if (lane == 0) s_err[wv] = zero ? -1.f : c2 > 1e-30f && size < 1e30f && x2 < 1e30f ? 1400.f * 0x1.0p-24f * size : INFINITY;
+    }
+    __syncthreads();
+    // threads 0 .. 63: a point and its nearest center, 64 .. 127: its second
+    // nearest where the estimates leave the choice open
+    if (tid < 2 * kAsgPts) {
+        const int p = tid & (kAsgPts - 1);
+        Near3 x = s_near[p];
+        const float err2 = s_err[p >> 4];
+        if (err2 < 0.f) {
+            x.u1 = 0;
+            s_near[p].u1 = 0;
+        }
+        const bool two = err2 >= 0.f && M > 1 && !(x.d2 - x.d1 > err2);
+        const bool full = err2 == INFINITY || (two && M > 2 && !(x.d3 - x.d1 > err2));
+        if (s_tok[p] >= 0) {
+            if (full) {
+                if (tid < kAsgPts) s_list[atomicAdd(&s_full, 1)] = p;
+            } else if (tid < kAsgPts) {
+                if (!FINAL && x.u1 < kAsgCen)
+                    s_e[p] = point_dist<D>(s_x[p], s_cd[FINAL ? 0 : x.u1]);
+                else if (!FINAL || two)
+                    s_e[p] = point_dist<D>(s_x[p], cb + static_cast<size_t>(x.u1) * D);
+                s_lab[p] = x.u1;
+            } else {
+                s_second[p] = two ? point_dist<D>(s_x[p], cb + static_cast<size_t>(x.u2) * D) : INFINITY;
             }
         }
     }
-    if (cg == 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
+    __syncthreads();
+    if (tid < kAsgPts && s_tok[tid] >= 0) {
+        const Near3 x = s_near[tid];
+        bool listed = false;
+        for (int i = 0; i < s_full; ++i) listed = listed || s_list[i] == tid;
+        const double second = listed ? INFINITY : s_second[tid];
+        if (!listed && second < INFINITY && (second < s_e[tid] || (second == s_e[tid] && x.u2 < x.u1))) {
+            s_e[tid] = second;
+            s_lab[tid] = x.u2;
+        }
+    }
+    // every center: half a wave per point
+    for (int i = tid >> 5; i < s_full; i += kAsgThreads / 32) {
+        const int p = s_list[i];
+        double bd = INFINITY;
+        int bu = 0x7fffffff;
+        for (int u = tid & 31; u < M; u += 32) {
+            const double d2 = point_dist<D>(s_x[p], cb + static_cast<size_t>(u) * D);
+            if (d2 < bd) {
+                bd = d2;
+                bu = u;
+            }
+        }
+        for (int off = 16; off > 0; off >>= 1) {
+            const double od = __shfl_xor(bd, off);
+            const int ou = __shfl_xor(bu, off);
+            if (od < bd || (od == bd && ou < bu)) {
+                bd = od;
+                bu = ou;
+            }
+        }
+        if ((tid & 31) == 0) {
             // no winner (NaN keys): center 0, so every label stays in range
-            s_lab[4 * pg + i] = bu[i] < M ? bu[i] : 0;
-            s_e[4 * pg + i] = bd[i];
+            s_lab[p] = bu < M ? bu : 0;
+            s_e[p] = bd;
         }
     }
     __syncthreads();
@@ -437,56 +600,81 @@ __global__ __launch_bounds__(kAsgThreads) void k_km_assign(
     }
     const int nv = min(kAsgPts, npts - p0);  // valid points: 0 .. nv - 1
     const size_t blk = static_cast<size_t>(bh) * gridDim.x + blockIdx.x;
-    if (tid == 0) {
+    if (tid == 2 * kAsgPts) {
         double s = 0.0;
-        for (int p = 0; p < nv; ++p) s = s + s_e[p];
+        for (int q0 = 0; q0 < nv; q0 += 16) {
+            double v[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = s_e[min(q0 + q, nv - 1)];
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                if (q0 + q < nv) s = s + v[q];
+        }
         binert[blk] = s;
     }
-    // points ordered by (center, position): a stable counting sort
-    if (tid < nv) {
-        const int u = s_lab[tid];
-        int r = 0;
-        for (int q = 0; q < nv; ++q) {
-            const int v = s_lab[q];
-            r += (v < u || (v == u && q < tid)) ? 1 : 0;
+    // points ordered by (center, position), a stable counting sort, by wave 0;
+    // the centers' counts by the waves after it (lane p holds point p's label)
+    static_assert(kAsgPts == kWave, "a lane per point");
+    {
+        const int lab = lane < nv ? s_lab[lane] : 0x7fffffff;
+        if (wv == 0) {
+            int r = 0;
+#pragma unroll 8
+            for (int q = 0; q < kAsgPts; ++q) {
+                const int v = readlane(lab, q);
+                r += (v < lab || (v == lab && q < lane)) ? 1 : 0;
+            }
+            if (lane < nv) s_ord[r] = lane;
+        } else {
+            for (int u0 = (wv - 1) * kWave; u0 < M; u0 += kAsgThreads - kWave) {  // uniform
+                const int u = u0 + lane;
+                int n = 0;
+#pragma unroll 8
+                for (int q = 0; q < kAsgPts; ++q) n += readlane(lab, q) == u ? 1 : 0;
+                if (u < M) bcnt[blk * M + u] = n;
+            }
         }
-        s_ord[r] = tid;
-    }
-    for (int u = tid; u < M; u += kAsgThreads) {
-        int n = 0;
-        for (int q = 0; q < nv; ++q) n += s_lab[q] == u ? 1 : 0;
-        bcnt[blk * M + u] = n;
     }
     __syncthreads();
-    // each present center's sum, in point order, one thread per dimension;
-    // 16 sorted points' positions, labels and values are read ahead of
-    // their additions (indices clamped into the valid points)
-    if (tid < D) {
-        int cur = -1;
-        double acc = 0.0;
-        for (int r0 = 0; r0 < nv; r0 += 16) {
-            int pp[16], uu[16];
-            float xx[16];
+    // each present center's sum, in point order: a wave takes the centers whose
+    // first sorted point lies in its quarter of the order, a lane D / 64
+    // dimensions; eight points' values are read ahead of their additions
+    {
+        constexpr int kDims = D / kWave;
+        const int ord = lane < nv ? s_ord[lane] : 0, lab = lane < nv ? s_lab[ord] : -1;
+        const int before = __shfl_up(lab, 1);
+        const uint64_t starts = __ballot(lane < nv && (lane == 0 || lab != before));
+        constexpr int kPart = kAsgPts / (kAsgThreads / kWave);
+        auto first = [&](int from) {  // the first center start at or after `from`
+            const uint64_t x = from < kWave ? starts >> from : 0;
+            return x != 0 ? from + __ffsll(static_cast<unsigned long long>(x)) - 1 : nv;
+        };
+        const int r1 = first((wv + 1) * kPart);
+        double acc[kDims];
+        for (int r0 = first(wv * kPart); r0 < r1; r0 += 8) {
+            float xx[8][kDims];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) pp[q] = s_ord[min(r0 + q, nv - 1)];
+            for (int q = 0; q < 8; ++q) {
+                const int p = readlane(ord, min(r0 + q, r1 - 1));
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                uu[q] = s_lab[pp[q]];
-                xx[q] = s_x[pp[q]][tid];
+                for (int e = 0; e < kDims; ++e) xx[q][e] = s_x[p][kDims * lane + e];
             }
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                if (r0 + q < nv) {
-                    if (uu[q] != cur) {
-                        if (cur >= 0) bpart[(blk * M + cur) * D + tid] = acc;
-                        cur = uu[q];
-                        acc = 0.0;
+            for (int q = 0; q < 8; ++q) {
+                const int r = r0 + q;
+                if (r < r1) {  // uniform
+                    const bool start = (starts >> r) & 1ull;
+#pragma unroll
+                    for (int e = 0; e < kDims; ++e)
+                        acc[e] = (start ? 0.0 : acc[e]) + static_cast<double>(xx[q][e]);
+                    if (r + 1 == r1 || ((starts >> (r + 1)) & 1ull)) {  // the center's last point
+#pragma unroll
+                        for (int e = 0; e < kDims; ++e)
+                            bpart[(blk * M + readlane(lab, r)) * D + kDims * lane + e] = acc[e];
                     }
-                    acc = acc + static_cast<double>(xx[q]);
                 }
             }
         }
-        if (cur >= 0) bpart[(blk * M + cur) * D + tid] = acc;
     }
 }
 

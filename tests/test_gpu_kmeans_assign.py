@@ -1,0 +1,62 @@
+"""Nearest-center choice of the k-means parents where its fp32 estimates cannot
+decide: equal keys and centers (ties go to the lower center), zero keys, keys
+whose squares leave fp32's range on either side, more centers than one tile of
+32, and token counts around a workgroup's 64 points.  Labels and steps are
+compared with the oracle bit for bit: where an estimate leaves the choice open
+the definition's fp64 distances take it, so nothing has a tolerance.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_35629_amd as sp
+from tests.gpu_util import log
+
+pytestmark = pytest.mark.gpu
+
+
+def _keys(kind, N, d, dtype):
+    g = np.random.default_rng(N + d)
+    x = g.standard_normal((N, d))
+    if kind == "grid":  # few distinct rows: tied centers and points
+        x = np.sign(x) * (np.arange(d) < 3)
+    elif kind == "copies":  # near copies of two rows, apart by less than the estimates resolve
+        x = x[np.arange(N) % 2] + 2.0**-7 * (g.integers(0, 3, (N, d)) - 1) * (np.arange(d) < 2)
+    elif kind == "zeros":
+        x[:] = 0.0
+    elif kind == "half_zero":
+        x[np.arange(N) % 3 != 0] = 0.0
+    elif kind == "huge":
+        x *= 1e22
+    elif kind == "tiny":
+        x *= 1e-25
+    elif kind == "mixed":
+        x *= 10.0 ** g.integers(-22, 22, (N, 1))
+    return torch.from_numpy(x).to(dtype)
+
+
+@pytest.mark.parametrize("kind,N,P,d,dtype", [
+    ("normal", 65, 16, 128, torch.bfloat16),
+    ("normal", 2113, 64, 64, torch.float32),
+    ("normal", 1500, 20, 128, torch.float32),  # 75 centers: three tiles, the last ragged
+    ("normal", 63, 63, 64, torch.bfloat16),  # two centers
+    ("huge", 63, 63, 64, torch.float32),  # two centers, no estimate
+    ("grid", 500, 30, 128, torch.bfloat16),
+    ("grid", 500, 13, 64, torch.float32),
+    ("copies", 640, 80, 64, torch.float32),
+    ("copies", 640, 64, 128, torch.bfloat16),
+    ("zeros", 200, 40, 128, torch.bfloat16),
+    ("half_zero", 300, 30, 64, torch.bfloat16),
+    ("huge", 400, 50, 128, torch.float32),
+    ("tiny", 400, 50, 64, torch.float32),
+    ("mixed", 400, 25, 128, torch.float32),
+])
+def test_labels_match_oracle(kind, N, P, d, dtype):
+    x = _keys(kind, N, d, dtype)
+    log(f"[gpu] kmeans assign {kind} N={N} P={P} d={d} {dtype}")
+    th = oracle.KMeansSettings(batch=200, max_iter=12)
+    labels, _, steps = sp.kmeans_parents(x[None, None].cuda(), P, batch_size=th.batch, max_iter=th.max_iter)
+    r = oracle.kmeans_parents(x.to(torch.float64).numpy(), P, th)
+    assert steps[0] == r.steps
+    np.testing.assert_array_equal(labels.cpu().numpy()[0, 0], r.labels)
