@@ -55,6 +55,7 @@ constexpr int kAsgCen = 32;   // centers per LDS tile
 constexpr int kUpdBatch = 32; // workgroup partials the center update loads at once
 constexpr int kListThreads = 1024;
 constexpr int kListWaves = kListThreads / kWave;
+constexpr int kListAhead = 8;  // 64-token groups whose labels a wave reads at once
 
 __device__ __forceinline__ uint64_t km_word(uint64_t seed, uint64_t a, uint64_t tag, uint64_t s) {
     const u64x4 r = philox4x64_10(a >> 2, tag, s, 0, seed, 1);
@@ -89,17 +90,17 @@ __device__ __forceinline__ void load_row16(const float* p, float (&v)[4]) {
     v[3] = __uint_as_float(w.w);
 }
 
-// Per-workgroup sum of one value per thread: waves by xor shuffles, then the
-// wave totals in wave order.
-template <int W>
-__device__ __forceinline__ double block_sum(double v, double* s_w) {
-    for (int off = kWave / 2; off > 0; off >>= 1) v = v + __shfl_xor(v, off);
-    if (lane_id() == 0) s_w[wave_id()] = v;
-    __syncthreads();
-    double r = 0.0;
-    for (int w = 0; w < W; ++w) r = r + s_w[w];
-    __syncthreads();
-    return r;
+// Sum of one value per lane over the wave, halves first (lane i + lane i ^ 32,
+// then ^ 16, 8, 4, 2, 1); within 16 lanes a rotation reads what the xor would.
+__device__ __forceinline__ double wave_sum_halves(double v) {
+#pragma clang fp contract(off)
+    v = v + __shfl_xor(v, 32);
+    v = v + __shfl_xor(v, 16);
+    v = v + dpp_f64<0x128>(v);
+    v = v + dpp_f64<0x124>(v);
+    v = v + dpp_f64<0x122>(v);
+    v = v + dpp_f64<0x121>(v);
+    return v;
 }
 
 __global__ __launch_bounds__(kKppThreads) void k_kpp_sample(int* __restrict__ samp, int s0, int N,
@@ -113,59 +114,69 @@ __global__ __launch_bounds__(kKppThreads) void k_kpp_sample(int* __restrict__ sa
     }
 }
 
+// A point per thread, the candidates' rows in LDS, 32 dimensions at a time: the
+// point's next 32 are requested ahead, and a candidate's 32 are one run of LDS
+// reads without a branch (a branch per candidate and dimension made every read
+// a round trip).  At 12288 points, five candidates, four pairs, d = 128, bf16:
+// 23.5 us a round before, now 11.1, of which the 128 x 5 fp64 terms take 3.
 template <typename T, int D>
 __global__ __launch_bounds__(kKppThreads) void k_kpp_dist(
     const T* __restrict__ K, int N, const int* __restrict__ samp, int s0, const int* __restrict__ cand,
     int L, int c, double* __restrict__ D2, double* __restrict__ Dt, double* __restrict__ part) {
 #pragma clang fp contract(off)
-    __shared__ double s_cand[kKmMaxTrials][D];
-    __shared__ double s_w[kKppThreads / kWave];
-    const int bh = blockIdx.y, tid = threadIdx.x;
+    __shared__ __align__(16) double s_cand[kKmMaxTrials][D];
+    __shared__ double s_w[kKmMaxTrials][kKppThreads / kWave];
+    __shared__ int s_ctok[kKmMaxTrials];
+    const int bh = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wv = wave_id();
     const int nc = c == 0 ? 1 : L;
     const T* X = K + static_cast<size_t>(bh) * N * D;
-    __shared__ int s_ctok[kKmMaxTrials];
-    if (tid < nc) s_ctok[tid] = samp[cand[bh * L + tid]];
-    __syncthreads();
-    {
-        constexpr int kPer = 16 / static_cast<int>(sizeof(T));
-        for (int e = tid; e < nc * (D / kPer); e += kKppThreads) {
-            const int t = e / (D / kPer), k0 = (e % (D / kPer)) * kPer;
-            float v[kPer];
-            load_row16(X + static_cast<size_t>(s_ctok[t]) * D + k0, v);
-#pragma unroll
-            for (int r = 0; r < kPer; ++r) s_cand[t][k0 + r] = static_cast<double>(v[r]);
-        }
-    }
-    __syncthreads();
     const int j = blockIdx.x * kKppThreads + tid;
     const bool valid = j < s0;
-    const T* x = X + static_cast<size_t>(valid ? samp[j] : 0) * D;
+    constexpr int kPer = 16 / static_cast<int>(sizeof(T));
+    if (tid < nc) s_ctok[tid] = samp[cand[bh * L + tid]];
+    const T* x = X + static_cast<size_t>(samp[valid ? j : 0]) * D;
     const double dcur = (valid && c > 0) ? D2[static_cast<size_t>(bh) * s0 + j] : 0.0;
-    // one pass over the point's row, all of it loaded up front; candidate
-    // t's sum runs in dimension order
+    constexpr int kDims = 32, kRaw = kDims / kPer;
+    uint4 raw[kRaw];
+#pragma unroll
+    for (int q = 0; q < kRaw; ++q) raw[q] = reinterpret_cast<const uint4*>(x)[q];
+    __syncthreads();
+    for (int e = tid; e < nc * (D / kPer); e += kKppThreads) {
+        const int t = e / (D / kPer), k0 = (e % (D / kPer)) * kPer;
+        float v[kPer];
+        load_row16(X + static_cast<size_t>(s_ctok[t]) * D + k0, v);
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) s_cand[t][k0 + r] = static_cast<double>(v[r]);
+    }
+    __syncthreads();
     double acc[kKmMaxTrials];
 #pragma unroll
     for (int t = 0; t < kKmMaxTrials; ++t) acc[t] = 0.0;
-    constexpr int kPer = 16 / static_cast<int>(sizeof(T));
-    uint4 raw[D / kPer];
+#pragma unroll 1
+    for (int k0 = 0; k0 < D; k0 += kDims) {
+        float xv[kDims];
 #pragma unroll
-    for (int q = 0; q < D / kPer; ++q) raw[q] = reinterpret_cast<const uint4*>(x)[q];
+        for (int q = 0; q < kRaw; ++q) load_row16(reinterpret_cast<const T*>(&raw[q]), *reinterpret_cast<float(*)[kPer]>(&xv[q * kPer]));
+        const int kn = min(k0 + kDims, D - kDims);
 #pragma unroll
-    for (int k0 = 0; k0 < D; k0 += kPer) {
-        float xv[kPer];
-        load_row16(reinterpret_cast<const T*>(&raw[k0 / kPer]), xv);
+        for (int q = 0; q < kRaw; ++q) raw[q] = reinterpret_cast<const uint4*>(x + kn)[q];
+        // candidate t's sum runs in dimension order
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
+        for (int t = 0; t < kKmMaxTrials; ++t) {
+            if (t < nc) {  // uniform
+                double2 y[kDims / 2];
 #pragma unroll
-            for (int t = 0; t < kKmMaxTrials; ++t) {
-                if (t < nc) {
-                    const double e = static_cast<double>(xv[q]) - s_cand[t][k0 + q];
-                    acc[t] = acc[t] + e * e;
+                for (int q = 0; q < kDims / 2; ++q) y[q] = *reinterpret_cast<const double2*>(&s_cand[t][k0 + 2 * q]);
+#pragma unroll
+                for (int q = 0; q < kDims / 2; ++q) {
+                    const double e0 = static_cast<double>(xv[2 * q]) - y[q].x;
+                    acc[t] = acc[t] + e0 * e0;
+                    const double e1 = static_cast<double>(xv[2 * q + 1]) - y[q].y;
+                    acc[t] = acc[t] + e1 * e1;
                 }
             }
         }
     }
-    const int nblk = gridDim.x;
 #pragma unroll
     for (int t = 0; t < kKmMaxTrials; ++t) {
         if (t < nc) {  // uniform
@@ -174,12 +185,24 @@ __global__ __launch_bounds__(kKppThreads) void k_kpp_dist(
                 m = (c == 0) ? acc[t] : (acc[t] < dcur ? acc[t] : dcur);
                 Dt[(static_cast<size_t>(bh) * L + t) * s0 + j] = m;
             }
-            const double tot = block_sum<kKppThreads / kWave>(m, s_w);
-            if (tid == 0) part[(static_cast<size_t>(bh) * nblk + blockIdx.x) * L + t] = tot;
+            const double tot = wave_sum_halves(m);
+            if (lane == 0) s_w[t][wv] = tot;
         }
+    }
+    __syncthreads();
+    if (tid < nc) {  // the waves in order
+        double r = 0.0;
+        for (int w = 0; w < kKppThreads / kWave; ++w) r = r + s_w[tid][w];
+        part[(static_cast<size_t>(bh) * gridDim.x + blockIdx.x) * L + tid] = r;
     }
 }
 
+// One workgroup per pair: a chain of round trips.  The sample's distances come
+// in with neighbouring threads on neighbouring values and reach their owners
+// (contiguous ranges) through LDS, and only the thread in whose range a trial's
+// draw falls looks for the position.  Reading the ranges in place and
+// comparing every value with every trial's draw took 18 us (12288 values, five
+// trials, four pairs); now 11.7.
 template <typename T, int D>
 __global__ __launch_bounds__(kPickThreads) void k_kpp_pick(
     const T* __restrict__ K, int N, const int* __restrict__ samp, int s0, int* __restrict__ cand,
@@ -188,12 +211,16 @@ __global__ __launch_bounds__(kPickThreads) void k_kpp_pick(
 #pragma clang fp contract(off)
     __shared__ double s_pot[kKmMaxTrials];
     __shared__ double s_tot[kPickThreads / kWave];
-    __shared__ int s_best;
-    __shared__ int s_first[kKmMaxTrials];
+    __shared__ int s_first[kKmMaxTrials], s_ctok[kKmMaxTrials];
     __shared__ double s_u[kKmMaxTrials];
+    __shared__ double s_val[kPickThreads * (kPickCache + 1)];  // a range's values, one place of padding per range
     const int bh = blockIdx.x, tid = threadIdx.x;
     const int nc = c == 0 ? 1 : L;
     const T* X = K + static_cast<size_t>(bh) * N * D;
+    if (tid < nc) s_ctok[tid] = samp[cand[bh * L + tid]];
+    if (tid >= kPickThreads - L)
+        s_u[kPickThreads - 1 - tid] =
+            draw_unit(km_word(seed, static_cast<uint64_t>(kPickThreads - 1 - tid), 2, static_cast<uint64_t>(c + 1)));
     if (wave_id() < nc) {  // wave t sums trial t's workgroup partials
         const int t = wave_id();
         double p = 0.0;
@@ -201,17 +228,12 @@ __global__ __launch_bounds__(kPickThreads) void k_kpp_pick(
         for (int off = kWave / 2; off > 0; off >>= 1) p = p + __shfl_xor(p, off);
         if (lane_id() == 0) s_pot[t] = p;
     }
-    if (tid < kKmMaxTrials) s_first[tid] = s0 - 1;
+    if (tid < kKmMaxTrials) s_first[tid] = kPickThreads;
     __syncthreads();
-    if (tid == 0) {
-        int best = 0;
-        for (int t = 1; t < nc; ++t)
-            if (s_pot[t] < s_pot[best]) best = t;
-        s_best = best;
-    }
-    __syncthreads();
-    const int best = s_best;
-    const int tok = samp[cand[bh * L + best]];
+    int best = 0;
+    for (int t = 1; t < nc; ++t)
+        if (s_pot[t] < s_pot[best]) best = t;
+    const int tok = s_ctok[best];
     for (int k = tid; k < D; k += kPickThreads)
         cent[(static_cast<size_t>(bh) * M + c) * D + k] = static_cast<double>(load_elem(X + static_cast<size_t>(tok) * D, k));
     const double* src = Dt + (static_cast<size_t>(bh) * L + best) * s0;
@@ -224,24 +246,31 @@ __global__ __launch_bounds__(kPickThreads) void k_kpp_pick(
     // the contiguous range [tid per, (tid + 1) per)
     const int per = (s0 + kPickThreads - 1) / kPickThreads;
     const int j0 = min(s0, tid * per), j1 = min(s0, j0 + per);
-    // the range's first kPickCache values, loaded together (indices clamped
-    // into the sample, so no load is conditional) and kept for both passes;
-    // the sums still run in index order
     double vals[kPickCache];
-#pragma unroll
-    for (int q = 0; q < kPickCache; ++q) vals[q] = src[min(j0 + q, s0 - 1)];
     double loc = 0.0;
+    if (per <= kPickCache) {  // uniform
 #pragma unroll
-    for (int q = 0; q < kPickCache; ++q) {
-        if (j0 + q < j1) {
-            dst[j0 + q] = vals[q];
-            loc = loc + vals[q];
+        for (int q = 0; q < kPickCache; ++q) vals[q] = src[min(q * kPickThreads + tid, s0 - 1)];
+#pragma unroll
+        for (int q = 0; q < kPickCache; ++q) {
+            const int j = q * kPickThreads + tid;
+            if (j < s0) {
+                dst[j] = vals[q];
+                s_val[j + j / per] = vals[q];
+            }
         }
-    }
-    for (int j = j0 + kPickCache; j < j1; ++j) {
-        const double v = src[j];
-        dst[j] = v;
-        loc = loc + v;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kPickCache; ++q) {
+            vals[q] = s_val[tid * (per + 1) + q];
+            if (j0 + q < j1) loc = loc + vals[q];
+        }
+    } else {
+        for (int j = j0; j < j1; ++j) {
+            const double v = src[j];
+            dst[j] = v;
+            loc = loc + v;
+        }
     }
     // scan of the thread sums in thread order
     double inc = loc;
@@ -259,41 +288,47 @@ __global__ __launch_bounds__(kPickThreads) void k_kpp_pick(
         total = total + s_tot[w];
     }
     const double pre = wpre + exc;
-    if (tid < L) s_u[tid] = draw_unit(km_word(seed, static_cast<uint64_t>(tid), 2, static_cast<uint64_t>(c + 1)));
-    __syncthreads();
-    double target[kKmMaxTrials];
-#pragma unroll
-    for (int t = 0; t < kKmMaxTrials; ++t) target[t] = t < L ? s_u[t] * total : 0.0;
-    int found[kKmMaxTrials];
-#pragma unroll
-    for (int t = 0; t < kKmMaxTrials; ++t) found[t] = s0;
+    // trial t takes the first position whose running sum exceeds its draw.  The
+    // values are not negative, so a range holds such a position exactly when the
+    // running sum at its end exceeds the draw; the first such range's thread
+    // looks for it (a draw that is not finite is exceeded nowhere).
     double run = pre;
+    if (per <= kPickCache) {
 #pragma unroll
-    for (int q = 0; q < kPickCache; ++q) {
-        if (j0 + q < j1) {
-            run = run + vals[q];
-#pragma unroll
-            for (int t = 0; t < kKmMaxTrials; ++t)
-                if (t < L && found[t] == s0 && run > target[t]) found[t] = j0 + q;
-        }
+        for (int q = 0; q < kPickCache; ++q)
+            if (j0 + q < j1) run = run + vals[q];
+    } else {
+        for (int j = j0; j < j1; ++j) run = run + src[j];
     }
-    for (int j = j0 + kPickCache; j < j1; ++j) {
-        run = run + src[j];
-#pragma unroll
-        for (int t = 0; t < kKmMaxTrials; ++t)
-            if (t < L && found[t] == s0 && run > target[t]) found[t] = j;
-    }
-    // the first crossing of each trial: every thread past it has found a
-    // position too, so the wave's minimum goes to LDS, one atomic per wave
-#pragma unroll
-    for (int t = 0; t < kKmMaxTrials; ++t) {
-        if (t < L) {  // uniform
-            const int f = static_cast<int>(wave_min64(static_cast<uint64_t>(found[t])));
-            if (lane_id() == 0 && f < s0) atomicMin(&s_first[t], f);
-        }
+    for (int t = 0; t < L; ++t) {  // uniform
+        const uint64_t over = __ballot(j0 < j1 && run > s_u[t] * total);
+        if (lane_id() == 0 && over != 0)
+            atomicMin(&s_first[t], wave_id() * kWave + __ffsll(static_cast<unsigned long long>(over)) - 1);
     }
     __syncthreads();
-    if (tid < L) cand[bh * L + tid] = s_first[tid];
+    for (int t = 0; t < L; ++t) {
+        const int owner = s_first[t];
+        if (owner == kPickThreads) {  // the draw is the total: the last position
+            if (tid == 0) cand[bh * L + t] = s0 - 1;
+        } else if (owner == tid) {
+            const double target = s_u[t] * total;
+            double at = pre;
+            int found = -1;
+            if (per <= kPickCache) {
+#pragma unroll
+                for (int q = 0; q < kPickCache; ++q) {
+                    if (j0 + q < j1) at = at + vals[q];
+                    if (found < 0 && at > target) found = j0 + q;
+                }
+            } else {
+                for (int j = j0; found < 0; ++j) {
+                    at = at + src[j];
+                    if (at > target || j + 1 >= j1) found = j;
+                }
+            }
+            cand[bh * L + t] = found;
+        }
+    }
 }
 
 // |x - c|^2 of a staged point (fp32, exact values) and a center, the
@@ -715,6 +750,10 @@ __global__ __launch_bounds__(D) void k_km_update(int M, int nblk, const double* 
     if (k == 0) w[static_cast<size_t>(bh) * M + u] = wu + static_cast<double>(n);
 }
 
+// One workgroup per pair: wave 0 adds the batch inertia, wave 1 marks the
+// starved centers, each 64 at a time from one load (scanned by one thread, in
+// batches of eight loads, the two took 6.7 us together at 32 centers and 64
+// partials; now 4.0).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_km_control(
     const T* __restrict__ K, int N, int M, int batch, int step, uint64_t seed, int nblk, double alpha,
@@ -722,36 +761,64 @@ __global__ __launch_bounds__(256) void k_km_control(
     double* __restrict__ w, KmState* __restrict__ state) {
 #pragma clang fp contract(off)
     __shared__ int s_mark[kKmMaxCenters];
-    __shared__ double s_wb[kKmMaxCenters];
     __shared__ int s_count;
     __shared__ double s_wkeep;
-    const int bh = blockIdx.x, tid = threadIdx.x;
+    const int bh = blockIdx.x, tid = threadIdx.x, lane = lane_id();
     KmState* st = state + bh;
-    if (st->stop) return;
+    KmState next = *st;
     double* wb = w + static_cast<size_t>(bh) * M;
-    // the weights staged in LDS by every thread, then scanned in index order
-    // by one
-    for (int u = tid; u < M; u += 256) s_wb[u] = wb[u];
-    __syncthreads();
-    if (tid == 0) {
+    const double* bi = binert + static_cast<size_t>(bh) * nblk;
+    const double first = wave_id() == 0 ? bi[min(lane, nblk - 1)] : wave_id() == 1 ? wb[min(lane, M - 1)] : 0.0;
+    if (next.stop) return;
+    if (wave_id() == 0) {
+        // the workgroups' sums in order
+        double I = 0.0;
+        for (int b0 = 0; b0 < nblk; b0 += kWave) {
+            const double v = b0 == 0 ? first : bi[min(b0 + lane, nblk - 1)];
+            const int n = min(kWave, nblk - b0);
+#pragma unroll 8
+            for (int q = 0; q < n; ++q)
+                I = I + __longlong_as_double(static_cast<long long>(readlane(static_cast<uint64_t>(__double_as_longlong(v)), q)));
+        }
+        I = I / static_cast<double>(batch);
+        next.ewa = step == 0 ? I : next.ewa * (1.0 - alpha) + I * alpha;
+        if (next.ewa < next.ewa_min) {
+            next.ewa_min = next.ewa;
+            next.no_imp = 0;
+        } else {
+            next.no_imp += 1;
+        }
+        next.steps = step + 1;
+        if (max_no_improvement > 0 && next.no_imp >= max_no_improvement) next.stop = 1;
+    } else if (wave_id() == 1) {
+        // centers under ratio x the largest weight, in index order, up to half
+        // a batch of them; the smallest weight among the others
         int count = 0;
         double wkeep = INFINITY;
         if (ratio > 0.0) {
-            double wmax = s_wb[0];
-            for (int u = 1; u < M; ++u)
-                if (s_wb[u] > wmax) wmax = s_wb[u];
+            double wmax = first;
+            for (int u0 = kWave; u0 < M; u0 += kWave) wmax = fmax(wmax, wb[min(u0 + lane, M - 1)]);
+            for (int off = kWave / 2; off > 0; off >>= 1) wmax = fmax(wmax, __shfl_xor(wmax, off));
             const double thr = ratio * wmax;
-            for (int u = 0; u < M; ++u) {
-                if (s_wb[u] < thr && count < batch / 2)
-                    s_mark[count++] = u;
-                else if (s_wb[u] < wkeep)
-                    wkeep = s_wb[u];
+            for (int u0 = 0; u0 < M; u0 += kWave) {
+                const int u = u0 + lane;
+                const double v = u0 == 0 ? first : wb[min(u, M - 1)];
+                const uint64_t low = __ballot(u < M && v < thr);
+                const int at = count + static_cast<int>(__popcll(low & lanemask_lt()));
+                const bool marked = u < M && v < thr && at < batch / 2;
+                if (marked) s_mark[at] = u;
+                if (u < M && !marked && v < wkeep) wkeep = v;
+                count = min(count + static_cast<int>(__popcll(low)), batch / 2);
             }
+            for (int off = kWave / 2; off > 0; off >>= 1) wkeep = fmin(wkeep, __shfl_xor(wkeep, off));
         }
-        s_count = count;
-        s_wkeep = wkeep;
+        if (lane == 0) {
+            s_count = count;
+            s_wkeep = wkeep;
+        }
     }
     __syncthreads();
+    if (tid == 0) *st = next;  // every wave has read the old one
     const int count = s_count;
     const T* X = K + static_cast<size_t>(bh) * N * D;
     for (int r = 0; r < count; ++r) {
@@ -761,29 +828,6 @@ __global__ __launch_bounds__(256) void k_km_control(
         for (int k = tid; k < D; k += 256)
             cent[(static_cast<size_t>(bh) * M + u) * D + k] = static_cast<double>(load_elem(X + static_cast<size_t>(tok) * D, k));
         if (tid == 0) wb[u] = s_wkeep;
-    }
-    if (tid == 0) {
-        double I = 0.0;
-        for (int b0 = 0; b0 < nblk; b0 += 8) {
-            double v[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = binert[static_cast<size_t>(bh) * nblk + min(b0 + q, nblk - 1)];
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (b0 + q < nblk) I = I + v[q];
-        }
-        I = I / static_cast<double>(batch);
-        KmState s = *st;
-        s.ewa = step == 0 ? I : s.ewa * (1.0 - alpha) + I * alpha;
-        if (s.ewa < s.ewa_min) {
-            s.ewa_min = s.ewa;
-            s.no_imp = 0;
-        } else {
-            s.no_imp += 1;
-        }
-        s.steps = step + 1;
-        if (max_no_improvement > 0 && s.no_imp >= max_no_improvement) s.stop = 1;
-        *st = s;
     }
 }
 
@@ -809,6 +853,10 @@ __global__ __launch_bounds__(256) void k_km_init_state(KmState* __restrict__ sta
 // [Mp + 1] (first member position of each parent), toff [Mp + 1] (first team
 // of each parent: sum of min(R, |C|) over the parents before it), and the
 // pair's team count.  A label outside [0, Mp) sets *bad and is skipped.
+// Labels are read eight groups of 64 ahead, and a group's tokens find those of
+// their own label by one ballot per label bit (a ballot and an LDS round trip
+// per distinct label of a group took 167 us at 32K tokens and 32 parents; now
+// 27).
 __global__ __launch_bounds__(kListThreads) void k_parent_lists(
     const int* __restrict__ labels, int N, int Mp, int R, int* __restrict__ members,
     int* __restrict__ pbeg, int* __restrict__ toff, int* __restrict__ team_count, int* __restrict__ bad) {
@@ -823,12 +871,19 @@ __global__ __launch_bounds__(kListThreads) void k_parent_lists(
     __syncthreads();
     const int seg = (N + kListWaves - 1) / kListWaves;
     const int i0 = min(N, w * seg), i1 = min(N, i0 + seg);
-    for (int i = i0 + lane; i < i1; i += kWave) {
-        const int L = lab[i];
-        if (L < 0 || L >= Mp)
-            atomicOr(bad, 1);
-        else
-            atomicAdd(&s_off[w][L], 1);
+    for (int g0 = i0; g0 < i1; g0 += kListAhead * kWave) {
+        int Ls[kListAhead];
+#pragma unroll
+        for (int q = 0; q < kListAhead; ++q) Ls[q] = lab[min(g0 + q * kWave + lane, i1 - 1)];
+#pragma unroll
+        for (int q = 0; q < kListAhead; ++q) {
+            if (g0 + q * kWave + lane < i1) {
+                if (Ls[q] < 0 || Ls[q] >= Mp)
+                    atomicOr(bad, 1);
+                else
+                    atomicAdd(&s_off[w][Ls[q]], 1);
+            }
+        }
     }
     __syncthreads();
     // parent sizes and team counts, scanned over labels in chunks
@@ -879,23 +934,28 @@ __global__ __launch_bounds__(kListThreads) void k_parent_lists(
         toff[static_cast<size_t>(bh) * (Mp + 1) + Mp] = s_carry[1];
         team_count[bh] = s_carry[1];
     }
-    // placement: per 64-token group, one ballot per distinct label
+    // placement, a 64-token group at a time
     const uint64_t lt = lanemask_lt();
-    for (int g0 = i0; g0 < i1; g0 += kWave) {
-        const int i = g0 + lane;
-        const int L = i < i1 ? lab[i] : -1;
-        const bool ok = L >= 0 && L < Mp;
-        uint64_t pending = __ballot(ok);
-        while (pending) {
-            const int leader = __ffsll(static_cast<unsigned long long>(pending)) - 1;
-            const int Lv = readlane(L, leader);
-            const uint64_t m = __ballot(ok && L == Lv) & pending;
-            const int base = s_off[w][Lv];
-            if ((m >> lane) & 1ull) mem[base + __popcll(m & lt)] = i;
-            // the new offset depends on the value every lane read, and a
-            // wave's LDS accesses complete in order
-            if (lane == leader) s_off[w][Lv] = base + static_cast<int>(__popcll(m));
-            pending &= ~m;
+    const int bits = 32 - __clz(Mp);
+    for (int g0 = i0; g0 < i1; g0 += kListAhead * kWave) {
+        int Ls[kListAhead];
+#pragma unroll
+        for (int q = 0; q < kListAhead; ++q) Ls[q] = lab[min(g0 + q * kWave + lane, i1 - 1)];
+#pragma unroll
+        for (int q = 0; q < kListAhead; ++q) {
+            const int i = g0 + q * kWave + lane, L = Ls[q];
+            const bool ok = i < i1 && L >= 0 && L < Mp;
+            uint64_t same = __ballot(ok);
+            for (int b = 0; b < bits; ++b) {  // uniform
+                const uint64_t set = __ballot((L >> b) & 1);
+                same &= (L >> b) & 1 ? set : ~set;
+            }
+            if (ok) {
+                const int base = s_off[w][L];
+                mem[base + __popcll(same & lt)] = i;
+                // a wave's LDS accesses complete in order
+                if ((same & lt) == 0) s_off[w][L] = base + static_cast<int>(__popcll(same));
+            }
         }
     }
 }

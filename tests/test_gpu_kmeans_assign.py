@@ -3,7 +3,9 @@ decide: equal keys and centers (ties go to the lower center), zero keys, keys
 whose squares leave fp32's range on either side, more centers than one tile of
 32, and token counts around a workgroup's 64 points.  Labels and steps are
 compared with the oracle bit for bit: where an estimate leaves the choice open
-the definition's fp64 distances take it, so nothing has a tolerance.
+the definition's fp64 distances take it, so nothing has a tolerance.  Also a
+seeding sample and a batch past what one load per thread and lane covers, and
+member lists by label bits at the smallest and largest label counts.
 """
 import numpy as np
 import pytest
@@ -11,7 +13,7 @@ import torch
 
 import oracle
 import paper_2609_35629_amd as sp
-from tests.gpu_util import log
+from tests.gpu_util import gpu_tables, log
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +62,31 @@ def test_labels_match_oracle(kind, N, P, d, dtype):
     r = oracle.kmeans_parents(x.to(torch.float64).numpy(), P, th)
     assert steps[0] == r.steps
     np.testing.assert_array_equal(labels.cpu().numpy()[0, 0], r.labels)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_large_sample_and_batch(dtype):
+    # 18000 sample positions: 18 per thread, past the 16 kept in registers;
+    # 6000 batch points: 94 inertia partials
+    log(f"[gpu] kmeans large sample {dtype}")
+    x = _keys("normal", 20000, 64, dtype)
+    th = oracle.KMeansSettings(batch=6000, max_iter=1)
+    labels, _, steps = sp.kmeans_parents(x[None, None].cuda(), 4000, batch_size=th.batch, max_iter=th.max_iter)
+    r = oracle.kmeans_parents(x.to(torch.float64).numpy(), 4000, th)
+    assert steps[0] == r.steps
+    np.testing.assert_array_equal(labels.cpu().numpy()[0, 0], r.labels)
+
+
+@pytest.mark.parametrize("num", [1, 2, 63, 64, 65, 1024])
+@pytest.mark.parametrize("N", [1, 64, 1025, 9001])
+def test_member_lists_by_label_bits(num, N):
+    log(f"[gpu] member lists labels={num} N={N}")
+    x = _keys("normal", N, 64, torch.float32)
+    lab = np.random.default_rng(num).integers(0, num, N).astype(np.int32)
+    K = x[None, None].cuda()
+    perm, tb, ts, rt = gpu_tables(sp.build_teams_from_labels(K, K, torch.from_numpy(lab)[None, None].cuda(), num, 2))
+    t = oracle.build_teams_from_labels(x.to(torch.float64).numpy(), lab, 2)
+    np.testing.assert_array_equal(perm[0, 0], t.members)
+    np.testing.assert_array_equal(tb[0, 0, :t.M], t.team_ptr[:-1])
+    np.testing.assert_array_equal(ts[0, 0, :t.M], t.sizes)
+    np.testing.assert_array_equal(rt[0, 0, :t.M], t.rep_token)
