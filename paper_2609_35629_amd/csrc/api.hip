@@ -356,9 +356,9 @@ bool fused_step(santapp_dtype dt, const DecodeLayout& L) {
     return !L.step && dt == SANTAPP_BF16 && fused_wanted() && L.nwg % 8 == 0;
 }
 
-DecodeLayout decode_layout(int B, int Hq, int Hkv, int T, int d, int M, int Kp, const int* cap, int cus,
-                           santapp_dtype dt, size_t ws_bytes) {
-    DecodeLayout L;
+StepLayout decode_layout(int B, int Hq, int Hkv, int T, int d, int M, int Kp, const int* cap, int cus,
+                         santapp_dtype dt, size_t ws_bytes) {
+    StepLayout L;
     const size_t BH = static_cast<size_t>(B) * Hkv, BQ = static_cast<size_t>(B) * Hq;
     const int G = Hq / Hkv;
     if (step_mode(dt, d, static_cast<long long>(BH), M, Kp, false, cus)) {
@@ -382,22 +382,22 @@ DecodeLayout decode_layout(int B, int Hq, int Hkv, int T, int d, int M, int Kp, 
     L.part = c.take(BH * L.maxwp * G * state_stride(d) * sizeof(float));
     L.total = c.off;
     if (M > kDecodeThreads && !fused_step(dt, L)) {
-        DecodeLayout X = L;
+        StepLayout X = L;
         X.keys = true;
-        X.kstride = (M + 3) / 4 * 4;
-        const size_t n = BQ * X.kstride;
-        X.yu = c.take(n * sizeof(uint32_t));
-        X.yk = c.take(n * sizeof(uint64_t));
-        X.phi = c.take(n * sizeof(double));
-        X.tokens = c.take(BH * key_blocks(M) * sizeof(uint64_t));
+        X.key.stride = (M + 3) / 4 * 4;
+        const size_t n = BQ * X.key.stride;
+        X.key.yu = c.take(n * sizeof(uint32_t));
+        X.key.yk = c.take(n * sizeof(uint64_t));
+        X.key.phi = c.take(n * sizeof(double));
+        X.key.tokens = c.take(BH * key_blocks(M) * sizeof(uint64_t));
         X.total = c.off;
         if (X.total <= ws_bytes) return X;
     }
     return L;
 }
 
-DecodeLayout dense_layout(int B, int Hq, int Hkv, int N, int T, int d, int cus, santapp_dtype dt) {
-    DecodeLayout L;
+StepLayout dense_layout(int B, int Hq, int Hkv, int N, int T, int d, int cus, santapp_dtype dt) {
+    StepLayout L;
     const size_t BH = static_cast<size_t>(B) * Hkv;
     const int G = Hq / Hkv;
     if (step_mode(dt, d, static_cast<long long>(BH), 0, 0, true, cus)) {
@@ -872,9 +872,9 @@ santapp_status santapp_decode_launch_info(const santapp_teams* t, int Hq, int T,
     if (T < 0 || K < 1) return fail(SANTAPP_EINVAL, "T must be >= 0 and K >= 1");
     const int Kp = std::min(K, t->M);
     const bool dense = Kp == t->M;
-    const DecodeLayout L = dense ? dense_layout(t->B, Hq, t->Hkv, t->N, T, t->d, t->cus, t->dtype)
-                                 : decode_layout(t->B, Hq, t->Hkv, T, t->d, t->M, Kp, t->cap.data(), t->cus,
-                                                 t->dtype);
+    const StepLayout L = dense ? dense_layout(t->B, Hq, t->Hkv, t->N, T, t->d, t->cus, t->dtype)
+                               : decode_layout(t->B, Hq, t->Hkv, T, t->d, t->M, Kp, t->cap.data(), t->cus,
+                                               t->dtype);
     const bool fused = fused_step(t->dtype, L);
     *kernels = L.step || fused ? 1 : (dense ? 2 : 3);
     *workgroups = L.nwg;
@@ -924,9 +924,9 @@ santapp_status santapp_decode(const santapp_teams* t, const float* q, const void
     const int Kp = std::min(K, t->M);
     const bool dense = Kp == t->M;
     if (!dense && t->M > kMaxTeams) return fail(SANTAPP_ELIMIT, "%d teams per KV head exceed %d", t->M, kMaxTeams);
-    const DecodeLayout L = dense ? dense_layout(t->B, Hq, t->Hkv, t->N, T, t->d, t->cus, t->dtype)
-                                 : decode_layout(t->B, Hq, t->Hkv, T, t->d, t->M, Kp, t->cap.data(), t->cus,
-                                                 t->dtype, ws_bytes);
+    const StepLayout L = dense ? dense_layout(t->B, Hq, t->Hkv, t->N, T, t->d, t->cus, t->dtype)
+                               : decode_layout(t->B, Hq, t->Hkv, T, t->d, t->M, Kp, t->cap.data(), t->cus,
+                                               t->dtype, ws_bytes);
     if (!workspace || ws_bytes < L.total)
         return fail(SANTAPP_EWORKSPACE, "workspace of %zu bytes needed (got %zu)", L.total, ws_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -960,6 +960,7 @@ santapp_status santapp_decode(const santapp_teams* t, const float* q, const void
     A.step = step;
     if (L.keys) A.token = call_token();
     A.lay = L;
+    A.key = L.key;
     A.ws = static_cast<char*>(workspace);
     if (dbg) {
         A.dbg_phi = dbg->phi;
@@ -1069,7 +1070,7 @@ santapp_status santapp_dense_decode(const float* q, const void* K, const void* V
     if (d != 64 && d != 128) return fail(SANTAPP_ELIMIT, "head dim %d not supported (64 or 128)", d);
     if (!(scale >= 0.0) || !isfinite(scale)) return fail(SANTAPP_EINVAL, "scale must be finite and >= 0");
     if (scale == 0.0) scale = 1.0 / sqrt(static_cast<double>(d));
-    const DecodeLayout L = dense_layout(B, Hq, Hkv, N, T, d, device_cus(), dtype);
+    const StepLayout L = dense_layout(B, Hq, Hkv, N, T, d, device_cus(), dtype);
     if (!workspace || ws_bytes < L.total)
         return fail(SANTAPP_EWORKSPACE, "workspace of %zu bytes needed (got %zu)", L.total, ws_bytes);
     DecodeArgs A{};
@@ -1094,6 +1095,7 @@ santapp_status santapp_dense_decode(const float* q, const void* K, const void* V
     A.scale = scale;
     A.scale_log2 = static_cast<float>(scale * 1.4426950408889634);
     A.lay = L;
+    A.key = L.key;
     A.ws = static_cast<char*>(workspace);
     A.fused = fused_step(dtype, L);
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -845,15 +845,15 @@ __device__ void sample_head(const DecodeArgs& a, const Views& v, int p, int j, c
 // all pairs, and the last workgroup of a pair to finish selects for its heads.
 // ---------------------------------------------------------------------------
 struct KeyViews {
-    uint32_t* yu;      // [B Hq, kstride] order key of the perturbed score rounded to fp32
-    uint64_t* yk;      // [B Hq, kstride] its order key
-    double* phi;       // [B Hq, kstride]
+    uint32_t* yu;      // [B Hq, stride] order key of the perturbed score rounded to fp32
+    uint64_t* yk;      // [B Hq, stride] its order key
+    double* phi;       // [B Hq, stride]
     uint64_t* arrive;  // [BH, workgroups of a pair] the call's token, once its scores are out
 };
 
 __device__ __forceinline__ KeyViews key_views(const DecodeArgs& a) {
-    return KeyViews{reinterpret_cast<uint32_t*>(a.ws + a.lay.yu), reinterpret_cast<uint64_t*>(a.ws + a.lay.yk),
-                    reinterpret_cast<double*>(a.ws + a.lay.phi), reinterpret_cast<uint64_t*>(a.ws + a.lay.tokens)};
+    return KeyViews{reinterpret_cast<uint32_t*>(a.ws + a.key.yu), reinterpret_cast<uint64_t*>(a.ws + a.key.yk),
+                    reinterpret_cast<double*>(a.ws + a.key.phi), reinterpret_cast<uint64_t*>(a.ws + a.key.tokens)};
 }
 
 // Maximum of an unsigned value over the wave (wave-uniform).
@@ -939,10 +939,10 @@ template <int KQ>
 __device__ void key_select(const DecodeArgs& a, const Views& v, int p, char* lds) {
     const int lane = lane_id(), h = wave_id(), M = a.M, Kp = a.Kp;
     const int b = p / a.Hkv, kv = p - b * a.Hkv;
-    const size_t bq = static_cast<size_t>(b) * a.Hq + kv * a.G + h, row = bq * a.lay.kstride;
+    const size_t bq = static_cast<size_t>(b) * a.Hq + kv * a.G + h, row = bq * a.key.stride;
     const KeyViews kw = key_views(a);
     // the scores come from other workgroups of this launch: coherent loads
-    const uint32_t ks = static_cast<uint32_t>(a.lay.kstride);
+    const uint32_t ks = static_cast<uint32_t>(a.key.stride);
     const __amdgpu_buffer_rsrc_t ru = coherent_rsrc(kw.yu + row, 4u * ks), rk = coherent_rsrc(kw.yk + row, 8u * ks),
                                  rp = coherent_rsrc(kw.phi + row, 8u * ks);
     auto key_of = [&](int g) __attribute__((always_inline)) {
@@ -1241,7 +1241,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_route_select(DecodeArgs a) {
     for (int k = 0; k < 2; ++k) {
         const int h = 4 * k + c;
         if (h < G && g0 + t < M) {
-            const size_t bq = static_cast<size_t>(b) * a.Hq + kv * G + h, o = bq * a.lay.kstride + g;
+            const size_t bq = static_cast<size_t>(b) * a.Hq + kv * G + h, o = bq * a.key.stride + g;
             const double phi = ln + a.scale * acc[k], y = phi + gumbel_of_word(s_word[h][t]);
             store_u32_coherent(kw.yu + o, order_key(static_cast<float>(y)));
             store_u64_coherent(kw.yk + o, order_key(y));
