@@ -381,7 +381,12 @@ StepLayout decode_layout(int B, int Hq, int Hkv, int T, int d, int M, int Kp, co
     L.lc = c.take(BQ * M * sizeof(float));
     L.part = c.take(BH * L.maxwp * G * state_stride(d) * sizeof(float));
     L.total = c.off;
-    if (M > kDecodeThreads && !fused_step(dt, L)) {
+    // The launch over all teams pays from about 1024 teams on, while the heads
+    // leave half the compute units to it (one step, this against a workgroup per
+    // head): 28 heads 656 teams 32.3 / 28.0 us, 1024 33.9 / 32.4, 1280 35.0 /
+    // 35.6, 2048 37.1 / 43.1; 112 heads 1024 teams 48.4 / 46.9, 1280 51.3 /
+    // 51.4, 2048 62.7 / 68.4; 256 heads 1024 teams 51.4 / 50.2, 2048 68.9 / 64.5.
+    if (M > kKeyMinTeams && BQ <= static_cast<size_t>(cus) / 2 && !fused_step(dt, L)) {
         StepLayout X = L;
         X.keys = true;
         X.key.stride = (M + 3) / 4 * 4;

@@ -1194,8 +1194,8 @@ __device__ void key_select(const DecodeArgs& a, const Views& v, int p, char* lds
 //
 // One workgroup per query head, which read its pair's keys at 25 GB/s and had
 // the whole table's noise to draw, took 84 us at 8192 teams (four pairs of
-// seven heads) and 25 us at 2048 (sixteen pairs); this takes 24 and 18 us.  At 512
-// teams and fewer the former (8 us, one launch less deep) is as fast.
+// seven heads) and 25 us at 2048 (sixteen pairs); this takes 24 and 18 us.  For
+// fewer teams or many heads the former is as fast (decode_layout).
 template <typename T, int D, int KQ>
 __global__ __launch_bounds__(kThreads, 1) void k_route_select(DecodeArgs a) {
     using Q = Quarter<T, D>;

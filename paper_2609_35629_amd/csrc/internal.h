@@ -60,7 +60,7 @@ struct DecodeLayout {
     size_t epoch = 0, xk = 0;
 };
 
-// Split launches of more than 512 teams (`keys`) add per (query head, team) the
+// Split launches over larger tables (`keys`) add per (query head, team) the
 // order key of the perturbed score in fp32 (`yu`) and fp64 (`yk`) and phi
 // (`phi`), rows of `stride` teams, and a word per workgroup of the sampling
 // launch (`tokens`) that a workgroup sets to the call's token; nothing of these
@@ -91,6 +91,7 @@ int step_wgs(int cus, long long BH);
 // Teams of a workgroup of the sampling launch that keeps scores in memory, and
 // its workgroups per (b, kv) pair.
 constexpr int kKeyTeamsWg = 128;
+constexpr int kKeyMinTeams = 1024;  // tables of more teams take it (decode_layout's rule)
 constexpr int key_blocks(int M) { return (M + kKeyTeamsWg - 1) / kKeyTeamsWg; }
 
 // Workgroup w of an attention grid of nwg workgroups serving BH (b, kv)
@@ -276,8 +277,8 @@ struct DecodeArgs {
     hipEvent_t ev_stop;      // stamped at its end (nullable)
     bool fused;              // sampling, attention and merge in one launch
     // Where lay.keys.  Last, past what the other kernels fetch: between the
-    // fields above they made the
-    // single-launch step at the 32K prompt 22.0 us instead of 21.7.
+    // fields above they made the single-launch step at the 32K prompt 22.0 us
+    // instead of 21.7.
     KeyLayout key;
     uint64_t token;          // of this call
 };

@@ -32,8 +32,8 @@ def _small_workspace(teams, db, wl, K):
 
 
 @pytest.mark.parametrize("dtype,d,Hq,Hkv,N,P,R,budgets", [
-    ("bf16", 128, 7, 1, 520, 1, 1, (1, 63, 64, 255, 256, 519)),
-    ("bf16", 64, 16, 2, 4096, 16, 4, (32, 65, 130, 300, 1023)),
+    ("bf16", 128, 7, 1, 1032, 1, 1, (1, 63, 64, 255, 256, 1031)),
+    ("bf16", 64, 16, 2, 4100, 16, 4, (32, 65, 130, 300, 1023)),
     ("fp32", 128, 5, 1, 2051, 4, 2, (31, 128, 700)),
     ("fp32", 64, 8, 1, 2561, 2, 1, (40, 1200)),
     ("bf16", 128, 8, 1, 8192, 1, 1, (33, 200, 4000)),
@@ -45,7 +45,7 @@ def test_budgets_match_oracle_and_small_workspace(dtype, d, Hq, Hkv, N, P, R, bu
     db = dev_batch(b)
     ot = oracle_teams(b)
     teams = sp.build_teams(db.K, db.V, P, R)
-    assert teams.M > 512
+    assert teams.M > 1024
     pairs = [(0, h) for h in range(Hq)]
     for K in budgets:
         log(f"[gpu] sampling {dtype} d={d} Hq={Hq} Hkv={Hkv} M={teams.M} K={K}")
@@ -74,11 +74,11 @@ def test_absent_teams_tie():
     b = datagen.generate(wl)
     db = dev_batch(b)
     rng = np.random.default_rng(2)
-    lab = np.stack([rng.integers(0, 300, size=3000), rng.integers(0, 20, size=3000)])[None].astype(np.int32)
-    teams = sp.build_teams_from_labels(db.K, db.V, torch.from_numpy(lab).cuda(), 300, 3)
+    lab = np.stack([rng.integers(0, 400, size=3000), rng.integers(0, 20, size=3000)])[None].astype(np.int32)
+    teams = sp.build_teams_from_labels(db.K, db.V, torch.from_numpy(lab).cuda(), 400, 3)
     count = teams.team_count().cpu().numpy()[0]
     K = 100
-    assert teams.M > 512 and count[1] <= K < count[0]
+    assert teams.M > 1024 and count[1] <= K < count[0]
     log(f"[gpu] absent teams M={teams.M} counts={count.tolist()} K={K}")
     dbg = sp.DebugOut(1, 4, 2, teams.M, K)
     out = sp.decode(teams, db.q, db.sK, db.sV, K, seed=3, step=1, scale=wl.scale, debug=dbg).cpu().numpy()
@@ -94,11 +94,11 @@ def test_absent_teams_tie():
 def test_graph_replays_and_shared_workspace():
     # a captured step brings the same token at every replay; between replays
     # other steps (another budget, and one over every team) use its workspace
-    wl = datagen.WORKLOADS["qwen8k"].with_(name="replay", N=4096, P=4, R=1, Hq=8, Hkv=2, T=4)
+    wl = datagen.WORKLOADS["qwen8k"].with_(name="replay", N=4104, P=4, R=1, Hq=8, Hkv=2, T=4)
     b = datagen.generate(wl)
     db = dev_batch(b)
     teams = sp.build_teams(db.K, db.V, wl.P, wl.R)
-    assert teams.M > 512
+    assert teams.M > 1024
     n = max(sp.decode_workspace(teams, wl.Hq, wl.T, k).numel() for k in (32, 300, teams.M))
     ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
     want = sp.decode(teams, db.q, db.sK, db.sV, 32, seed=1, step=2)
@@ -119,3 +119,18 @@ def test_graph_replays_and_shared_workspace():
             got = sp.decode(teams, db.q, db.sK, db.sV, k, seed=1, step=2, workspace=ws)
             torch.cuda.synchronize()
             assert torch.equal(got, ref)
+
+
+def test_rule_by_teams_and_heads():
+    # the scores' regions come in past 1024 teams, and only while the heads
+    # take at most half the compute units
+    half = torch.cuda.get_device_properties(0).multi_processor_count // 2
+    for B, keys in ((1, True), (half // 4, True), (half // 4 + 1, False)):
+        size = []
+        for N in (1024, 1025):
+            log(f"[gpu] sampling rule B={B} Hq=4 M={N}")
+            K = torch.randn((B, 1, N, 64), device="cuda").bfloat16()
+            teams = sp.build_teams(K, K, 1, 1)
+            assert teams.M == N
+            size.append(sp.decode_workspace(teams, 4, 0, 8).numel())
+        assert (size[1] - size[0] > 20 * B * 4 * 1024) == keys
