@@ -49,6 +49,7 @@
 
 #include <hip/hip_ext.h>
 
+#include "arrive.h"
 #include "common.h"
 #include "internal.h"
 
@@ -842,7 +843,7 @@ __device__ void sample_head(const DecodeArgs& a, const Views& v, int p, int j, c
 
 // ---------------------------------------------------------------------------
 // Sampling of larger tables (split launches): one launch routes all teams of
-// all pairs, and the last workgroup of a pair to finish selects for its heads.
+// all pairs, and the last workgroup of a pair to arrive selects for its heads.
 // ---------------------------------------------------------------------------
 struct KeyViews {
     uint32_t* yu;      // [B Hq, stride] order key of the perturbed score rounded to fp32
@@ -1181,16 +1182,42 @@ __device__ void key_select(const DecodeArgs& a, const Views& v, int p, char* lds
     }
 }
 
+// A pair's arrival slots in the workspace, one per workgroup, handled by one wave.
+struct ArrivalSlots {
+    uint64_t* slot;
+    int mine, n;
+    __device__ void leave(uint64_t token) {
+        if (lane_id() == 0) store_u64_coherent(slot + mine, token);
+        lds_order();
+        __builtin_amdgcn_s_waitcnt(0);  // the store is complete before the slots are read
+        lds_order();
+    }
+    __device__ bool all(uint64_t token) {
+        bool here = true;
+        for (int i = lane_id(); i < n; i += kWave) here = here && load_u64_coherent(slot + i) == token;
+        return __ballot(!here) == 0;
+    }
+    __device__ bool take(uint64_t token) {
+        bool mine = false;
+        if (lane_id() == 0)
+            mine = __hip_atomic_compare_exchange_strong(slot, &token, 0ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT);
+        return __ballot(mine) != 0;
+    }
+    __device__ void clear() {
+        for (int i = lane_id(); i < n; i += kWave) store_u64_coherent(slot + i, 0);
+    }
+};
+
 // A workgroup takes kRouteTeamsWg teams of a pair, a wave 16 of them: phi of
 // every head (16 x 16 tiles of v_mfma_f64_16x16x4_f64: A head i on lanes
 // 16 c + i, B team j on lanes 16 c + j, lane group c holding dims [c D / 4,
 // (c + 1) D / 4); result register q of lane 16 c + j is head 4 q + c of team
 // j), the workgroup's Philox blocks one a thread, and on the result's lanes the
-// Gumbel variates and keys.  The pair's last workgroup (dispatched after the
-// others, which wait for nothing) waits until all have left the call's token,
-// clears the tokens for the next call (a replayed graph brings the same one)
-// and selects, one wave per head.  What a workspace held before cannot be
-// taken for the 64-bit token, so it needs no state between calls.
+// Gumbel variates and keys.  The workgroup that finds all of its pair's
+// arrived selects, one wave per head; none waits, so a launch held back by other
+// streams' work only takes longer.  What a workspace held before cannot be taken
+// for the 64-bit token, so it needs no state between calls.
 //
 // One workgroup per query head, which read its pair's keys at 25 GB/s and had
 // the whole table's noise to draw, took 84 us at 8192 teams (four pairs of
@@ -1202,7 +1229,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_route_select(DecodeArgs a) {
     typedef double f64x4 __attribute__((ext_vector_type(4)));
     extern __shared__ __align__(16) char s_keys[];
     uint64_t(*const s_word)[kRouteTeamsWg] = reinterpret_cast<uint64_t(*)[kRouteTeamsWg]>(s_keys);
-    __shared__ int s_ok;
+    __shared__ int s_last;
     const int tid = threadIdx.x, lane = lane_id(), c = lane >> 4, j = lane & 15;
     const int p = blockIdx.y, b = p / a.Hkv, kv = p - b * a.Hkv, G = a.G, M = a.M;
     const int g0 = blockIdx.x * kRouteTeamsWg, t = wave_id() * 16 + j;
@@ -1251,32 +1278,14 @@ __global__ __launch_bounds__(kThreads, 1) void k_route_select(DecodeArgs a) {
         }
     }
     drain_and_sync();
-    uint64_t* const arrive = kw.arrive + static_cast<size_t>(p) * gridDim.x;
-    if (tid == 0) store_u64_coherent(arrive + blockIdx.x, a.token);
-    if (blockIdx.x + 1 != gridDim.x) return;  // uniform
     if (tid < kWave) {
-        bool here = false;
-        for (int it = 0; it < kSpinLimit; ++it) {
-            here = true;
-            for (int i = lane; i < static_cast<int>(gridDim.x); i += kWave)
-                here = here && load_u64_coherent(arrive + i) == a.token;
-            if (__ballot(!here) == 0) break;  // uniform
-            __builtin_amdgcn_s_sleep(2);
-        }
-        const uint64_t missing = __ballot(!here);
-        for (int i = lane; i < static_cast<int>(gridDim.x); i += kWave) store_u64_coherent(arrive + i, 0);
-        if (lane == 0) s_ok = missing == 0 ? 1 : 0;
+        ArrivalSlots slots{kw.arrive + static_cast<size_t>(p) * gridDim.x, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x)};
+        const bool last = last_to_arrive(slots, a.token);
+        if (lane == 0) s_last = last ? 1 : 0;
     }
     __syncthreads();
-    const Views v = views_of(a);
-    if (wave_id() >= G) return;
-    if (s_ok != 0) {
-        key_select<KQ>(a, v, p, s_keys);
-    } else {  // a wait that ran out: the head's output becomes NaN
-        const size_t bq = static_cast<size_t>(b) * a.Hq + kv * G + wave_id();
-        for (int i = lane; i < a.lay.swords; i += kWave) v.sbits[bq * a.lay.swords + i] = i == 0 ? 1 : 0;
-        if (lane == 0) v.lc[bq * M] = __builtin_nanf("");
-    }
+    if (s_last == 0 || wave_id() >= G) return;
+    key_select<KQ>(a, views_of(a), p, s_keys);
 }
 
 // Scores of one 16-row tile.  Lane l = 16 c + j feeds row j of the tile and
