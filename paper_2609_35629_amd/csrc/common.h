@@ -225,6 +225,14 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 __device__ __forceinline__ int wave_id() { return threadIdx.x / kWave; }
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
+// Orders this wave's memory accesses for the compiler where its lanes read what
+// others of them wrote (the LDS executes a wave's instructions in order).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // DPP row rotations (within each 16-lane row of the wave): row_ror:n is
 // control word 0x120 + n.
 template <int CTRL>

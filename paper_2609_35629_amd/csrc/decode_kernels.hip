@@ -80,12 +80,6 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // wait for the value copies in flight).
 __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
 
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Every memory access of every thread of the workgroup is complete, then the
 // workgroup synchronises (the barrier alone does not wait for stores).
 __device__ __forceinline__ void drain_and_sync() {

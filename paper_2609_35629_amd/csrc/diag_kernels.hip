@@ -189,11 +189,13 @@ __global__ __launch_bounds__(kKlThreads) void k_kl_rows(const T* __restrict__ pa
     if (row0 < N) {  // uniform
         const int g0 = team_of_row(begin, M, row0);
         s_team[w][lane] = g0;
+        wave_lds_sync();
         for (int g = g0 + 1 + lane;; g += kWave) {
             const int first = g < M ? begin[g] : N;
             if (first <= last) atomicMax(&s_team[w][first - row0], g);
             if (__ballot(first <= last) != ~0ull) break;
         }
+        wave_lds_sync();
         team = s_team[w][lane];
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) {

@@ -1,0 +1,38 @@
+"""Where lanes of a wave read from LDS what other lanes of it wrote, without a
+workgroup barrier, the compiled code must keep the accesses in order: it may
+otherwise hand a lane the value that the lane itself wrote.  Checked in the
+LLVM IR of the kernels, where the order is a wave barrier between fences."""
+import re
+import subprocess
+
+import pytest
+
+from paper_2609_35629_amd.build import CFLAGS, CSRC, hipcc
+
+
+def _kernels(src, name, tmp_path):
+    ir = str(tmp_path / "k.ll")
+    r = subprocess.run([hipcc(), *CFLAGS, "--offload-device-only", "-emit-llvm", "-S", f"{CSRC}/{src}", "-o", ir],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    with open(ir) as f:
+        found = re.findall(r"^define[^\n]*" + name + r".*?^}", f.read(), re.M | re.S)
+    assert found
+    return found
+
+
+def _ordered(text):
+    """Whether the text holds release fence, wave barrier, acquire fence."""
+    return re.search(r'syncscope\("wavefront"\) release.*?wave\.barrier.*?syncscope\("wavefront"\) acquire', text, re.S)
+
+
+def test_team_marks_of_the_routing_kl(tmp_path):
+    # lane's own mark stored, other lanes' marks by atomic maximum, then read
+    for body in _kernels("diag_kernels.hip", "k_kl_rows", tmp_path):
+        marks = [m.start() for m in re.finditer(r"atomicrmw max ptr addrspace\(3\)", body)]
+        assert len(marks) == 1
+        store = body.rfind("store i32", 0, marks[0])
+        load = re.compile(r"load i32, ptr addrspace\(3\)").search(body, marks[0]).start()
+        assert _ordered(body[store:marks[0]])
+        assert _ordered(body[marks[0]:load])
+
