@@ -950,12 +950,13 @@ __global__ __launch_bounds__(kListThreads) void k_parent_lists(
                 const uint64_t set = __ballot((L >> b) & 1);
                 same &= (L >> b) & 1 ? set : ~set;
             }
+            const int base = ok ? s_off[w][L] : 0;
+            wave_lds_sync();
             if (ok) {
-                const int base = s_off[w][L];
                 mem[base + __popcll(same & lt)] = i;
-                // a wave's LDS accesses complete in order
                 if ((same & lt) == 0) s_off[w][L] = base + static_cast<int>(__popcll(same));
             }
+            wave_lds_sync();
         }
     }
 }

@@ -36,3 +36,13 @@ def test_team_marks_of_the_routing_kl(tmp_path):
         assert _ordered(body[store:marks[0]])
         assert _ordered(body[marks[0]:load])
 
+
+def test_member_offsets_of_the_parent_lists(tmp_path):
+    # each group of 64 tokens reads its labels' offsets, then one lane per
+    # label moves the label's offset on for the next group
+    for body in _kernels("kmeans_kernels.hip", "k_parent_lists", tmp_path):
+        place = body[body.rfind("s.barrier"):]
+        acc = [(m.start(), m.group(1)) for m in re.finditer(r"\b(load|store) i32[^\n]*ptr addrspace\(3\)", place)]
+        assert len(acc) >= 4
+        for (a, x), (b, y) in zip(acc, acc[1:]):
+            assert x == y or _ordered(place[a:b]), place[a:b]
