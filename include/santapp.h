@@ -32,7 +32,9 @@
  *     santapp_dtype; queries are fp32; outputs are fp32.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *     Every call only enqueues work on that stream; none synchronises except
- *     santapp_build_teams, which waits for its own kernels before returning.
+ *     santapp_build_teams, santapp_build_teams_from_labels and
+ *     santapp_kmeans_parents, which wait for their own kernels before
+ *     returning.
  *   - Every call returns a santapp_status.  On failure nothing is enqueued
  *     after the failing step and santapp_last_error() returns a message for
  *     the calling thread.  No call aborts the process.
@@ -54,7 +56,7 @@ typedef enum {
     SANTAPP_OK = 0,
     SANTAPP_EINVAL = 1,     /* invalid argument (size, budget, null pointer, scale) */
     SANTAPP_EDTYPE = 2,     /* unsupported element type                             */
-    SANTAPP_ENOMEM = 3,     /* device allocation failed (santapp_build_teams only)  */
+    SANTAPP_ENOMEM = 3,     /* device allocation failed (the calls that allocate)   */
     SANTAPP_EHIP = 4,       /* a HIP runtime call or kernel launch failed           */
     SANTAPP_EWORKSPACE = 5, /* workspace missing or smaller than required           */
     SANTAPP_ELIMIT = 6      /* valid but beyond this library's supported sizes      */
@@ -241,7 +243,13 @@ typedef struct {
  * routing scores, the samples and partial results, with per (b, kv) pair
  * either a call counter whose value tags every word a call publishes (the
  * single-launch step) or counters that every completed call leaves at zero
- * (the three-launch kernels).  A workspace must be zeroed once before its
+ * (the three-launch kernels).  Sampled steps over more than 1024 teams per
+ * (b, kv), with at most half as many query heads (B * Hq) as compute units,
+ * add 20 bytes per (query head, team) for scores kept in memory, and a word
+ * per sampling workgroup that every completed call leaves at zero; a workspace
+ * without room for these is accepted down to the size without them, and the
+ * step then samples by the kernel that keeps its scores on chip (the same
+ * sample, slower).  A workspace must be zeroed once before its
  * first use (santapp_workspace_zero) and needs nothing between calls.  Calls
  * that share a workspace must not overlap in time (use one workspace per
  * stream).  The size depends on the compute units of the device the table
@@ -252,9 +260,8 @@ santapp_status santapp_decode_workspace_bytes(const santapp_teams* teams, int Hq
 
 /*
  * How santapp_decode runs a step with these sizes (host-only query): the
- * kernel launches of one step in *kernels (1 for the single-launch step,
- * which bf16 tables of at most 512 teams per KV head and budgets of at most
- * 128 teams take, and for the launches SANTAPP_DECODE_LAUNCH=fused asks for;
+ * kernel launches of one step in *kernels (1 for the single-launch step, see
+ * santapp_decode, and for the launches SANTAPP_DECODE_LAUNCH=fused asks for;
  * 3 otherwise for a sampled step, 2 for a budget that takes every team) and
  * the workgroups of its main launch in *workgroups.  Errors as
  * santapp_decode_workspace_bytes.
@@ -287,13 +294,14 @@ santapp_status santapp_workspace_zero(void* ws, size_t bytes, void* stream);
  * out:      [B,Hq,d] fp32 estimate U^ / Z^.
  * Routing logits, the perturbed scores, the selection and tau are computed in
  * fp64; attention scores and the online softmax in fp32.
- * A step on a bf16 table with d of 64 or 128, at most 512 teams per (b, kv)
- * and at most one (b, kv) pair per compute unit runs as one launch, whose
- * workgroups hand the perturbed scores and their partial results to each
- * other through tagged words in the workspace; any other step runs as three
- * launches (sampling, attention, merge).  santapp_decode_launch_info reports
+ * A step on a bf16 table with at most one (b, kv) pair per compute unit, that
+ * takes every team or samples from at most 512 teams per (b, kv), runs as one
+ * launch, whose workgroups hand the perturbed scores and their partial results
+ * to each other through tagged words in the workspace; any other sampled step
+ * runs as three launches (sampling, attention, merge), any other that takes
+ * every team as two.  santapp_decode_launch_info reports
  * which.  The environment variable SANTAPP_DECODE_LAUNCH (read at the first
- * call of a process) set to "split" forces the three launches, "fused" their
+ * call of a process) set to "split" forces the separate launches, "fused" their
  * one-launch form with counters in the workspace.
  * Never allocates and never synchronises.
  */
@@ -309,8 +317,10 @@ santapp_status santapp_decode(const santapp_teams* teams, const float* q, const 
  * buffer the library owns -- a static device array of 4 MiB on every GPU the
  * library runs on, held until the process ends.  The call allocates nothing
  * and never synchronises; its first use on a device enqueues a clear of that
- * device's array on `stream` ahead of the step.  Steps whose workspace
- * (santapp_decode_workspace_bytes) exceeds 4 MiB return SANTAPP_ELIMIT.
+ * device's array on `stream` ahead of the step.  A step whose workspace
+ * (santapp_decode_workspace_bytes) exceeds 4 MiB takes the least workspace
+ * that santapp_decode accepts, and returns SANTAPP_ELIMIT if that exceeds
+ * 4 MiB too.
  * Every call on one GPU shares that GPU's array, which keeps the last call's
  * contents: calls that overlap in time on one GPU (other streams, other host
  * threads) race and must be serialised by the caller.

@@ -1,5 +1,6 @@
-"""The sampling launch that keeps scores in memory (tables of more than 512
-teams, and a workspace that holds them) against the oracle and against the
+"""The sampling launch that keeps scores in memory (tables of more than 1024
+teams, at most half as many heads as compute units, and a workspace that holds
+the scores) against the oracle and against the
 sampling kernel that a smaller workspace takes: the same teams, tau and log c
 for budgets at the edges of its ranking (64 and 256 listed teams, nearly all
 teams), for the largest table, and where absent teams tie."""

@@ -1,7 +1,7 @@
 """santapp_decode_static (the entry point for callers that cannot allocate)
 against santapp_decode with a workspace of its own: bit-identical outputs and
-diagnostics on two calls in a row, the second on a smaller input, and the
-size limit of the static scratch."""
+diagnostics on two calls in a row, the second on a smaller input, the size
+limit of the static scratch, and steps past it that take a smaller workspace."""
 import numpy as np
 import pytest
 import torch
@@ -62,4 +62,22 @@ def test_static_scratch_limit():
         sp.decode_static(teams, db.q, db.sK, db.sV, wl.K, out, seed=1, step=0)
     assert e.value.status == sp._lib.ELIMIT
     assert b"static scratch" in sp._lib.load().santapp_last_error()
+    teams.close()
+
+
+@pytest.mark.parametrize("N,K", [(2500, 24), (2500, 700), (2048, 24)])
+def test_static_scratch_without_room_for_scores(N, K):
+    # every key its own team: 20 bytes of scores per (head, team) exceed the
+    # scratch, the step without them fits it
+    wl, b, db, teams = _case("qwen8k", N=N, P=1, R=1, T=6, B=4, data_seeds=tuple(range(30, 34)))
+    ws = sp.decode_workspace(teams, wl.Hq, wl.T, K)
+    assert ws.numel() > 4 << 20
+    log(f"[gpu] static scratch: least workspace M={teams.M} K={K}")
+    dbg = [sp.DebugOut(wl.B, wl.Hq, wl.Hkv, teams.M, K) for _ in range(2)]
+    want = sp.decode(teams, db.q, db.sK, db.sV, K, seed=5, step=9, workspace=ws, debug=dbg[0])
+    got = torch.full_like(want, float("nan"))
+    sp.decode_static(teams, db.q, db.sK, db.sV, K, got, seed=5, step=9, debug=dbg[1])
+    torch.cuda.synchronize()
+    assert torch.equal(dbg[0].sel, dbg[1].sel)
+    assert ((got - want).norm() / want.norm()).item() <= 1e-6
     teams.close()
