@@ -208,9 +208,19 @@ santapp_status santapp_teams_set_route_keys(santapp_teams* teams, santapp_route_
 /* Fill *desc with the table's sizes and device pointers. */
 santapp_status santapp_teams_info(const santapp_teams* teams, santapp_teams_desc* desc);
 
-/* Free a table and its device buffers (NULL is ignored).  The caller must
- * make sure no enqueued decode still reads it. */
+/* Free a table (NULL is ignored).  The caller must make sure no enqueued
+ * decode still reads it; the call waits for the device.  The library keeps the
+ * device memory of destroyed tables and of finished preparation calls for later
+ * ones: at most 16 blocks and 1 GiB in all, given back by santapp_trim and
+ * whenever one of its own allocations fails. */
 void santapp_teams_destroy(santapp_teams* teams);
+
+/* Give the device memory that the library keeps for later tables and
+ * preparation calls back to the device (tables in use keep theirs), for
+ * instance before another allocator needs it or after the last build.  Any
+ * thread may call it at any time; it waits for the device when there is
+ * something to free. */
+santapp_status santapp_trim(void);
 
 /*
  * eq. method-budget: K = min(M, S / (P / R)) for a nominal row budget S.

@@ -16,7 +16,7 @@ from . import _lib
 from ._lib import SantappError, check  # noqa: F401
 
 __all__ = ["Teams", "build_teams", "decode", "decode_static", "dense_decode", "decode_workspace",
-           "dense_workspace", "budget_to_K", "SantappError"]
+           "dense_workspace", "budget_to_K", "trim", "SantappError"]
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -129,6 +129,12 @@ def build_teams(K: torch.Tensor, V: torch.Tensor, parent_size: int, reps_per_par
                                           parent_size, reps_per_parent, _stream(stream),
                                           ctypes.byref(h)))
     return Teams(h, K.dtype)
+
+
+def trim() -> None:
+    """Give back the device memory that the library keeps from closed tables
+    and finished preparation calls (santapp_trim)."""
+    check(_lib.load().santapp_trim())
 
 
 def kmeans_parents(K: torch.Tensor, parent_size: int, batch_size: int = 4096, max_iter: int = 100,

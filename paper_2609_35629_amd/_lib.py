@@ -20,6 +20,7 @@ EXPORTS = [
     "santapp_dense_workspace_bytes", "santapp_dense_decode", "santapp_last_error",
     "santapp_teams_set_route_keys", "santapp_routing_kl_workspace_bytes", "santapp_routing_kl",
     "santapp_kmeans_parents", "santapp_build_teams_from_labels", "santapp_decode_launch_info",
+    "santapp_trim",
 ]
 
 ROUTE_REPRESENTATIVE, ROUTE_CENTROID = 0, 1
@@ -79,6 +80,7 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     L.santapp_build_teams_from_labels.argtypes = [vp, vp, i, i, i, i, i, vp, i, i, vp, ctypes.POINTER(vp)]
     L.santapp_teams_destroy.argtypes = [vp]
     L.santapp_teams_destroy.restype = None
+    L.santapp_trim.argtypes = []
     L.santapp_budget_to_K.argtypes = [i, i, i, i, ctypes.POINTER(i)]
     L.santapp_decode_workspace_bytes.argtypes = [vp, i, i, i, ctypes.POINTER(sz)]
     L.santapp_workspace_zero.argtypes = [vp, sz, vp]

@@ -108,7 +108,7 @@ long long team_count(int N, int P, int R) {
 //     scratch whose only stream the caller has waited for.
 //   - Bounded: at most kBlocks blocks and kBytes bytes over all devices; what
 //     does not fit is freed, the oldest first, and all of it is freed when an
-//     allocation fails.
+//     allocation fails or the caller asks for it (santapp_trim).
 //   - Any thread may call; a block goes back to the device it came from.
 class BlockPool {
    public:
@@ -135,7 +135,7 @@ class BlockPool {
         e = hipMalloc(p, bytes);
         if (e != hipSuccess) {
             (void)hipGetLastError();
-            drop_all();
+            (void)drop_all();
             e = hipMalloc(p, bytes);
         }
         *got = bytes;
@@ -176,6 +176,22 @@ class BlockPool {
             (void)hipFree(p);
     }
 
+    // Frees every block kept.
+    hipError_t drop_all() {
+        Block out[kBlocks];
+        int nout = 0;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            while (n_ > 0) out[nout++] = take(0);
+        }
+        hipError_t first = hipSuccess;
+        for (int i = 0; i < nout; ++i) {
+            const hipError_t e = hipFree(out[i].p);
+            if (first == hipSuccess) first = e;
+        }
+        return first;
+    }
+
    private:
     static constexpr int kBlocks = 16;
     static constexpr size_t kBytes = size_t(1) << 30, kGrain = size_t(1) << 16;
@@ -208,15 +224,6 @@ class BlockPool {
             } else {
                 out[nout++] = Block{p, bytes, dev};
             }
-        }
-        for (int i = 0; i < nout; ++i) (void)hipFree(out[i].p);
-    }
-    void drop_all() {
-        Block out[kBlocks];
-        int nout = 0;
-        {
-            std::lock_guard<std::mutex> lock(mu_);
-            while (n_ > 0) out[nout++] = take(0);
         }
         for (int i = 0; i < nout; ++i) (void)hipFree(out[i].p);
     }
@@ -765,6 +772,11 @@ santapp_status santapp_teams_info(const santapp_teams* t, santapp_teams_desc* d)
 }
 
 void santapp_teams_destroy(santapp_teams* t) { free_teams(t); }
+
+santapp_status santapp_trim(void) {
+    const hipError_t e = pool().drop_all();
+    return e == hipSuccess ? ok() : hip_fail(e, "freeing kept blocks");
+}
 
 santapp_status santapp_teams_set_route_keys(santapp_teams* t, santapp_route_key kind, void* stream) {
     if (!t) return fail(SANTAPP_EINVAL, "teams is NULL");
