@@ -631,9 +631,9 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
             const uint64_t at = __ballot(far == wm);
             const int lsel = __ffsll(static_cast<unsigned long long>(at)) - 1;
             const int idx = readlane(fi, lsel);
+            const float nidx = __int_as_float(readlane(__float_as_int(nx0), lsel));
             if (lane == 0)
-                s_best[set + w] = make_float4(wm, __int_as_float(idx), __int_as_float(__popcll(in) > 1 || in2 != 0 ? 1 : 0),
-                                              __int_as_float(readlane(__float_as_int(nx0), lsel)));
+                s_best[set + w] = make_float4(wm, __int_as_float(idx), __int_as_float(__popcll(in) > 1 || in2 != 0 ? 1 : 0), nidx);
             if constexpr (ONE) {
                 if ((lane >> 4) == (lsel >> 4)) {
                     const int kk = lsel & 15;  // wave-uniform

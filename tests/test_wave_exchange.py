@@ -1,7 +1,12 @@
-"""Where lanes of a wave read from LDS what other lanes of it wrote, without a
+"""Data passed between lanes of a wave, checked in the LLVM IR of the kernels.
+
+Where lanes read from LDS what other lanes of their wave wrote, without a
 workgroup barrier, the compiled code must keep the accesses in order: it may
-otherwise hand a lane the value that the lane itself wrote.  Checked in the
-LLVM IR of the kernels, where the order is a wave barrier between fences."""
+otherwise hand a lane the value that the lane itself wrote.  The order is a wave
+barrier between fences.
+
+Where one lane alone runs, no register of another lane may be read: if that
+value is spilled, only the running lane's part is loaded back for the read."""
 import re
 import subprocess
 
@@ -46,3 +51,15 @@ def test_member_offsets_of_the_parent_lists(tmp_path):
         assert len(acc) >= 4
         for (a, x), (b, y) in zip(acc, acc[1:]):
             assert x == y or _ordered(place[a:b]), place[a:b]
+
+
+@pytest.mark.parametrize("src,name", [("build_kernels.hip", "k_build"), ("kmeans_kernels.hip", "k_k"),
+                                      ("diag_kernels.hip", "k_")])
+def test_one_lane_reads_no_other_lane(src, name, tmp_path):
+    for body in _kernels(src, name, tmp_path):
+        lane = set(re.findall(r"^  (%\S+) = and i32 %\S+, 63$", body, re.M))
+        first = {m.group(1) for m in re.finditer(r"^  (%\S+) = icmp eq i32 (%\S+), 0$", body, re.M) if m.group(2) in lane}
+        blocks = dict(re.findall(r"^(\d+|[\w.]+):.*?\n(.*?)(?=^\S|\Z)", body, re.M | re.S))
+        for m in re.finditer(r"br i1 (%\S+), label %(\S+), label %", body):
+            if m.group(1) in first:
+                assert not re.search(r"amdgcn\.(readlane|update\.dpp|ds\.bpermute)", blocks[m.group(2).rstrip(",")]), m.group(0)
