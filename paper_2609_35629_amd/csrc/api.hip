@@ -241,7 +241,54 @@ void free_teams(santapp_teams* t) {
     delete t;
 }
 
-santapp_status finish_table(santapp_teams* t, hipStream_t s, santapp_teams** out);
+santapp::TeamTable table_arrays(const santapp_teams* t) {
+    return santapp::TeamTable{t->packed_K, t->packed_V, t->reps, t->team_begin, t->team_size,
+                              t->log_n, t->rep_token, t->perm};
+}
+
+// Waits for the build queued on s (and for build_open's launches, where parents
+// were left open), then sets the chunk capacities and the
+// device's compute units of the table; frees it on failure.
+template <typename Open>
+santapp_status finish_table(santapp_teams* t, hipStream_t s, santapp_teams** out, Open&& build_open) {
+    const size_t BH = static_cast<size_t>(t->B) * t->Hkv;
+    std::vector<int> sizes(BH * t->M);
+    auto fetch = [&]() {
+        const hipError_t e = hipMemcpyAsync(sizes.data(), t->team_size, sizes.size() * sizeof(int), hipMemcpyDeviceToHost, s);
+        return e == hipSuccess ? hipStreamSynchronize(s) : e;
+    };
+    hipError_t e = fetch();
+    int sign = 0;
+    if (e == hipSuccess)
+        for (int x : sizes) sign |= x;
+    if (sign < 0) {  // parents left open
+        e = build_open();
+        if (e == hipSuccess) e = fetch();
+    }
+    if (e != hipSuccess) {
+        free_teams(t);
+        return hip_fail(e, "team build");
+    }
+    int dev = 0;
+    t->cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&t->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        t->cus = 0;
+    (void)hipGetLastError();
+    t->cap.assign(t->M + 1, 0);
+    std::vector<int> cnt(t->M);
+    for (size_t bh = 0; bh < BH; ++bh) {
+        for (int g = 0; g < t->M; ++g) cnt[g] = santapp::chunk_count(sizes[bh * t->M + g]);
+        std::sort(cnt.begin(), cnt.end(), std::greater<int>());
+        int run = 0;
+        for (int x = 1; x <= t->M; ++x) {
+            run += cnt[x - 1];
+            t->cap[x] = std::max(t->cap[x], run);
+        }
+    }
+    *out = t;
+    return ok();
+}
 
 }  // namespace
 
@@ -492,8 +539,7 @@ santapp_status santapp_build_teams(const void* K, const void* V, int B, int Hkv,
     }
     const char* what = "team build";
     e = launch_build_parents(K, V, dtype, static_cast<int>(BH), N, d, parent_size, reps_per_parent,
-                             t->M, state, t->team_begin, t->team_size, t->log_n,
-                             t->rep_token, t->perm, t->packed_K, t->packed_V, t->reps, t->team_count, s);
+                             t->M, state, table_arrays(t), t->team_count, s);
     if (e == hipSuccess && !packed) {
         what = "packing K";
         e = launch_gather_rows(K, t->packed_K, t->perm, static_cast<int>(BH), N, N, row, s);
@@ -513,49 +559,16 @@ santapp_status santapp_build_teams(const void* K, const void* V, int B, int Hkv,
         free_teams(t);
         return hip_fail(e, what);
     }
-    const santapp_status st = finish_table(t, s, out);  // waits for the build
+    const santapp_status st = finish_table(t, s, out, [&]() {  // waits for the build
+        return launch_build_open(K, V, dtype, static_cast<int>(BH), N, d, parent_size, reps_per_parent, t->M,
+                                 table_arrays(t), s);
+    });
     if (st == SANTAPP_OK)
         pool().release_idle(state, state_bytes);
     else
         pool().release(state, state_bytes);
     return st;
 }
-
-namespace {
-
-// Waits for the build queued on s, then sets the chunk capacities and the
-// device's compute units of the table; frees it on failure.
-santapp_status finish_table(santapp_teams* t, hipStream_t s, santapp_teams** out) {
-    const size_t BH = static_cast<size_t>(t->B) * t->Hkv;
-    std::vector<int> sizes(BH * t->M);
-    hipError_t e = hipMemcpyAsync(sizes.data(), t->team_size, sizes.size() * sizeof(int), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-        free_teams(t);
-        return hip_fail(e, "team build");
-    }
-    int dev = 0;
-    t->cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&t->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        t->cus = 0;
-    (void)hipGetLastError();
-    t->cap.assign(t->M + 1, 0);
-    std::vector<int> cnt(t->M);
-    for (size_t bh = 0; bh < BH; ++bh) {
-        for (int g = 0; g < t->M; ++g) cnt[g] = chunk_count(sizes[bh * t->M + g]);
-        std::sort(cnt.begin(), cnt.end(), std::greater<int>());
-        int run = 0;
-        for (int x = 1; x <= t->M; ++x) {
-            run += cnt[x - 1];
-            t->cap[x] = std::max(t->cap[x], run);
-        }
-    }
-    *out = t;
-    return ok();
-}
-
-}  // namespace
 
 santapp_status santapp_kmeans_parents(const void* K, int B, int Hkv, int N, int d, santapp_dtype dtype,
                                       int parent_size, const santapp_kmeans_settings* theta, int* labels,
@@ -721,8 +734,7 @@ santapp_status santapp_build_teams_from_labels(const void* K, const void* V, int
     if (e == hipSuccess) {
         what = "team build";
         e = launch_build_parent_lists(K, dtype, static_cast<int>(BH), N, d, Mp, reps_per_parent, M, members,
-                                      pbeg, toff, scratch + o_state, t->team_begin, t->team_size, t->log_n,
-                                      t->rep_token, t->perm, s);
+                                      pbeg, toff, scratch + o_state, table_arrays(t), s);
     }
     if (e == hipSuccess) {
         what = "packing K";
@@ -741,7 +753,7 @@ santapp_status santapp_build_teams_from_labels(const void* K, const void* V, int
         free_teams(t);
         return hip_fail(e, what);
     }
-    const santapp_status st = finish_table(t, s, out);  // waits for the build
+    const santapp_status st = finish_table(t, s, out, []() { return hipErrorUnknown; });  // waits for the build
     if (st == SANTAPP_OK)
         pool().release_idle(block, block_bytes);
     else

@@ -33,16 +33,25 @@ constexpr int kRankBlock = kWave;    // representatives ranked per ballot block
 constexpr float kInf = __builtin_inff();
 
 // Bound on |estimate - the definition's distance| over a parent whose largest
-// squared norm is nmax: a lane's chain of at most eight products, the four
-// additions over the sixteen lanes and the final combination round at most 20
-// times per inner product, each by at most 2^-23 of sum |x_i c_i| <=
-// (|x|^2 + |c|^2) / 2 <= nmax; three inner products (one of them twice) and
-// the final additions stay below 100 x 2^-23 nmax.
-constexpr float kEstimate = 128.f * 0x1.0p-23f;
+// squared norm is nmax.  An inner product rounds at most twelve times on any
+// path (a lane's chain: eight fused multiply-adds, or four dot products of two
+// exact bf16 products with two roundings each; then four additions over the
+// lanes), each time by at most 2^-23 of sum |x_i c_i| <= nmax.  |x|^2, |c|^2 and
+// twice x.c are off by 48 x 2^-23 nmax, their combination rounds by 6 x 2^-23
+// nmax more, and the rounding of the mean to fp32 adds 3: below 64 x 2^-23 nmax
+// with what products below fp32's normal range can lose (kNormMin).
+constexpr float kEstimate = 64.f * 0x1.0p-23f;
 // Parents whose largest squared norm lies outside this range (fp32 products
 // could overflow or vanish, or a key is not finite) are built by the
 // definition's arithmetic throughout.
-constexpr float kNormMin = 1e-30f, kNormMax = 1e30f;
+constexpr float kNormMin = 1e-28f, kNormMax = 1e30f;
+
+// A tie within estimates wider than this share of the farthest distance takes
+// the parent to the definition's arithmetic: at 32K tokens (bf16, d = 128, P =
+// 1024, R = 16) keys with four channels at 300 times the others' spread (share
+// 0.014) take 179 us compared member by member, 276 by the definition; all
+// channels at 100 times it (0.05) take 404 us so, 228 by the definition.
+constexpr float kWide = 1.f / 32.f;
 
 // (value, index) reductions with ties broken toward the lower index.
 struct ArgVal {
@@ -58,18 +67,37 @@ __device__ __forceinline__ ArgVal pick_max(ArgVal a, ArgVal b) {
     return (b.v > a.v || (b.v == a.v && b.i < a.i)) ? b : a;
 }
 
+// The best of the wave's lanes (no lane's value is NaN).
+template <bool kMax>
+__device__ __forceinline__ ArgVal wave_arg(ArgVal x) {
+    const double v = kMax ? x.v : -x.v;
+    double m = v;
+    m = fmax(m, dpp_f64<0x128>(m));
+    m = fmax(m, dpp_f64<0x124>(m));
+    m = fmax(m, dpp_f64<0x122>(m));
+    m = fmax(m, dpp_f64<0x121>(m));
+    m = fmax(m, __shfl_xor(m, 16));
+    m = fmax(m, __shfl_xor(m, 32));
+    const uint64_t at = __ballot(v == m);
+    int i;
+    if (__popcll(at) == 1) {  // uniform
+        i = readlane(x.i, __ffsll(static_cast<unsigned long long>(at)) - 1);
+    } else {
+        i = v == m ? x.i : 0x7fffffff;
+        for (int off = kWave / 2; off > 0; off >>= 1) i = min(i, __shfl_xor(i, off));
+    }
+    return ArgVal{kMax ? m : -m, i};
+}
+
 template <bool kMax>
 __device__ ArgVal block_arg(ArgVal x, ArgVal* s_red, int nw) {
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        ArgVal y;
-        y.v = __shfl_xor(x.v, off);
-        y.i = __shfl_xor(x.i, off);
-        x = kMax ? pick_max(x, y) : pick_min(x, y);
-    }
-    if (lane_id() == 0) s_red[wave_id()] = x;
+    const int lane = lane_id();
+    x = wave_arg<kMax>(x);
+    if (lane == 0) s_red[wave_id()] = x;
     __syncthreads();
-    ArgVal r = s_red[0];
-    for (int w = 1; w < nw; ++w) r = kMax ? pick_max(r, s_red[w]) : pick_min(r, s_red[w]);
+    ArgVal r{kMax ? -INFINITY : INFINITY, 0x7fffffff};
+    if (lane < nw) r = s_red[lane];
+    r = wave_arg<kMax>(r);
     __syncthreads();
     return r;
 }
@@ -107,7 +135,23 @@ __device__ double sqdist_to(const T* __restrict__ row, const double* __restrict_
     return acc;
 }
 
-// The same between two rows in memory.
+// s plus `n` values in order, at(i) apart from p, sixteen read ahead of their
+// additions.
+template <typename T, typename At>
+__device__ __forceinline__ double sum_rows(double s, const T* p, int n, At at) {
+    int i = 0;
+    for (; i + 16 <= n; i += 16) {
+        float x[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) x[q] = load_elem(p, at(i + q));
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s = s + static_cast<double>(x[q]);
+    }
+    for (; i < n; ++i) s = s + static_cast<double>(load_elem(p, at(i)));
+    return s;
+}
+
+// |a - c|^2 of two rows in memory.
 template <typename T, int D>
 __device__ double sqdist_rows(const T* __restrict__ a, const T* __restrict__ c) {
 #pragma clang fp contract(off)
@@ -132,6 +176,44 @@ __device__ double sqdist_rows(const T* __restrict__ a, const T* __restrict__ c) 
     }
     return acc;
 }
+
+// A row in registers, and its squared distance to c in LDS the same way.
+template <typename T, int D>
+struct Row {
+    static constexpr int V = D * static_cast<int>(sizeof(T)) / 16;
+    uint4 v[V];
+    __device__ __forceinline__ void load(const T* p) {
+#pragma unroll
+        for (int q = 0; q < V; ++q) v[q] = reinterpret_cast<const uint4*>(p)[q];
+    }
+    __device__ __forceinline__ void store(T* p) const {
+#pragma unroll
+        for (int q = 0; q < V; ++q) reinterpret_cast<uint4*>(p)[q] = v[q];
+    }
+    __device__ __forceinline__ double sqdist(const double* __restrict__ c) {
+#pragma clang fp contract(off)
+        constexpr int kPer = 16 / static_cast<int>(sizeof(T));
+        double acc = 0.0;
+#pragma unroll
+        for (int q = 0; q < V; ++q) {
+            // 16 bytes of the row are widened at a time (widened as a whole it
+            // would not fit the registers)
+            asm volatile("" : "+v"(acc), "+v"(v[q].x), "+v"(v[q].y), "+v"(v[q].z), "+v"(v[q].w) : : "memory");
+            const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+            for (int k = 0; k < kPer; k += 2) {
+                const double2 y = *reinterpret_cast<const double2*>(c + q * kPer + k);
+                const float x0 = kPer == 8 ? bf16lo(w[k / 2]) : __uint_as_float(w[k & 3]);
+                const float x1 = kPer == 8 ? bf16hi(w[k / 2]) : __uint_as_float(w[(k + 1) & 3]);
+                const double t0 = static_cast<double>(x0) - y.x;
+                acc = acc + t0 * t0;
+                const double t1 = static_cast<double>(x1) - y.y;
+                acc = acc + t1 * t1;
+            }
+        }
+        return acc;
+    }
+};
 
 // Completes x here: work on rows streamed through registers is not put off
 // (which would keep the rows alive).
@@ -272,7 +354,7 @@ struct MemberState {
 
 // LDS of a build workgroup of nw waves and up to r representatives (bytes).
 struct BuildLds {
-    int part, vec, row, best, red, tie_i, tie_v, tie_o, reps, cnt, off, wcnt, misc, total;
+    int part, vec, row, best, red, tie_i, tie_v, reps, cnt, off, wcnt, misc, total;
 };
 __host__ __device__ inline BuildLds build_lds(int nw, int r, int d, int esz) {
     BuildLds L{};
@@ -290,7 +372,6 @@ __host__ __device__ inline BuildLds build_lds(int nw, int r, int d, int esz) {
     L.red = take(nw * static_cast<int>(sizeof(ArgVal)));
     L.tie_i = take(kTie * 4);
     L.tie_v = take(kTie * 8);
-    L.tie_o = take(kTie * 4);
     L.reps = take(r * 4);
     L.cnt = take(r * 4);
     L.off = take(r * 4);
@@ -298,6 +379,145 @@ __host__ __device__ inline BuildLds build_lds(int nw, int r, int d, int esz) {
     L.misc = take((nw + 4) * 4);
     L.total = o;
     return L;
+}
+
+// The thread index as a value of its own: what is derived from it here is not
+// kept in registers from (or for) another phase of the kernel.
+__device__ __forceinline__ int fresh_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// Arrays of a table, written by the build kernels.
+template <typename T>
+struct TeamArrays {
+    int* team_begin;
+    int* team_size;
+    double* log_n;
+    int* rep_token;
+    int* perm;
+    T* packed_K;
+    T* packed_V;
+    T* reps;
+};
+
+// The end of a parent's build: its teams (of the representatives in LDS and
+// owner(i) of each member), its part of perm and, with PACK, its packed rows and
+// routing keys.  store_row(k, to) writes row k of a lane group's sixteen, for
+// the HELD rows that registers hold.
+template <typename T, int D, bool ONE, bool PACK, int HELD, typename Tok, typename Owner, typename Store>
+__device__ __forceinline__ void write_teams(const TeamArrays<T>& out, const T* __restrict__ K, const T* __restrict__ V,
+                                            int N, int R, int M, int bh, int start, int n, int team0, char* lds, Tok tok,
+                                            Owner owner, Store store_row) {
+    using C = Chunk<T, D>;
+    constexpr int E = C::E;
+    const int tid = fresh_tid(), nt = blockDim.x, nw = nt / kWave;
+    const int lane = tid & (kWave - 1), w = tid / kWave, sub = tid & 15, g16 = tid & ~15, lbase = lane & 48;
+    const int r = min(R, n), nblk = ONE ? 1 : (n + nt - 1) / nt, wstride = min(R, kRankBlock);
+    const BuildLds L = build_lds(nw, R, D, sizeof(T));
+    const int* const s_reps = reinterpret_cast<const int*>(lds + L.reps);
+    int* const s_cnt = reinterpret_cast<int*>(lds + L.cnt);
+    int* const s_off = reinterpret_cast<int*>(lds + L.off);
+    int* const s_wcnt = reinterpret_cast<int*>(lds + L.wcnt);
+    int* const s_misc = reinterpret_cast<int*>(lds + L.misc);
+
+            // team sizes and offsets inside the parent
+            __syncthreads();
+            for (int u = tid; u < r; u += nt) s_cnt[u] = 0;
+            __syncthreads();
+            for (int i = tid; i < n; i += nt) atomicAdd(&s_cnt[owner(i)], 1);
+            __syncthreads();
+            for (int base = 0; base < r; base += nt) {
+                const int u = base + tid;
+                const int c = u < r ? s_cnt[u] : 0;
+                const int inc = wave_incl_scan(c);
+                if (lane == kWave - 1) s_misc[4 + w] = inc;
+                __syncthreads();
+                int pre = base > 0 ? s_off[base - 1] + s_cnt[base - 1] : 0;
+                for (int v = 0; v < w; ++v) pre += s_misc[4 + v];
+                if (u < r) s_off[u] = pre + inc - c;
+                __syncthreads();
+            }
+            const size_t tbase = static_cast<size_t>(bh) * M + team0;
+            for (int u = tid; u < r; u += nt) {
+                out.team_begin[tbase + u] = start + s_off[u];
+                out.team_size[tbase + u] = s_cnt[u];
+                out.log_n[tbase + u] = log(static_cast<double>(s_cnt[u]));
+                out.rep_token[tbase + u] = tok(s_reps[u]);
+            }
+            __syncthreads();
+
+            // packed position of each member: its team's offset plus its rank among
+            // the team's members in token order, per block of nt members and of 64
+            // representatives, one ballot per representative and wave
+            int* const pperm = out.perm + static_cast<size_t>(bh) * N + start;
+            const uint64_t lt = lanemask_lt();
+            int pos = 0;
+            for (int b = 0; b < nblk; ++b) {
+                const int i = b * nt + tid;
+                const int o = i < n ? owner(i) : -1;
+                for (int ub = 0; ub < r; ub += kRankBlock) {
+                    const int nb = min(kRankBlock, r - ub);
+                    int rank = 0;
+                    for (int q = 0; q < nb; ++q) {
+                        const uint64_t bm = __ballot(o == ub + q);
+                        if (o == ub + q) rank = __popcll(bm & lt);
+                        if (lane == 0) s_wcnt[w * wstride + q] = __popcll(bm);
+                    }
+                    __syncthreads();
+                    if (o >= ub && o < ub + nb) {
+                        int ps = s_off[o] + rank;
+                        for (int v = 0; v < w; ++v) ps += s_wcnt[v * wstride + o - ub];
+                        pperm[ps] = tok(i);
+                        pos = ps;
+                    }
+                    __syncthreads();
+                    if (!ONE) {  // the next block's members follow
+                        for (int q = tid; q < nb; q += nt) {
+                            int add = 0;
+                            for (int v = 0; v < nw; ++v) add += s_wcnt[v * wstride + q];
+                            s_off[ub + q] += add;
+                        }
+                        __syncthreads();
+                    }
+                }
+            }
+
+            // packed copies of a contiguous parent of one block: whole rows, sixteen
+            // lanes each, keys from the registers that hold them
+            if constexpr (PACK) {
+                const size_t prow0 = static_cast<size_t>(bh) * N + start;
+                auto dst = [&](T* base, int k) { return base + (prow0 + __shfl(pos, lbase + k)) * D + sub * E; };
+    #pragma unroll
+                for (int k = 0; k < HELD; ++k) {
+                    T* const to = dst(out.packed_K, k);
+                    if (g16 + k < n) store_row(k, to);
+                }
+                // rows k0 .. 15 of src
+                auto copy = [&](const T* src, T* to, int k0) {
+    #pragma unroll 1
+                    for (; k0 < 16; k0 += 4) {
+                        C x[4];
+    #pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            if (g16 + k0 + k < n) x[k].load(src + (prow0 + g16 + k0 + k) * D + sub * E);
+    #pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            T* const p = dst(to, k0 + k);
+                            if (g16 + k0 + k < n) x[k].store(p);
+                        }
+                    }
+                };
+                copy(K, out.packed_K, HELD);
+                copy(V, out.packed_V, 0);
+                for (int e = tid; e < r * 16; e += nt) {
+                    const int u = e >> 4, c = e & 15;
+                    C x;
+                    x.load(K + (static_cast<size_t>(bh) * N + tok(s_reps[u])) * D + c * E);
+                    x.store(out.reps + (tbase + u) * D + c * E);
+                }
+            }
 }
 
 // Thread t owns members t, t + nt, ... of its parent (nt = blockDim.x; ONE:
@@ -318,26 +538,19 @@ __host__ __device__ inline BuildLds build_lds(int nw, int r, int d, int esz) {
 // every round (4.1 us a round; 620 us in fp64 with 256 threads).  P = 16, R = 4
 // at 32K: 64 us, one wave per parent (518 us).  K-means parents at 32K: 140 us
 // (782 us).
-// The thread index as a value of its own: what is derived from it here is not
-// kept in registers from (or for) another phase of the kernel.
-__device__ __forceinline__ int fresh_tid() {
-    int t = threadIdx.x;
-    asm volatile("" : "+v"(t));
-    return t;
-}
-
 template <typename T, int D, bool LIST, bool ONE>
 __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, int N, int R, int M, int bh, int start,
                              int n, int team0, const int* __restrict__ mem, MemberState* __restrict__ state_all,
-                             int* __restrict__ team_begin, int* __restrict__ team_size, double* __restrict__ log_n,
-                             int* __restrict__ rep_token, int* __restrict__ perm, T* __restrict__ packed_K,
-                             T* __restrict__ packed_V, T* __restrict__ reps, char* lds) {
+                             const TeamArrays<T>& out, char* lds) {
     using C = Chunk<T, D>;
     constexpr int E = C::E;
     // rows kept in registers, and rows of the others in flight at once: what
     // 128 registers a thread hold beside the sixteen sums
     constexpr int CACHE = C::W == 2 ? 16 : C::W == 4 && ONE ? 16 : 4;
     constexpr int BATCH = C::W == 2 ? 8 : C::W == 4 ? 4 : 2;
+    // whole rows fit the registers: parents that the estimates leave open are
+    // built by k_build_open
+    constexpr bool DEFER = ONE && !LIST && CACHE == 16;
     const int tid = threadIdx.x, nt = blockDim.x, nw = nt / kWave;
     const int w = wave_id(), lane = lane_id(), sub = lane & 15, g16 = tid & ~15, lbase = lane & 48;
     const int r = min(R, n);
@@ -351,11 +564,7 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
     int* const s_ti = reinterpret_cast<int*>(lds + L.tie_i);
     unsigned long long* const s_tv = reinterpret_cast<unsigned long long*>(lds + L.tie_v);
     int* const s_reps = reinterpret_cast<int*>(lds + L.reps);
-    int* const s_cnt = reinterpret_cast<int*>(lds + L.cnt);
-    int* const s_off = reinterpret_cast<int*>(lds + L.off);
-    int* const s_wcnt = reinterpret_cast<int*>(lds + L.wcnt);
     int* const s_misc = reinterpret_cast<int*>(lds + L.misc);
-    const int wstride = min(R, kRankBlock);
 
     const T* const Kb = K + static_cast<size_t>(bh) * N * D;
     auto tok = [&](int i) { return LIST ? mem[i] : start + i; };
@@ -455,12 +664,70 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
     if (tid == 0) s_misc[0] = 0;
     __syncthreads();
     bool exact = !(nmax >= kNormMin && nmax <= kNormMax);  // uniform
+    bool zero = false;
+    if (nmax == 0.f) {  // uniform: padding, as a rule; every distance is 0 then
+        const int tid = fresh_tid();
+        uint32_t bits = 0;
+        for (int i = tid; i < n; i += nt) {
+#pragma unroll 4
+            for (int q = 0; q < D * static_cast<int>(sizeof(T)) / 16; ++q) {
+                const uint4 x = reinterpret_cast<const uint4*>(row(i))[q];
+                bits |= x.x | x.y | x.z | x.w;
+            }
+        }
+        bits &= sizeof(T) == 2 ? 0x7fff7fffu : 0x7fffffffu;  // (zeros of either sign)
+        if (__ballot(bits != 0) != 0 && (tid & (kWave - 1)) == 0) s_misc[0] = 1;
+        __syncthreads();
+        zero = s_misc[0] == 0;
+        __syncthreads();
+        if (tid == 0) s_misc[0] = 0;
+    }
     const float err2 = 2.f * kEstimate * nmax;
 
     MemberState st;
     st.reset();
     st.nx = nx0;
     int rep = 0;
+
+    // s_vec = the members' mean, each dimension summed in token order.
+    auto definition_mean = [&]() {
+        const int tid = fresh_tid(), sub = tid & 15, g16 = tid & ~15;
+        __syncthreads();
+        // rows held in registers reach the summing threads through LDS
+        const int stage = DEFER ? nw * 8 / static_cast<int>(sizeof(T)) : 0;
+        if (stage >= 16 && D <= nt) {  // uniform
+            T* const s_rows = reinterpret_cast<T*>(s_row);
+            const int step = stage & ~15;
+            double s = 0.0;
+            for (int i0 = 0; i0 < n; i0 += step) {
+                if (g16 >= i0 && g16 < i0 + step) {
+#pragma unroll
+                    for (int k = 0; k < CACHE; ++k) cache[k].store(s_rows + (g16 - i0 + k) * D + sub * E);
+                }
+                __syncthreads();
+                if (tid < D) s = sum_rows(s, s_rows + tid, min(step, n - i0), [](int i) { return static_cast<size_t>(i) * D; });
+                __syncthreads();
+            }
+            if (tid < D) s_vec[tid] = s / static_cast<double>(n);
+        } else {
+            for (int j = tid; j < D; j += nt) {
+                const double s = sum_rows(0.0, Kb + j, n, [&](int i) { return static_cast<size_t>(tok(i)) * D; });
+                s_vec[j] = s / static_cast<double>(n);
+            }
+        }
+        __syncthreads();
+    };
+
+    // The member nearest that mean.  A reduction without a winner (NaN keys)
+    // falls back to member 0, so that every index stays inside the parent.
+    auto first_by_definition = [&]() {
+        definition_mean();
+        const int tid = fresh_tid();
+        ArgVal best{INFINITY, 0x7fffffff};
+        for (int i = tid; i < n; i += nt) best = pick_min(best, ArgVal{sqdist_to(row(i), s_vec, D), i});
+        best = block_arg<false>(best, s_red, nw);
+        return best.i < n ? best.i : 0;
+    };
 
     // The members listed in s_ti (cnt <= kTie of them, s_tv preset to ~0):
     // their running minima over the first nv representatives by the
@@ -474,6 +741,7 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
         }
     };
 
+    int known = 0;  // representatives the estimates found
     if (!exact) {
         // first representative: the member nearest the mean
         const int tid = fresh_tid(), lane = tid & (kWave - 1), w = tid / kWave;
@@ -543,8 +811,10 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
             }
             __syncthreads();
             const int cnt = s_misc[0];
-            if (cnt > kTie) {
+            if (cnt == n && n > kTie) {
                 exact = true;  // uniform
+            } else if (cnt > kTie) {
+                rep = first_by_definition();
             } else {
                 if (tid < cnt) s_tv[tid] = static_cast<unsigned long long>(__double_as_longlong(sqdist_to(row(s_ti[tid]), s_vec, D)));
                 __syncthreads();
@@ -557,21 +827,7 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
                     clear = clear && (s_ti[c] == win.i || __longlong_as_double(static_cast<long long>(s_tv[c])) > win.v + slack);
                 rep = win.i;
                 if (!clear) {  // uniform
-                    __syncthreads();
-                    for (int j = tid; j < D; j += nt) {
-                        double s = 0.0;
-                        int i = 0;
-                        for (; i + 16 <= n; i += 16) {
-                            float x[16];
-#pragma unroll
-                            for (int q = 0; q < 16; ++q) x[q] = load_elem(row(i + q), j);
-#pragma unroll
-                            for (int q = 0; q < 16; ++q) s = s + static_cast<double>(x[q]);
-                        }
-                        for (; i < n; ++i) s = s + static_cast<double>(load_elem(row(i), j));
-                        s_vec[j] = s / static_cast<double>(n);
-                    }
-                    __syncthreads();
+                    definition_mean();
                     if (tid < cnt) s_tv[tid] = static_cast<unsigned long long>(__double_as_longlong(sqdist_to(row(s_ti[tid]), s_vec, D)));
                     __syncthreads();
                     win = ArgVal{INFINITY, 0x7fffffff};
@@ -583,6 +839,8 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
             __syncthreads();
             if (tid == 0) s_misc[0] = 0;
         }
+        known = exact ? 0 : 1;
+        if (tid == 0) s_reps[0] = rep;
     }
 
     if (!exact) {
@@ -686,8 +944,9 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
             }
             __syncthreads();
             const int cnt = s_misc[0];
-            if (cnt > kTie) {
+            if (cnt > kTie || err2 > kWide * T0) {
                 exact = true;  // uniform
+                known = u + 1;
                 break;
             }
             tie_minima(cnt, u + 1);
@@ -702,11 +961,25 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
             if (tid == 0) s_misc[0] = 0;
         }
     }
-    if (!exact) {
+    if (zero) {
+        // the lowest members become the representatives, the rest join the first
+        const int tid = fresh_tid();
+        for (int u = tid; u < r; u += nt) s_reps[u] = u;
+        for (int i = tid; i < n; i += nt) {
+            const uint32_t o = i < r ? static_cast<uint32_t>(i) : 0u;
+            if (ONE)
+                st.own = o;
+            else
+                state[i].own = o;
+        }
+    } else if (!exact) {
         // owners the estimates leave open: the definition's distances to the
-        // two nearest representatives (to all where a third is as near)
+        // two nearest representatives, or to all where a third is as near (by
+        // sixteen lanes each, where members have a thread of their own)
         const int tid = fresh_tid();
         __syncthreads();
+        int* const s_list = reinterpret_cast<int*>(s_row);
+        int listed = -1;
         for (int b = 0; b < nblk; ++b) {
             const int i = b * nt + tid;
             if (i >= n) continue;
@@ -714,6 +987,11 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
             if (s.m1 > -kInf && s.m2 - s.m1 <= err2) {
                 int o = static_cast<int>(s.own & 0xffffu);
                 if (s.m3 - s.m1 <= err2) {
+                    if (ONE) {
+                        listed = atomicAdd(&s_misc[0], 1);
+                        s_list[listed] = i;
+                        continue;
+                    }
                     double m = INFINITY;
                     for (int v = 0; v < r; ++v) {
                         const double d2 = sqdist_rows<T, D>(row(i), row(s_reps[v]));
@@ -734,24 +1012,56 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
                     state[i].own = static_cast<uint32_t>(o);
             }
         }
-    } else {
-        // the definition's arithmetic throughout
-        const int tid = fresh_tid();
-        __syncthreads();
-        for (int j = tid; j < D; j += nt) {
-            double s = 0.0;
-            for (int i = 0; i < n; ++i) s = s + static_cast<double>(load_elem(row(i), j));
-            s_vec[j] = s / static_cast<double>(n);
+        if (ONE) {
+            __syncthreads();
+            const int cnt = s_misc[0];
+            for (int c = tid >> 4; c < cnt; c += nt / 16) {
+                const T* const x = row(s_list[c]);
+                double m = INFINITY;
+                int o = 0x7fffffff;
+                for (int v = tid & 15; v < r; v += 16) {
+                    const double d2 = sqdist_rows<T, D>(x, row(s_reps[v]));
+                    if (d2 < m) {
+                        m = d2;
+                        o = v;
+                    }
+                }
+                for (int off = 8; off > 0; off >>= 1) {
+                    const double om = __shfl_xor(m, off);
+                    const int oo = __shfl_xor(o, off);
+                    if (om < m || (om == m && oo < o)) {
+                        m = om;
+                        o = oo;
+                    }
+                }
+                if ((tid & 15) == 0) s_list[c] = o;
+            }
+            __syncthreads();
+            if (listed >= 0) st.own = static_cast<uint32_t>(s_list[listed]);
         }
+    } else if constexpr (DEFER) {
+        // left to k_build_open, with the representatives found so far
+        const int tid = fresh_tid();
+        const size_t tbase = static_cast<size_t>(bh) * M + team0;
         __syncthreads();
-        ArgVal best{INFINITY, 0x7fffffff};
-        for (int i = tid; i < n; i += nt) best = pick_min(best, ArgVal{sqdist_to(row(i), s_vec, D), i});
-        best = block_arg<false>(best, s_red, nw);
-        // a reduction without a winner (NaN keys) falls back to member 0, so
-        // that every index stays inside the parent
-        rep = best.i < n ? best.i : 0;
+        for (int u = tid; u < known; u += nt) out.rep_token[tbase + u] = start + s_reps[u];
+        if (tid == 0) out.team_size[tbase] = -1 - known;
+        return;
+    } else {
+        // the definition's arithmetic throughout (the representatives that the
+        // estimates found are the definition's)
+        const int tid = fresh_tid();
+        if (known == 0) {
+            rep = first_by_definition();
+            known = 1;
+            if (tid == 0) s_reps[0] = rep;
+        }
         for (int u = 0; u < r; ++u) {
-            if (tid == 0) s_reps[u] = rep;
+            __syncthreads();
+            if (u < known)
+                rep = s_reps[u];
+            else if (tid == 0)
+                s_reps[u] = rep;
             for (int j = tid; j < D; j += nt) s_vec[j] = static_cast<double>(load_elem(row(rep), j));
             __syncthreads();
             // fold the new representative into the running minimum; a chosen
@@ -782,136 +1092,139 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
                     state[i].set_exact(m, o);
                 far = pick_max(far, ArgVal{m, i});
             }
-            if (u + 1 < r) {
+            if (u + 1 < r && u + 1 >= known) {
                 far = block_arg<true>(far, s_red, nw);
                 rep = far.i < n ? far.i : 0;
             }
         }
     }
-    {
-        const int tid = fresh_tid();
-        const int lane = tid & (kWave - 1), w = tid / kWave, sub = tid & 15, g16 = tid & ~15, lbase = lane & 48;
-        auto owner = [&](int i) { return static_cast<int>((ONE ? st.own : state[i].own) & 0xffffu); };
-
-        // team sizes and offsets inside the parent
-        __syncthreads();
-        for (int u = tid; u < r; u += nt) s_cnt[u] = 0;
-        __syncthreads();
-        for (int i = tid; i < n; i += nt) atomicAdd(&s_cnt[owner(i)], 1);
-        __syncthreads();
-        for (int base = 0; base < r; base += nt) {
-            const int u = base + tid;
-            const int c = u < r ? s_cnt[u] : 0;
-            const int inc = wave_incl_scan(c);
-            if (lane == kWave - 1) s_misc[4 + w] = inc;
-            __syncthreads();
-            int pre = base > 0 ? s_off[base - 1] + s_cnt[base - 1] : 0;
-            for (int v = 0; v < w; ++v) pre += s_misc[4 + v];
-            if (u < r) s_off[u] = pre + inc - c;
-            __syncthreads();
-        }
-        const size_t tbase = static_cast<size_t>(bh) * M + team0;
-        for (int u = tid; u < r; u += nt) {
-            team_begin[tbase + u] = start + s_off[u];
-            team_size[tbase + u] = s_cnt[u];
-            log_n[tbase + u] = log(static_cast<double>(s_cnt[u]));
-            rep_token[tbase + u] = tok(s_reps[u]);
-        }
-        __syncthreads();
-
-        // packed position of each member: its team's offset plus its rank among
-        // the team's members in token order, per block of nt members and of 64
-        // representatives, one ballot per representative and wave
-        int* const pperm = perm + static_cast<size_t>(bh) * N + start;
-        const uint64_t lt = lanemask_lt();
-        int pos = 0;
-        for (int b = 0; b < nblk; ++b) {
-            const int i = b * nt + tid;
-            const int o = i < n ? owner(i) : -1;
-            for (int ub = 0; ub < r; ub += kRankBlock) {
-                const int nb = min(kRankBlock, r - ub);
-                int rank = 0;
-                for (int q = 0; q < nb; ++q) {
-                    const uint64_t bm = __ballot(o == ub + q);
-                    if (o == ub + q) rank = __popcll(bm & lt);
-                    if (lane == 0) s_wcnt[w * wstride + q] = __popcll(bm);
-                }
-                __syncthreads();
-                if (o >= ub && o < ub + nb) {
-                    int ps = s_off[o] + rank;
-                    for (int v = 0; v < w; ++v) ps += s_wcnt[v * wstride + o - ub];
-                    pperm[ps] = tok(i);
-                    pos = ps;
-                }
-                __syncthreads();
-                if (!ONE) {  // the next block's members follow
-                    for (int q = tid; q < nb; q += nt) {
-                        int add = 0;
-                        for (int v = 0; v < nw; ++v) add += s_wcnt[v * wstride + q];
-                        s_off[ub + q] += add;
-                    }
-                    __syncthreads();
-                }
-            }
-        }
-
-        // packed copies of a contiguous parent of one block: whole rows, sixteen
-        // lanes each, keys from the registers that hold them
-        if constexpr (ONE && !LIST) {
-            const size_t prow0 = static_cast<size_t>(bh) * N + start;
-            auto dst = [&](T* base, int k) { return base + (prow0 + __shfl(pos, lbase + k)) * D + sub * E; };
-#pragma unroll
-            for (int k = 0; k < CACHE; ++k) {
-                T* const to = dst(packed_K, k);
-                if (g16 + k < n) cache[k].store(to);
-            }
-            // rows k0 .. 15 of src
-            auto copy = [&](const T* src, T* to, int k0) {
-#pragma unroll 1
-                for (; k0 < 16; k0 += 4) {
-                    C x[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (g16 + k0 + k < n) x[k].load(src + (prow0 + g16 + k0 + k) * D + sub * E);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        T* const p = dst(to, k0 + k);
-                        if (g16 + k0 + k < n) x[k].store(p);
-                    }
-                }
-            };
-            copy(K, packed_K, CACHE);
-            copy(V, packed_V, 0);
-            for (int e = tid; e < r * 16; e += nt) {
-                const int u = e >> 4, c = e & 15;
-                C x;
-                x.load(row(s_reps[u]) + c * E);
-                x.store(reps + (tbase + u) * D + c * E);
-            }
-        }
-    }
+    write_teams<T, D, ONE, ONE && !LIST, CACHE>(
+        out, K, V, N, R, M, bh, start, n, team0, lds, tok,
+        [&](int i) { return static_cast<int>((ONE ? st.own : state[i].own) & 0xffffu); },
+        [&](int k, T* to) { cache[k].store(to); });
 }
 
 // Contiguous parents [pP, min(pP + P, N)); every pair has M teams.
 template <typename T, int D, bool ONE>
 __global__ __launch_bounds__(kBuildThreads) void k_build_contiguous(
     const T* __restrict__ K, const T* __restrict__ V, int N, int P, int R, int M, MemberState* __restrict__ state,
-    int* __restrict__ team_begin, int* __restrict__ team_size, double* __restrict__ log_n,
-    int* __restrict__ rep_token, int* __restrict__ perm, T* __restrict__ packed_K, T* __restrict__ packed_V,
-    T* __restrict__ reps, int* __restrict__ team_count) {
+    TeamArrays<T> out, int* __restrict__ team_count) {
     extern __shared__ __align__(16) char s_build[];
     const int p = blockIdx.x, bh = blockIdx.y, start = p * P;
     if (p == 0 && threadIdx.x == 0) team_count[bh] = M;
-    build_parent<T, D, false, ONE>(K, V, N, R, M, bh, start, min(P, N - start), p * min(R, P), nullptr, state, team_begin,
-                                   team_size, log_n, rep_token, perm, packed_K, packed_V, reps, s_build);
+    build_parent<T, D, false, ONE>(K, V, N, R, M, bh, start, min(P, N - start), p * min(R, P), nullptr, state, out, s_build);
+}
+
+// LDS of k_build_open: build_lds, then the rows that nt threads load at once, one
+// 16-byte piece each (16 bytes of padding a row spread them over the banks).
+template <typename T, int D>
+__host__ __device__ constexpr int open_rows(int nt) { return nt * 16 / (D * static_cast<int>(sizeof(T))); }
+template <typename T, int D>
+__host__ __device__ constexpr int open_stage_bytes(int nt) { return open_rows<T, D>(nt) * (D * static_cast<int>(sizeof(T)) + 16); }
+
+// The contiguous parents that k_build_contiguous left open (first team's size
+// negative: -1 - the representatives it found, which stand in rep_token): the
+// definition's arithmetic throughout, each thread's member in its registers.
+// What bounds it is fp64 issue, 128 dimensions x 5 operations a member and
+// representative.  A 32K table of equal rows (bf16, d = 128, P = 1024, R = 16;
+// host time, an allocation included) takes 231 us, with rows past fp32's range
+// 214; with every row read from memory each round they took 341 and 331, with all
+// tables built by the definition 263 and 257.
+template <typename T, int D>
+__global__ __launch_bounds__(kBuildThreads) void k_build_open(const T* __restrict__ K, const T* __restrict__ V, int N,
+                                                              int P, int R, int M, TeamArrays<T> out) {
+    extern __shared__ __align__(16) char s_build[];
+    const int p = blockIdx.x, bh = blockIdx.y, start = p * P, n = min(P, N - start), team0 = p * min(R, P);
+    const size_t tbase = static_cast<size_t>(bh) * M + team0;
+    const int left = out.team_size[tbase];
+    if (left >= 0) return;  // uniform
+    const int known = -1 - left, r = min(R, n);
+    const int tid = threadIdx.x, nt = blockDim.x, nw = nt / kWave;
+    const BuildLds L = build_lds(nw, R, D, sizeof(T));
+    double* const s_vec = reinterpret_cast<double*>(s_build + L.vec);
+    ArgVal* const s_red = reinterpret_cast<ArgVal*>(s_build + L.red);
+    int* const s_reps = reinterpret_cast<int*>(s_build + L.reps);
+    T* const s_rows = reinterpret_cast<T*>(s_build + L.total);
+    constexpr int kPieces = D * static_cast<int>(sizeof(T)) / 16, kStride = D + 16 / static_cast<int>(sizeof(T));
+    for (int u = tid; u < known; u += nt) s_reps[u] = out.rep_token[tbase + u] - start;
+
+    // the members' rows, whole lines from memory, through LDS to their threads;
+    // and their mean on the way, each dimension summed in token order
+    const int step = open_rows<T, D>(nt);
+    const T* const Kp = K + (static_cast<size_t>(bh) * N + start) * D;
+    const int lr = tid / kPieces, lc = tid % kPieces;
+    auto piece = [&](int i) { return reinterpret_cast<const uint4*>(Kp + static_cast<size_t>(min(i, n - 1)) * D)[lc]; };
+    Row<T, D> own;
+#pragma unroll
+    for (int q = 0; q < Row<T, D>::V; ++q) own.v[q] = make_uint4(0, 0, 0, 0);
+    double sum[D / kWave];
+#pragma unroll
+    for (int q = 0; q < D / kWave; ++q) sum[q] = 0.0;
+    uint4 next = piece(lr);
+    for (int i0 = 0; i0 < n; i0 += step) {
+        reinterpret_cast<uint4*>(s_rows + lr * kStride)[lc] = next;
+        next = piece(i0 + step + lr);
+        __syncthreads();
+        if (known == 0) {
+#pragma unroll
+            for (int q = 0; q < D / kWave; ++q)
+                if (q * nt + tid < D)
+                    sum[q] = sum_rows(sum[q], s_rows + q * nt + tid, min(step, n - i0),
+                                      [](int i) { return static_cast<size_t>(i) * kStride; });
+        }
+        if (tid >= i0 && tid < i0 + step) own.load(s_rows + (tid - i0) * kStride);
+        __syncthreads();
+    }
+    int rep = 0;
+    if (known == 0) {
+#pragma unroll
+        for (int q = 0; q < D / kWave; ++q)
+            if (q * nt + tid < D) s_vec[q * nt + tid] = sum[q] / static_cast<double>(n);
+        __syncthreads();
+        const double dd = own.sqdist(s_vec);
+        ArgVal best{INFINITY, 0x7fffffff};
+        if (tid < n) best = pick_min(best, ArgVal{dd, tid});
+        best = block_arg<false>(best, s_red, nw);
+        rep = best.i < n ? best.i : 0;  // no winner among NaN keys: member 0
+    }
+    double m = 0.0;
+    int owner = 0;
+    for (int u = 0; u < r; ++u) {
+        if (u < known)
+            rep = s_reps[u];
+        else if (tid == 0)
+            s_reps[u] = rep;
+        if (tid == rep) own.store(s_rows);
+        __syncthreads();
+        for (int j = tid; j < D; j += nt) s_vec[j] = static_cast<double>(load_elem(s_rows, j));
+        __syncthreads();
+        // fold the new representative into the running minimum; a chosen
+        // representative gets -1 so that it is never chosen again
+        const double dd = own.sqdist(s_vec);
+        if (u == 0 || dd < m) {
+            m = dd;
+            owner = u;
+        }
+        if (tid == rep) {
+            m = -1.0;
+            owner = u;
+        }
+        if (u + 1 < r && u + 1 >= known) {
+            ArgVal far{-INFINITY, 0x7fffffff};
+            if (tid < n) far = pick_max(far, ArgVal{m, tid});
+            far = block_arg<true>(far, s_red, nw);
+            rep = far.i < n ? far.i : 0;
+        }
+    }
+    write_teams<T, D, true, true, 0>(out, K, V, N, R, M, bh, start, n, team0, s_build, [=](int i) { return start + i; },
+                                     [=](int) { return owner; }, [](int, T*) {});
 }
 
 // Label-defined parents: the members are the token indices mem[0 .. n)
 // (ascending) of the pair's member lists.
 template <typename T, int D>
 __global__ __launch_bounds__(kBuildThreads) void k_build_lists(
-    const T* __restrict__ K, int N, int R, int M, MemberState* __restrict__ state, int* __restrict__ team_begin,
-    int* __restrict__ team_size, double* __restrict__ log_n, int* __restrict__ rep_token, int* __restrict__ perm,
+    const T* __restrict__ K, int N, int R, int M, MemberState* __restrict__ state, TeamArrays<T> out,
     const int* __restrict__ members, const int* __restrict__ pbeg, const int* __restrict__ toff, int Mp) {
     extern __shared__ __align__(16) char s_build[];
     const int p = blockIdx.x, bh = blockIdx.y;
@@ -920,11 +1233,9 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_lists(
     if (n <= 0) return;  // empty parents are omitted (uniform over the workgroup)
     const int* const mem = members + static_cast<size_t>(bh) * N + start;
     if (n <= static_cast<int>(blockDim.x))  // uniform
-        build_parent<T, D, true, true>(K, nullptr, N, R, M, bh, start, n, toff[at], mem, state, team_begin, team_size,
-                                       log_n, rep_token, perm, nullptr, nullptr, nullptr, s_build);
+        build_parent<T, D, true, true>(K, nullptr, N, R, M, bh, start, n, toff[at], mem, state, out, s_build);
     else
-        build_parent<T, D, true, false>(K, nullptr, N, R, M, bh, start, n, toff[at], mem, state, team_begin, team_size,
-                                        log_n, rep_token, perm, nullptr, nullptr, nullptr, s_build);
+        build_parent<T, D, true, false>(K, nullptr, N, R, M, bh, start, n, toff[at], mem, state, out, s_build);
 }
 
 // Row gather into team order: packed[bh][pos] = src[bh][perm[bh][pos]], and the
@@ -953,52 +1264,72 @@ size_t build_state_bytes() { return sizeof(MemberState); }
 // state stays in registers and the workgroup writes the packed rows itself.
 bool build_packs_in_place(int N, int P) { return std::min(P, N) <= kBuildThreads; }
 
-hipError_t launch_build_parents(const void* K, const void* V, santapp_dtype dtype, int BH, int N,
-                                int d, int P, int R, int M, void* state,
-                                int* team_begin, int* team_size, double* log_n, int* rep_token,
-                                int* perm, void* packed_K, void* packed_V, void* reps, int* team_count,
-                                hipStream_t s) {
-    const dim3 grid((N + P - 1) / P, BH);
-    const int members = std::min(P, N);
-    const int threads = std::min(kBuildThreads, (members + kWave - 1) / kWave * kWave);
-    const bool one = build_packs_in_place(N, P);
-    const int lds = build_lds(threads / kWave, R, d, dtype == SANTAPP_BF16 ? 2 : 4).total;
-#define SANTAPP_BUILD(TT, DD)                                                                        \
-    do {                                                                                            \
-        auto kern = one ? k_build_contiguous<TT, DD, true> : k_build_contiguous<TT, DD, false>;    \
-        kern<<<grid, threads, lds, s>>>(static_cast<const TT*>(K), static_cast<const TT*>(V), N, P, R, M, \
-                                        static_cast<MemberState*>(state), team_begin, team_size, log_n,   \
-                                        rep_token, perm, static_cast<TT*>(packed_K),               \
-                                        static_cast<TT*>(packed_V), static_cast<TT*>(reps), team_count);  \
-        return hipGetLastError();                                                                   \
-    } while (0)
-    if (dtype == SANTAPP_BF16 && d == 128) SANTAPP_BUILD(bf16_t, 128);
-    if (dtype == SANTAPP_BF16 && d == 64) SANTAPP_BUILD(bf16_t, 64);
-    if (dtype == SANTAPP_FP32 && d == 128) SANTAPP_BUILD(float, 128);
-    if (dtype == SANTAPP_FP32 && d == 64) SANTAPP_BUILD(float, 64);
-#undef SANTAPP_BUILD
+namespace {
+
+// f(element type, dims) of a build
+template <typename F>
+hipError_t build_forms(santapp_dtype dtype, int d, F&& f) {
+    if (dtype == SANTAPP_BF16 && d == 128) return f(bf16_t{}, std::integral_constant<int, 128>{});
+    if (dtype == SANTAPP_BF16 && d == 64) return f(bf16_t{}, std::integral_constant<int, 64>{});
+    if (dtype == SANTAPP_FP32 && d == 128) return f(float{}, std::integral_constant<int, 128>{});
+    if (dtype == SANTAPP_FP32 && d == 64) return f(float{}, std::integral_constant<int, 64>{});
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_build_parent_lists(const void* K, santapp_dtype dtype, int BH, int N, int d, int Mp,
-                                     int R, int M, const int* members, const int* pbeg, const int* toff,
-                                     void* state, int* team_begin, int* team_size,
-                                     double* log_n, int* rep_token, int* perm, hipStream_t s) {
+template <typename T>
+TeamArrays<T> team_arrays(const TeamTable& t) {
+    return TeamArrays<T>{t.team_begin, t.team_size, t.log_n, t.rep_token, t.perm,
+                         static_cast<T*>(t.packed_K), static_cast<T*>(t.packed_V), static_cast<T*>(t.reps)};
+}
+
+int build_threads(int N, int P) { return std::min(kBuildThreads, (std::min(P, N) + kWave - 1) / kWave * kWave); }
+
+}  // namespace
+
+hipError_t launch_build_parents(const void* K, const void* V, santapp_dtype dtype, int BH, int N, int d, int P, int R,
+                                int M, void* state, const TeamTable& t, int* team_count, hipStream_t s) {
+    const dim3 grid((N + P - 1) / P, BH);
+    const int threads = build_threads(N, P);
+    const int lds = build_lds(threads / kWave, R, d, dtype == SANTAPP_BF16 ? 2 : 4).total;
+    return build_forms(dtype, d, [&](auto elem, auto dims) {
+        using T = decltype(elem);
+        constexpr int D = decltype(dims)::value;
+        auto kern = build_packs_in_place(N, P) ? k_build_contiguous<T, D, true> : k_build_contiguous<T, D, false>;
+        kern<<<grid, threads, lds, s>>>(static_cast<const T*>(K), static_cast<const T*>(V), N, P, R, M,
+                                        static_cast<MemberState*>(state), team_arrays<T>(t), team_count);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_build_open(const void* K, const void* V, santapp_dtype dtype, int BH, int N, int d, int P, int R, int M,
+                             const TeamTable& t, hipStream_t s) {
+    const dim3 grid((N + P - 1) / P, BH);
+    const int threads = build_threads(N, P);
+    const int lds = build_lds(threads / kWave, R, d, dtype == SANTAPP_BF16 ? 2 : 4).total;
+    return build_forms(dtype, d, [&](auto elem, auto dims) -> hipError_t {
+        using T = decltype(elem);
+        constexpr int D = decltype(dims)::value;
+        if constexpr (D * sizeof(T) > 256) {
+            return hipErrorInvalidValue;  // such parents are never left open
+        } else {
+            k_build_open<T, D><<<grid, threads, lds + open_stage_bytes<T, D>(threads), s>>>(
+                static_cast<const T*>(K), static_cast<const T*>(V), N, P, R, M, team_arrays<T>(t));
+            return hipGetLastError();
+        }
+    });
+}
+
+hipError_t launch_build_parent_lists(const void* K, santapp_dtype dtype, int BH, int N, int d, int Mp, int R, int M,
+                                     const int* members, const int* pbeg, const int* toff, void* state,
+                                     const TeamTable& t, hipStream_t s) {
     const dim3 grid(Mp, BH);
     const int lds = build_lds(kBuildWaves, R, d, dtype == SANTAPP_BF16 ? 2 : 4).total;
-#define SANTAPP_LISTS(TT, DD)                                                                         \
-    do {                                                                                             \
-        k_build_lists<TT, DD><<<grid, kBuildThreads, lds, s>>>(                                     \
-            static_cast<const TT*>(K), N, R, M, static_cast<MemberState*>(state), team_begin, team_size, log_n, \
-            rep_token, perm, members, pbeg, toff, Mp);                                              \
-        return hipGetLastError();                                                                    \
-    } while (0)
-    if (dtype == SANTAPP_BF16 && d == 128) SANTAPP_LISTS(bf16_t, 128);
-    if (dtype == SANTAPP_BF16 && d == 64) SANTAPP_LISTS(bf16_t, 64);
-    if (dtype == SANTAPP_FP32 && d == 128) SANTAPP_LISTS(float, 128);
-    if (dtype == SANTAPP_FP32 && d == 64) SANTAPP_LISTS(float, 64);
-#undef SANTAPP_LISTS
-    return hipErrorInvalidValue;
+    return build_forms(dtype, d, [&](auto elem, auto dims) {
+        using T = decltype(elem);
+        k_build_lists<T, decltype(dims)::value><<<grid, kBuildThreads, lds, s>>>(
+            static_cast<const T*>(K), N, R, M, static_cast<MemberState*>(state), team_arrays<T>(t), members, pbeg, toff, Mp);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_gather_rows(const void* src, void* dst, const int* index, int BH, int rows_out,

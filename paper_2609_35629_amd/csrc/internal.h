@@ -149,14 +149,23 @@ bool build_packs_in_place(int N, int P);
 // Bytes of member state per token of the team build.
 size_t build_state_bytes();
 
+// A table's device arrays.
+struct TeamTable {
+    void *packed_K, *packed_V, *reps;
+    int *team_begin, *team_size;
+    double* log_n;
+    int *rep_token, *perm;
+};
+
 // Team table of every contiguous parent, and team_count[bh] = M.  Where
 // build_packs_in_place, the packed copies too (state may be null); otherwise
-// the caller gathers them from perm and rep_token.
-hipError_t launch_build_parents(const void* K, const void* V, santapp_dtype dtype, int BH, int N,
-                                int d, int P, int R, int M, void* state,
-                                int* team_begin, int* team_size, double* log_n, int* rep_token,
-                                int* perm, void* packed_K, void* packed_V, void* reps, int* team_count,
-                                hipStream_t s);
+// the caller gathers them from perm and rep_token.  A parent whose choices the
+// estimates leave open may come back unbuilt, its first team's size negative:
+// launch_build_open then builds all of these.
+hipError_t launch_build_parents(const void* K, const void* V, santapp_dtype dtype, int BH, int N, int d, int P, int R,
+                                int M, void* state, const TeamTable& t, int* team_count, hipStream_t s);
+hipError_t launch_build_open(const void* K, const void* V, santapp_dtype dtype, int BH, int N, int d, int P, int R, int M,
+                             const TeamTable& t, hipStream_t s);
 
 hipError_t launch_gather_rows(const void* src, void* dst, const int* index, int BH, int rows_out,
                               int rows_in, size_t row_bytes, hipStream_t s);
@@ -164,10 +173,9 @@ hipError_t launch_gather_rows(const void* src, void* dst, const int* index, int 
 // Team table of label-defined parents: parent u of pair bh has the members
 // members[bh N + pbeg[bh (Mp+1) + u] ..] (token order) and its first team is
 // toff[bh (Mp+1) + u]; team_begin is a position in that member order.
-hipError_t launch_build_parent_lists(const void* K, santapp_dtype dtype, int BH, int N, int d, int Mp,
-                                     int R, int M, const int* members, const int* pbeg, const int* toff,
-                                     void* state, int* team_begin, int* team_size,
-                                     double* log_n, int* rep_token, int* perm, hipStream_t s);
+hipError_t launch_build_parent_lists(const void* K, santapp_dtype dtype, int BH, int N, int d, int Mp, int R, int M,
+                                     const int* members, const int* pbeg, const int* toff, void* state,
+                                     const TeamTable& t, hipStream_t s);
 
 // k-means state of one (b, kv): smoothed batch inertia and its minimum, the
 // count of steps without a new minimum, the stop flag and the steps run.

@@ -70,6 +70,52 @@ def test_hard_keys_match_oracle(kind, dtype, d, N, P, R):
         np.testing.assert_array_equal(gl[3][0, kv, :t.M], t.rep_token)
 
 
+@pytest.mark.parametrize("kind", ["few", "equal", "pad", "outlier", "offset", "late", "huge"])
+@pytest.mark.parametrize("dtype,d,N,P,R", [
+    ("bf16", 128, 2100, 1024, 9), ("bf16", 64, 1500, 1000, 70), ("fp32", 64, 2100, 1024, 9), ("fp32", 128, 1024, 1024, 5),
+    ("bf16", 128, 330, 150, 12), ("fp32", 64, 200, 100, 3),
+])
+def test_open_parents_match_oracle(kind, dtype, d, N, P, R):
+    """Parents with more candidates at one choice than the estimates' kernel
+    compares (64), from the first choice or after some rounds: the second build
+    kernel goes on from the representatives found."""
+    log(f"[gpu] build open parents keys={kind} {dtype} d={d} N={N} P={P} R={R}")
+    rng = np.random.default_rng(9)
+    x = rng.standard_normal((1, 2, N, d))
+    if kind in ("few", "equal"):
+        x = x[:, :, rng.integers(0, 5 if kind == "few" else 1, size=N)]
+    elif kind == "pad":
+        x[:, :, N // 2:] = 0.0
+    elif kind == "outlier":
+        x[:, :, ::P] *= 300.0
+    elif kind == "offset":
+        x += 300.0
+    elif kind == "late":  # distinct far rows first, then copies of a nearer one
+        x = 0.01 * x
+        x[:, :, ::3] = rng.standard_normal((1, 2, 1, d))
+        far = rng.integers(0, N, size=(N + P - 1) // P * 3)
+        x[:, :, far] = 5.0 * rng.standard_normal((1, 2, far.size, d))
+    else:
+        x *= 1e22
+    K = x.astype(np.float32)
+    K = datagen.round_bf16_bits(K) if dtype == "bf16" else K
+    Kd = to_dev(K, dtype)
+    x = _widen(K, dtype)
+    teams = sp.build_teams(Kd, -Kd, P, R)
+    torch.cuda.synchronize()
+    gt = gpu_tables(teams)
+    as_int = torch.int16 if dtype == "bf16" else torch.int32
+    for kv in range(2):
+        assert_tables_equal(gt, [[oracle.build_teams(x[0, k], P, R) for k in range(2)]], 0, kv)
+        perm, rt = torch.from_numpy(gt[0][0, kv]).long().cuda(), torch.from_numpy(gt[3][0, kv]).long().cuda()
+        for got, src, idx in ((teams.packed_K(), Kd, perm), (teams.packed_V(), -Kd, perm), (teams.reps(), Kd, rt)):
+            assert torch.equal(got.view(as_int)[0, kv], src.view(as_int)[0, kv][idx])
+    if R < P:  # a step over the table: the chunk capacities are those of the finished one
+        q = torch.randn((1, 4, d), device="cuda")
+        out = sp.decode(teams, q, None, None, min(4, teams.M - 1), seed=1, step=1, scale=0.01)
+        assert torch.isfinite(out).all()
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("fp32", 128), ("fp32", 64)])
 @pytest.mark.parametrize("N,P,R", [
     (97, 1, 1), (97, 15, 4), (160, 16, 4), (161, 17, 3), (200, 64, 64), (195, 65, 8),
