@@ -52,6 +52,7 @@ constexpr int kPickCache = 16;  // sample values per thread k_kpp_pick keeps in 
 constexpr int kAsgThreads = 256;
 constexpr int kAsgPts = 64;   // batch points per assignment workgroup
 constexpr int kAsgCen = 32;   // centers per LDS tile
+constexpr int kFullTile = 12; // points of a workgroup past which all are compared with every center together
 constexpr int kUpdBatch = 32; // workgroup partials the center update loads at once
 constexpr int kListThreads = 1024;
 constexpr int kListWaves = kListThreads / kWave;
@@ -602,30 +603,107 @@ __global__ __launch_bounds__(kAsgThreads) void k_km_assign(
             s_lab[tid] = x.u2;
         }
     }
-    // every center: half a wave per point
-    for (int i = tid >> 5; i < s_full; i += kAsgThreads / 32) {
-        const int p = s_list[i];
+    // every center: half a wave per point, or, for many points, all points
+    // against 16 centers at a time in LDS (a lane per point, a wave per four
+    // centers).  Where every point comes here (keys whose common offset is 100
+    // times their spread), k-means parents of 32K tokens (32 centers, four pairs,
+    // d = 128, bf16) took 2600 us with half a wave per point alone, 2210 with fp64
+    // distances throughout; now 1590.  The line: eight points take half a wave
+    // each 2 us, all points together 2.7.
+    if (s_full > kFullTile) {  // uniform
+        typedef double f64x2 __attribute__((ext_vector_type(2)));
+        constexpr int kCen = 16, kRow = D + 2;
+        static_assert(kCen * kRow * sizeof(double) <= sizeof(s_c), "the fp64 tile lies where the fp32 one was");
+        double* const s_t = reinterpret_cast<double*>(&s_c[0][0]);
         double bd = INFINITY;
         int bu = 0x7fffffff;
-        for (int u = tid & 31; u < M; u += 32) {
-            const double d2 = point_dist<D>(s_x[p], cb + static_cast<size_t>(u) * D);
-            if (d2 < bd) {
-                bd = d2;
-                bu = u;
+        for (int ct = 0; ct < M; ct += kCen) {
+            constexpr int kPieces = kCen * D / (2 * kAsgThreads);
+            f64x2 v[kPieces];
+#pragma unroll
+            for (int q = 0; q < kPieces; ++q) {
+                const int e = q * kAsgThreads + tid, u = e / (D / 2), k = 2 * (e % (D / 2));
+                v[q] = *reinterpret_cast<const f64x2*>(cb + static_cast<size_t>(min(ct + u, M - 1)) * D + k);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kPieces; ++q) {
+                const int e = q * kAsgThreads + tid, u = e / (D / 2), k = 2 * (e % (D / 2));
+                *reinterpret_cast<f64x2*>(s_t + u * kRow + k) = v[q];
+            }
+            __syncthreads();
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+            for (int k = 0; k < D; k += 4) {
+                const float4 x = *reinterpret_cast<const float4*>(&s_x[lane][k]);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const double2 y0 = *reinterpret_cast<const double2*>(s_t + (4 * wv + c) * kRow + k);
+                    const double2 y1 = *reinterpret_cast<const double2*>(s_t + (4 * wv + c) * kRow + k + 2);
+                    const double t0 = static_cast<double>(x.x) - y0.x;
+                    acc[c] = acc[c] + t0 * t0;
+                    const double t1 = static_cast<double>(x.y) - y0.y;
+                    acc[c] = acc[c] + t1 * t1;
+                    const double t2 = static_cast<double>(x.z) - y1.x;
+                    acc[c] = acc[c] + t2 * t2;
+                    const double t3 = static_cast<double>(x.w) - y1.y;
+                    acc[c] = acc[c] + t3 * t3;
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int u = ct + 4 * wv + c;
+                if (u < M && acc[c] < bd) {
+                    bd = acc[c];
+                    bu = u;
+                }
             }
         }
-        for (int off = 16; off > 0; off >>= 1) {
-            const double od = __shfl_xor(bd, off);
-            const int ou = __shfl_xor(bu, off);
-            if (od < bd || (od == bd && ou < bu)) {
-                bd = od;
-                bu = ou;
+        // the four waves' best of each point
+        static_assert(kAsgPts == kWave && kAsgThreads == 4 * kWave, "a lane per point, four centers a wave");
+        int* const s_u = reinterpret_cast<int*>(s_t + kAsgThreads);
+        __syncthreads();
+        s_t[tid] = bd;
+        s_u[tid] = bu;
+        __syncthreads();
+        if (tid < s_full) {
+            const int p = s_list[tid];
+            for (int w = 0; w < kAsgThreads / kWave; ++w) {
+                const double od = s_t[w * kWave + p];
+                const int ou = s_u[w * kWave + p];
+                if (w == 0 || od < bd || (od == bd && ou < bu)) {
+                    bd = od;
+                    bu = ou;
+                }
             }
-        }
-        if ((tid & 31) == 0) {
-            // no winner (NaN keys): center 0, so every label stays in range
-            s_lab[p] = bu < M ? bu : 0;
+            s_lab[p] = bu < M ? bu : 0;  // as below
             s_e[p] = bd;
+        }
+    } else {
+        for (int i = tid >> 5; i < s_full; i += kAsgThreads / 32) {
+            const int p = s_list[i];
+            double bd = INFINITY;
+            int bu = 0x7fffffff;
+            for (int u = tid & 31; u < M; u += 32) {
+                const double d2 = point_dist<D>(s_x[p], cb + static_cast<size_t>(u) * D);
+                if (d2 < bd) {
+                    bd = d2;
+                    bu = u;
+                }
+            }
+            for (int off = 16; off > 0; off >>= 1) {
+                const double od = __shfl_xor(bd, off);
+                const int ou = __shfl_xor(bu, off);
+                if (od < bd || (od == bd && ou < bu)) {
+                    bd = od;
+                    bu = ou;
+                }
+            }
+            if ((tid & 31) == 0) {
+                // no winner (NaN keys): center 0, so every label stays in range
+                s_lab[p] = bu < M ? bu : 0;
+                s_e[p] = bd;
+            }
         }
     }
     __syncthreads();

@@ -90,3 +90,27 @@ def test_member_lists_by_label_bits(num, N):
     np.testing.assert_array_equal(tb[0, 0, :t.M], t.team_ptr[:-1])
     np.testing.assert_array_equal(ts[0, 0, :t.M], t.sizes)
     np.testing.assert_array_equal(rt[0, 0, :t.M], t.rep_token)
+
+
+@pytest.mark.parametrize("kind,N,P,d,dtype", [
+    ("huge", 1500, 20, 128, torch.bfloat16),  # 75 centers: five tiles of 16, the last ragged
+    ("huge", 700, 41, 64, torch.float32),  # 17 centers
+    ("offset", 640, 40, 64, torch.float32),
+    ("offset", 640, 20, 128, torch.bfloat16),
+    ("some", 900, 30, 128, torch.float32),
+])
+def test_points_compared_with_every_center(kind, N, P, d, dtype):
+    """Workgroups where most points, or a few, are left open by the estimates:
+    compared with all centers together, or half a wave each."""
+    x = _keys("huge" if kind == "huge" else "normal", N, d, dtype).float()
+    if kind == "offset":
+        x += 200.0
+    elif kind == "some":
+        x[::40] *= 1e20
+    x = x.to(dtype)
+    log(f"[gpu] kmeans assign all centers {kind} N={N} P={P} d={d} {dtype}")
+    th = oracle.KMeansSettings(batch=200, max_iter=12)
+    labels, _, steps = sp.kmeans_parents(x[None, None].cuda(), P, batch_size=th.batch, max_iter=th.max_iter)
+    r = oracle.kmeans_parents(x.to(torch.float64).numpy(), P, th)
+    assert steps[0] == r.steps
+    np.testing.assert_array_equal(labels.cpu().numpy()[0, 0], r.labels)
