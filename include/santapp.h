@@ -255,10 +255,11 @@ typedef struct {
  * single-launch step) or counters that every completed call leaves at zero
  * (the three-launch kernels).  Sampled steps over more than 1024 teams per
  * (b, kv), with at most half as many query heads (B * Hq) as compute units,
- * add 20 bytes per (query head, team) for scores kept in memory, and a word
- * per sampling workgroup that every completed call leaves at zero; a workspace
- * without room for these is accepted down to the size without them, and the
- * step then samples by the kernel that keeps its scores on chip (the same
+ * add 20 bytes per (query head, team) for scores kept in memory, which budgets
+ * up to 144 over more than 1200 teams use, and a word per sampling workgroup
+ * that every completed call leaves at zero; a workspace without room for these
+ * is accepted down to the size without them, and the step then samples by the
+ * kernel that keeps its scores on chip, as other steps do (the same
  * sample, slower).  A workspace must be zeroed once before its
  * first use (santapp_workspace_zero) and needs nothing between calls.  Calls
  * that share a workspace must not overlap in time (use one workspace per

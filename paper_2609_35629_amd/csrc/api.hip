@@ -435,14 +435,20 @@ StepLayout decode_layout(int B, int Hq, int Hkv, int T, int d, int M, int Kp, co
     L.lc = c.take(BQ * M * sizeof(float));
     L.part = c.take(BH * L.maxwp * G * state_stride(d) * sizeof(float));
     L.total = c.off;
-    // The launch over all teams pays from about 1024 teams on, while the heads
+    // The launch over all teams pays from about 1200 teams on, while the heads
     // leave half the compute units to it (one step, this against a workgroup per
     // head): 28 heads 656 teams 32.3 / 28.0 us, 1024 33.9 / 32.4, 1280 35.0 /
-    // 35.6, 2048 37.1 / 43.1; 112 heads 1024 teams 48.4 / 46.9, 1280 51.3 /
-    // 51.4, 2048 62.7 / 68.4; 256 heads 1024 teams 51.4 / 50.2, 2048 68.9 / 64.5.
+    // 35.6, 2048 37.1 / 43.1; 112 heads 1024 teams 48.4 / 46.9, 1100 35.3 / 34.4,
+    // 1280 51.3 / 51.4, 2048 62.7 / 68.4; 256 heads 1024 teams 51.4 / 50.2, 2048
+    // 68.9 / 64.5.  And for budgets whose teams, with those that the bound lets in
+    // beside them (about 210 at K = 144, 250 at 160, whatever the table), fit its
+    // list of 256; past that it ranks all teams (28 heads, K = 300: 2048 teams 59 /
+    // 46.6 us, 8192 teams 130 / 117).  The regions are part of the size from 1024
+    // teams on and for every budget, so that a workspace for one budget of a table
+    // serves its others.
     if (M > kKeyMinTeams && BQ <= static_cast<size_t>(cus) / 2 && !fused_step(dt, L)) {
         StepLayout X = L;
-        X.keys = true;
+        X.keys = M > kKeyUseTeams && Kp <= kKeyMaxK;
         X.key.stride = (M + 3) / 4 * 4;
         const size_t n = BQ * X.key.stride;
         X.key.yu = c.take(n * sizeof(uint32_t));

@@ -154,6 +154,7 @@ __device__ __forceinline__ float4 load_f4_coherent(const float* p) {
 // nothing.
 typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2v __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 constexpr int kCoherentPolicy = 16;  // sc1
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t coherent_rsrc(const void* base, uint32_t bytes) {
@@ -922,10 +923,12 @@ __host__ __device__ inline KeyLds key_lds(int M, int G) {
 //   - The K-th largest of 256 maxima (four a lane, the low half of their fp32
 //     keys dropped) bounds tau from below; the teams at or above it, a few more
 //     than K, are listed in team order and ranked by their exact keys.
-//   - More than kTopList of them (K near or past 256): the fp32 key of rank K
-//     over all teams; the teams above it are taken, those equal to it listed.
-//   - More than kTopList of those (absent teams): their exact keys' differing
-//     bits are fixed one by one, from memory.
+//   - More than kTopList of them (scores close for their size): rank K's upper half over
+//     all teams, bit by bit in LDS; the teams above it are taken, those equal to
+//     it listed.
+//   - More than kTopList of those: the same on the lower halves of their keys.
+//   - More than kTopList still (absent teams): their exact keys' differing bits
+//     are fixed one by one, from memory.
 // Every launch runs this code once, so its time is round trips and instruction
 // fetches: all keys are requested at once, and the loops over them stay rolled
 // (with the list's loop unrolled over keys in registers the launch took 31 us
@@ -965,29 +968,32 @@ __device__ void key_select(const DecodeArgs& a, const Views& v, int p, char* lds
         w.w = g + 3 < M ? w.w : 0;
         return w;
     };
+    // The groups of the maxima step through the lanes' and the quads' places: teams
+    // come in runs of R per parent, whose first representatives score higher, and
+    // with a fixed place some groups held most of the sample (8192 teams of R = 4,
+    // K = 128: more than 256 teams above the bound, 167 us a step instead of 47).
     uint32_t gm[4] = {0, 0, 0, 0};
     {
         u32x4v w[KQ];
 #pragma unroll
-        for (int i = 0; i < KQ; ++i) w[i] = load4(4 * (64 * i + lane));
+        for (int i = 0; i < KQ; ++i) w[i] = load4(4 * (64 * i + ((lane + i) & (kWave - 1))));
 #pragma unroll
         for (int i = 0; i < KQ; ++i) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) gm[e] = max(gm[e], w[i][e]);
-            const int g = 4 * (64 * i + lane);
+            for (int e = 0; e < 4; ++e) gm[(e + i + (i >> 2)) & 3] = max(gm[(e + i + (i >> 2)) & 3], w[i][e]);
+            const int g = 4 * (64 * i + ((lane + i) & (kWave - 1)));
             if (g < Mr)
                 *reinterpret_cast<uint2*>(yh + g) =
                     make_uint2((w[i].x >> 16) | (w[i].y & 0xffff0000u), (w[i].z >> 16) | (w[i].w & 0xffff0000u));
         }
     }
     lds_order();
-    int n = kTopList + 1, want = Kp;
-    uint32_t t = 0;   // the listed teams' least key, or their key
+    int n = 0, want = Kp;
+    uint32_t t = 0;   // the half that the listed teams share, where they do
     bool up = false;  // teams were taken without a look at their exact keys
-    if (Kp < 4 * kWave) {  // uniform
-        // the teams whose upper half is at or above the bound's, in team order
-        const uint32_t t16 = wave_kth<4>(gm, Kp, 16) >> 16;
-        n = 0;
+    // the teams whose upper half is at or above the bound's, in team order
+    const uint32_t t16 = wave_kth<4>(gm, Kp, 16) >> 16;
+    {
 #pragma unroll 1
         for (int g0 = 0; g0 < Mr; g0 += 8 * kWave) {
             const int g = g0 + 8 * lane;
@@ -1005,52 +1011,87 @@ __device__ void key_select(const DecodeArgs& a, const Views& v, int p, char* lds
         }
     }
     if (n > kTopList) {  // uniform
-        // f(g, keys of teams g .. g + 3)
-        auto each4 = [&](auto&& f) __attribute__((always_inline)) {
+        up = true;
+        // f(g, in): bit e of in says that the half of team g + e lies in [lo, lo + span]
+        auto each8 = [&](uint32_t lo, uint32_t span, auto&& f) __attribute__((always_inline)) {
 #pragma unroll 1
-            for (int g0 = 0; g0 < M; g0 += 32 * kWave) {
-                u32x4v w[8];
+            for (int g0 = 0; g0 < Mr; g0 += 8 * kWave) {
+                const int g = g0 + 8 * lane;
+                const uint4 w = *reinterpret_cast<const uint4*>(yh + g);
+                const uint32_t y[4] = {w.x, w.y, w.z, w.w};
+                uint32_t in = 0;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) w[i] = load4(g0 + 4 * (64 * i + lane));
-#pragma unroll
-                for (int i = 0; i < 8; ++i) f(g0 + 4 * (64 * i + lane), w[i]);
+                for (int e = 0; e < 8; ++e) in |= ((y[e >> 1] >> (16 * (e & 1))) & 0xffffu) - lo <= span && g + e < M ? 1u << e : 0u;
+                if (__ballot(in != 0) != 0) f(g, in);  // uniform
             }
         };
-        for (int bit = 31; bit >= 0; --bit) {
-            const uint32_t c = t | (1u << bit);
-            int cnt = 0;
-            each4([&](int, const u32x4v& w) __attribute__((always_inline)) {
-                cnt += (w.x >= c ? 1 : 0) + (w.y >= c ? 1 : 0) + (w.z >= c ? 1 : 0) + (w.w >= c ? 1 : 0);
+        // the halves at or above c (c >= 1)
+        auto at_least = [&](uint32_t c) __attribute__((always_inline)) {
+            const u16x2 below = {static_cast<unsigned short>(c - 1), static_cast<unsigned short>(c - 1)};
+            const u16x2 one = {1, 1};
+            u16x2 cnt = {0, 0};
+#pragma unroll 4
+            for (int g0 = 0; g0 < Mr; g0 += 8 * kWave) {
+                const uint4 w = *reinterpret_cast<const uint4*>(yh + g0 + 8 * lane);
+                const uint32_t y[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    cnt += __builtin_elementwise_min(__builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, y[e]), below), one);
+            }
+            return wave_sum(static_cast<int>(cnt.x) + static_cast<int>(cnt.y));
+        };
+        t = t16;
+        for (int level = 0; level < 2 && n > kTopList; ++level) {  // uniform
+            // the half of rank `want`: the bound, or of the lower halves the
+            // largest, where it is that (absent teams); else bit by bit
+            if (level == 0 ? at_least(t + 1) > want : at_least(t) <= want) {
+                t = 0;
+                for (int bit = 15; bit >= 0; --bit) {
+                    const uint32_t c = t | (1u << bit);
+                    if (at_least(c) > want) t = c;
+                }
+            }
+            // above it: taken; equal: listed in team order
+            int above = 0;
+            each8(t + 1, 0xffffu, [&](int g, uint32_t in) __attribute__((always_inline)) {
+                if (in != 0) atomicOr(&bits[g >> 5], in << (g & 31));
+                above += static_cast<int>(__popc(in));
             });
-            if (wave_sum(cnt) > Kp) t = c;
-        }
-        up = true;
-        n = 0;
-        each4([&](int g, const u32x4v& w) __attribute__((always_inline)) {
-            bool in[4];
-            int above = 0, mine = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (w[e] > t) {  // past the table the key is 0
-                    take(g + e);
-                    ++above;
-                }
-                in[e] = g + e < M && w[e] == t;
-                mine += in[e] ? 1 : 0;
-            }
             want -= wave_sum(above);
-            if (__ballot(mine != 0) == 0) return;  // uniform
-            const int inc = wave_incl_scan(mine);
-            int at = n + inc - mine;
+            n = 0;
+            each8(t, 0, [&](int g, uint32_t in) __attribute__((always_inline)) {
+                const int mine = static_cast<int>(__popc(in)), inc = wave_incl_scan(mine);
+                int at = n + inc - mine;
+                for (; in != 0; in &= in - 1, ++at)
+                    if (at < kTopList) s_list[at] = static_cast<uint16_t>(g + __ffs(static_cast<int>(in)) - 1);
+                n += readlane(inc, kWave - 1);
+            });
+            if (level == 0 && n > kTopList) {
+                // the equal ones' lower halves (0 counted with 1) in their place,
+                // the others out of it
+                lds_order();
+                uint32_t top = 0;
+#pragma unroll 1
+                for (int g0 = 0; g0 < Mr; g0 += 32 * kWave) {
+                    u32x4v w[8];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (in[e]) {
-                    if (at < kTopList) s_list[at] = static_cast<uint16_t>(g + e);
-                    ++at;
+                    for (int i = 0; i < 8; ++i) w[i] = load4(g0 + 4 * (64 * i + lane));
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int g = g0 + 4 * (64 * i + lane);
+                        uint32_t h[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            h[e] = (w[i][e] >> 16) == t && g + e < M ? max(w[i][e] & 0xffffu, 1u) : 0u;
+                            top = max(top, h[e]);
+                        }
+                        if (g < Mr) *reinterpret_cast<uint2*>(yh + g) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+                    }
                 }
+                lds_order();
+                t = wave_max_u32(top);
             }
-            n += readlane(inc, kWave - 1);
-        });
+        }
     }
     lds_order();
     // rank `want` among the listed teams, by their exact keys
@@ -1112,16 +1153,25 @@ __device__ void key_select(const DecodeArgs& a, const Views& v, int p, char* lds
             need -= static_cast<int>(__popcll(be));
         }
     } else {
-        // the listed teams' keys in team order, 64 teams at a time
-        up = true;
+        // the teams whose (lower) half is t: their keys in team order, eight times
+        // 64 teams' requested at once
         auto each = [&](auto&& f) __attribute__((always_inline)) {
-            for (int g0 = 0; g0 < M; g0 += kWave) {
-                const int g = min(g0 + lane, M - 1);
-                f(g, g0 + lane < M && load_u32_coherent(kw.yu + row + g) == t, key_of(g));
+#pragma unroll 1
+            for (int g0 = 0; g0 < M; g0 += 8 * kWave) {
+                uint64_t k[8];
+                bool in[8];
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    const int g = g0 + r * kWave + lane;
+                    in[r] = g < M && yh[min(g, M - 1)] == t;
+                    k[r] = in[r] ? key_of(g) : 0;
+                }
+#pragma unroll
+                for (int r = 0; r < 8; ++r) f(g0 + r * kWave + lane, in[r], k[r]);
             }
         };
         uint64_t kand = ~0ull, kor = 0;
-        each([&](int, bool in, uint64_t k) {
+        each([&](int, bool in, uint64_t k) __attribute__((always_inline)) {
             if (in) {
                 kand &= k;
                 kor |= k;
@@ -1134,30 +1184,56 @@ __device__ void key_select(const DecodeArgs& a, const Views& v, int p, char* lds
             const uint64_t bit = 1ull << (63 - __clzll(static_cast<long long>(diff)));
             const uint64_t c = tkey | bit;
             int cnt = 0;
-            each([&](int, bool in, uint64_t k) { cnt += static_cast<int>(__popcll(__ballot(in && k >= c))); });
+            each([&](int, bool in, uint64_t k) __attribute__((always_inline)) { cnt += static_cast<int>(__popcll(__ballot(in && k >= c))); });
             if (cnt > want) tkey = c;
             diff &= ~bit;
         }
         int need = want;
-        each([&](int, bool in, uint64_t k) { need -= static_cast<int>(__popcll(__ballot(in && k > tkey))); });
-        each([&](int g, bool in, uint64_t k) {
+        if (kand != kor)  // uniform
+            each([&](int, bool in, uint64_t k) __attribute__((always_inline)) { need -= static_cast<int>(__popcll(__ballot(in && k > tkey))); });
+        auto choose = [&](int g, bool in, uint64_t k) __attribute__((always_inline)) {
             const uint64_t be = __ballot(in && k == tkey);
             if (in && (k > tkey || (k == tkey && static_cast<int>(__popcll(be & lt)) < need))) take(g);
             need -= static_cast<int>(__popcll(be));
-        });
+        };
+        if (kand != kor) {  // uniform
+            each(choose);
+        } else {  // equal keys, as absent teams have: the first `want` of them
+#pragma unroll 1
+            for (int g0 = 0; g0 < M && need > 0; g0 += kWave) {
+                const int g = g0 + lane;
+                choose(g, g < M && yh[min(g, M - 1)] == t, tkey);
+            }
+        }
     }
     lds_order();
     // the sample words, and log c of the teams that have none yet
     const double tau = key_value(tkey);
-    for (int i = lane; i < a.lay.swords; i += kWave) {
-        const uint64_t w = (static_cast<uint64_t>(bits[2 * i + 1]) << 32) | bits[2 * i];
-        v.sbits[bq * a.lay.swords + i] = w;
-        if (up) {
-            for (uint64_t x = w; x != 0; x &= x - 1) {
-                const int g = 64 * i + __ffsll(static_cast<unsigned long long>(x)) - 1;
-                v.lc[bq * M + g] = log_inclusion(static_cast<float>(phi_of(g) - tau));
-            }
+    for (int i = lane; i < a.lay.swords; i += kWave)
+        v.sbits[bq * a.lay.swords + i] = (static_cast<uint64_t>(bits[2 * i + 1]) << 32) | bits[2 * i];
+    if (up) {
+        // the sample's teams, listed, so that all of its phi are requested at once
+        static_assert(kKeyMaxK <= kTopList, "the sample fits the list");
+        int at = 0;
+        for (int i0 = 0; i0 < words; i0 += kWave) {
+            uint32_t x = i0 + lane < words ? bits[i0 + lane] : 0;
+            const int mine = static_cast<int>(__popc(x)), inc = wave_incl_scan(mine);
+            for (int j = at + inc - mine; x != 0; x &= x - 1, ++j)
+                if (j < kTopList) s_list[j] = static_cast<uint16_t>(32 * (i0 + lane) + __ffs(static_cast<int>(x)) - 1);
+            at += readlane(inc, kWave - 1);
         }
+        lds_order();
+        double ph[kTopList / kWave];
+        int g[kTopList / kWave];
+#pragma unroll
+        for (int r = 0; r < kTopList / kWave; ++r) {
+            const bool in = r * kWave + lane < Kp;
+            g[r] = in ? s_list[r * kWave + lane] : 0;
+            ph[r] = in ? phi_of(g[r]) : 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < kTopList / kWave; ++r)
+            if (r * kWave + lane < Kp) v.lc[bq * M + g[r]] = log_inclusion(static_cast<float>(ph[r] - tau));
     }
     if (lane == 0 && a.dbg_tau) a.dbg_tau[bq] = tau;
     if (a.dbg_sel || a.dbg_logc) {  // the sample in ascending team order

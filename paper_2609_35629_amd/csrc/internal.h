@@ -91,7 +91,9 @@ int step_wgs(int cus, long long BH);
 // Teams of a workgroup of the sampling launch that keeps scores in memory, and
 // its workgroups per (b, kv) pair.
 constexpr int kKeyTeamsWg = 128;
-constexpr int kKeyMinTeams = 1024;  // tables of more teams take it (decode_layout's rule)
+constexpr int kKeyMinTeams = 1024;  // tables of more teams have its regions in their workspace,
+constexpr int kKeyUseTeams = 1200;  // of more than this take it,
+constexpr int kKeyMaxK = 144;       // for budgets up to this (decode_layout's rule)
 constexpr int key_blocks(int M) { return (M + kKeyTeamsWg - 1) / kKeyTeamsWg; }
 
 // Workgroup w of an attention grid of nwg workgroups serving BH (b, kv)

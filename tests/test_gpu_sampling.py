@@ -1,6 +1,6 @@
-"""The sampling launch that keeps scores in memory (tables of more than 1024
-teams, at most half as many heads as compute units, and a workspace that holds
-the scores) against the oracle and against the
+"""The sampling launch that keeps scores in memory (tables of more than 1200
+teams, budgets up to 144, at most half as many heads as compute units, and a
+workspace that holds the scores) against the oracle and against the
 sampling kernel that a smaller workspace takes: the same teams, tau and log c
 for budgets at the edges of its ranking (64 and 256 listed teams, nearly all
 teams), for the largest table, and where absent teams tie."""
@@ -66,6 +66,37 @@ def test_budgets_match_oracle_and_small_workspace(dtype, d, Hq, Hkv, N, P, R, bu
         assert torch.equal(got[0][1].sel, got[1][1].sel)
         assert torch.equal(got[0][1].union_teams, got[1][1].union_teams)
         assert torch.equal(got[0][1].union_rows, got[1][1].union_rows)
+
+
+@pytest.mark.parametrize("offset", [0.0, 200.0, 5000.0, 2e7])
+@pytest.mark.parametrize("dtype,d,N,budgets", [("bf16", 128, 8192, (100, 144, 145)), ("fp32", 64, 1500, (20, 144))])
+def test_scores_close_for_their_size(dtype, d, N, budgets, offset):
+    """Equal keys, so that scores are `offset` plus the noise: from some offset on
+    more than 256 teams share the upper half of their fp32 score with rank K, then
+    the whole fp32 score, and only the fp64 scores tell them apart."""
+    wl = datagen.WORKLOADS["qwen8k" if dtype == "bf16" else "tiny"].with_(
+        name="close", d=d, Hq=4, Hkv=2, N=N, P=1, R=1, T=0)
+    b = datagen.generate(wl)
+    b.K[:] = b.K[:, :, :1]
+    dot = (b.q.astype(np.float64).reshape(1, 2, 2, d) * b.f64(b.K[:, :, :1])).sum(-1)
+    b.q[:] = (b.q.reshape(1, 2, 2, d) / dot[..., None]).reshape(1, 4, d)  # q . k = 1
+    scale = max(offset, 1e-3)
+    db = dev_batch(b)
+    teams = sp.build_teams(db.K, db.V, 1, 1)
+    ot = oracle_teams(b)
+    pairs = [(0, h) for h in range(4)]
+    for K in budgets:
+        log(f"[gpu] close scores {dtype} d={d} M={teams.M} K={K} offset={offset}")
+        full, small = _small_workspace(teams, db, wl, K)
+        so = oracle.decode(b.q, b.f64(b.K), b.f64(b.V), b.f64(b.sK), b.f64(b.sV), ot, K, 7, K, scale, heads=pairs)
+        for ws in (full, small):
+            dbg = sp.DebugOut(1, 4, 2, teams.M, K)
+            out = sp.decode(teams, db.q, None, None, K, seed=7, step=K, scale=scale, workspace=ws, debug=dbg)
+            torch.cuda.synchronize()
+            sel, o = dbg.sel.cpu().numpy()[0], out.cpu().numpy()[0]
+            for h in range(4):
+                np.testing.assert_array_equal(sel[h], so.heads[0][h].sel)
+                assert oracle.rel_l2(o[h], so.heads[0][h].out) <= 1e-4
 
 
 def test_absent_teams_tie():
