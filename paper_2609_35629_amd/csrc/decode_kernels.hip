@@ -1715,7 +1715,8 @@ __device__ __forceinline__ bool walk_units(const DecodeArgs& a, const Views& v, 
         int run_u = nsuf, run_rows = 0, base = 0;
         do {
             int at = slot[0] - base;
-            for (uint32_t x = any; x != 0; x &= x - 1) {
+            // (a thread whose teams all belong to other passes has nothing to list)
+            for (uint32_t x = at < kPlanRecs && at + mine[0] > 0 ? any : 0; x != 0; x &= x - 1) {
                 const int k = __ffs(static_cast<int>(x)) - 1;
                 if (at >= 0 && at < kPlanRecs) {
                     int m = 0;
@@ -3348,10 +3349,23 @@ template <typename T, int D, int HK, bool DENSE, bool FUSED>
 __device__ __forceinline__ void attend_all(const DecodeArgs& a, const Views& v, char* t0, char* t1, char* misc) {
     const int w = blockIdx.x, nwg = gridDim.x;
     const int BH = a.B * a.Hkv;
+    // The separate launches list the union first (walk_units), which loses where
+    // nearly every team is in it: 8192 teams, the union expected from independent
+    // heads at 0.86 of them 176 us a step (182 over all teams in order), at 0.99
+    // 198 (187); the line is 7/8.
+    bool list = true;
+    if constexpr (HK == 16 && !DENSE && !FUSED) {
+        const float out = 1.f - static_cast<float>(a.Kp) / static_cast<float>(a.M);
+        float none = 1.f;  // a team is in no head's sample
+        for (int h = 0; h < a.G; ++h) none *= out;
+        list = none > 0.125f;
+    } else if constexpr (FUSED) {
+        list = static_cast<long long>(a.G) * a.Kp <= kPlanRecs;
+    }
     auto one = [&](int p, int iw, int nwp) {
-        if (HK > 1 && !DENSE && (!FUSED || static_cast<long long>(a.G) * a.Kp <= kPlanRecs))
+        if (HK > 1 && !DENSE && list)
             attend_pair<T, D, DENSE, FUSED, HK>(a, v, p, iw, nwp, t0, t1, misc);
-        else if constexpr (HK == 1 || DENSE || FUSED)
+        else if constexpr (HK == 1 || DENSE || FUSED || HK == 16)
             attend_pair<T, D, DENSE, FUSED, 1>(a, v, p, iw, nwp, t0, t1, misc);
     };
     if (BH <= nwg) {
