@@ -35,23 +35,34 @@ __device__ __forceinline__ uint16_t f64_to_bf16(double x) {
 __device__ __forceinline__ void store_mean(bf16_t* p, double v) { p->bits = f64_to_bf16(v); }
 __device__ __forceinline__ void store_mean(float* p, double v) { *p = static_cast<float>(v); }
 
+// U rows' values of dimension j of a team's rows from row i on, all in flight,
+// then added in order (cnt of them; a sum from 0.0 is never -0.0, so adding 0.0
+// changes nothing).
+template <int U, bool FULL, typename T, int D>
+__device__ __forceinline__ double add_rows(double s, const T* __restrict__ col, int i, int cnt) {
+    float v[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) v[k] = load_elem(col, static_cast<size_t>(i + (FULL ? k : min(k, cnt - 1))) * D);
+#pragma unroll
+    for (int k = 0; k < U; ++k) s = s + (FULL || k < cnt ? static_cast<double>(v[k]) : 0.0);
+    return s;
+}
+
 // Team means: thread j sums dimension j over the team's rows in packed
 // order (ascending token index), then divides by n_g.  The order of the sum
 // is the definition's, so a team is one serial chain, and the largest team
-// bounds the launch (700 rows at the 32K prompt): 64 rows at a time are read
-// whole and passed through LDS, the next 64 in flight while these are added
-// (reading a column per thread, 8 rows at a time, took 37 us; 31 us now).
+// bounds the launch: its rows are requested 32 at a time, the last ones in the
+// smallest block that holds them.  One call at 32K tokens, d = 128: P = 1024, R =
+// 16 (largest team 700 rows) bf16 33 us, fp32 48; bf16 P = 16, R = 4 18.5; 30000
+// tokens of fp32 d = 64 in teams of two 15.8.  Eight rows at a time took 48, 51,
+// 21.4 and 16.1; 64 at a time through LDS was slower the smaller the teams (36.5
+// and 61 for the last two).
 template <typename T, int D>
 __global__ __launch_bounds__(D) void k_team_centroid(const T* __restrict__ packed_K,
-                                                     const int* __restrict__ team_begin,
-                                                     const int* __restrict__ team_size, int N, int M,
-                                                     T* __restrict__ reps) {
+                                                      const int* __restrict__ team_begin,
+                                                      const int* __restrict__ team_size, int N, int M,
+                                                      T* __restrict__ reps) {
 #pragma clang fp contract(off)
-    constexpr int kRows = 64;
-    constexpr int kChunks = D * static_cast<int>(sizeof(T)) / 16;  // 16-byte chunks of a row
-    constexpr int kPerPass = D / kChunks;                          // rows one load of the workgroup covers
-    constexpr int kLoads = kRows / kPerPass;
-    __shared__ __align__(16) T s_rows[kRows][D];
     const int g = blockIdx.x, bh = blockIdx.y, j = threadIdx.x;
     const size_t t = static_cast<size_t>(bh) * M + g;
     const int begin = team_begin[t], n = team_size[t];
@@ -59,34 +70,20 @@ __global__ __launch_bounds__(D) void k_team_centroid(const T* __restrict__ packe
         store_mean(reps + t * D + j, 0.0);
         return;
     }
-    const T* const first = packed_K + (static_cast<size_t>(bh) * N + begin) * D;
-    const int lr = j / kChunks, lc = j % kChunks;
-    // chunk lc of row i (rows past the team's last repeat it)
-    auto chunk = [&](int i) {
-        return reinterpret_cast<const u32x4_t*>(first + static_cast<size_t>(min(i, n - 1)) * D)[lc];
-    };
-    u32x4_t x[kLoads];
-#pragma unroll
-    for (int k = 0; k < kLoads; ++k) x[k] = chunk(k * kPerPass + lr);
+    const T* const col = packed_K + (static_cast<size_t>(bh) * N + begin) * D + j;
     double s = 0.0;
-    for (int i0 = 0; i0 < n; i0 += kRows) {
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kLoads; ++k) reinterpret_cast<u32x4_t*>(s_rows[k * kPerPass + lr])[lc] = x[k];
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kLoads; ++k) x[k] = chunk(i0 + kRows + k * kPerPass + lr);
-        const int cnt = min(kRows, n - i0);
-        int i = 0;
-        for (; i + 16 <= cnt; i += 16) {
-            float v[16];
-#pragma unroll
-            for (int k = 0; k < 16; ++k) v[k] = load_elem(&s_rows[i + k][0], j);
-#pragma unroll
-            for (int k = 0; k < 16; ++k) s = s + static_cast<double>(v[k]);
-        }
-        for (; i < cnt; ++i) s = s + static_cast<double>(load_elem(&s_rows[i][0], j));
-    }
+    int i = 0;
+    for (; n - i >= 32; i += 32) s = add_rows<32, true, T, D>(s, col, i, 32);
+    if (n - i > 16)
+        s = add_rows<32, false, T, D>(s, col, i, n - i);
+    else if (n - i > 8)
+        s = add_rows<16, false, T, D>(s, col, i, n - i);
+    else if (n - i > 4)
+        s = add_rows<8, false, T, D>(s, col, i, n - i);
+    else if (n - i > 2)
+        s = add_rows<4, false, T, D>(s, col, i, n - i);
+    else if (n - i > 0)
+        s = add_rows<2, false, T, D>(s, col, i, n - i);
     store_mean(reps + t * D + j, s / static_cast<double>(n));
 }
 

@@ -168,3 +168,19 @@ def test_routing_kl_absent_teams():
         t = oracle.build_teams_from_labels(x, lab[0, kv], 4)
         ref = oracle.routing_kl(b.q[0, h], x, t, oracle.routing_keys(x, t, "representative", wl.dtype), wl.scale)
         assert abs(kl[0, h] - ref) <= 1e-9 + 1e-9 * abs(ref), (h, kl[0, h], ref)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("fp32", 128), ("fp32", 64)])
+def test_centroid_keys_by_team_size(dtype, d):
+    # teams of the sizes where the mean's blocks of rows change
+    sizes = [1, 2, 3, 4, 5, 8, 9, 16, 17, 31, 32, 33, 48, 49, 64, 65, 300]
+    lab = np.random.default_rng(4).permutation(np.repeat(np.arange(len(sizes), dtype=np.int32), sizes))
+    wl = datagen.WORKLOADS["qwen8k" if dtype == "bf16" else "tiny"].with_(
+        name="sizes", d=d, N=lab.size, Hq=1, Hkv=1, T=0)
+    log(f"[gpu] centroid keys by team size {dtype} d={d}")
+    b = datagen.generate(wl)
+    db = dev_batch(b)
+    teams = sp.build_teams_from_labels(db.K, db.V, torch.from_numpy(lab[None, None]).cuda(), len(sizes), 1)
+    sp.set_route_keys(teams, "centroid")
+    t = oracle.build_teams_from_labels(b.f64(b.K[0, 0]), lab, 1)
+    _check_keys(teams, b, [[oracle.routing_keys(b.f64(b.K[0, 0]), t, "centroid", wl.dtype)]])
