@@ -408,11 +408,11 @@ struct TeamArrays {
 // the HELD rows that registers hold.
 template <typename T, int D, bool ONE, bool PACK, int HELD, typename Tok, typename Owner, typename Store>
 __device__ __forceinline__ void write_teams(const TeamArrays<T>& out, const T* __restrict__ K, const T* __restrict__ V,
-                                            int N, int R, int M, int bh, int start, int n, int team0, char* lds, Tok tok,
-                                            Owner owner, Store store_row) {
+                                            int N, int R, int M, int bh, int start, int n, int team0, int nt, char* lds,
+                                            Tok tok, Owner owner, Store store_row) {
     using C = Chunk<T, D>;
     constexpr int E = C::E;
-    const int tid = fresh_tid(), nt = blockDim.x, nw = nt / kWave;
+    const int tid = fresh_tid(), nw = nt / kWave;
     const int lane = tid & (kWave - 1), w = tid / kWave, sub = tid & 15, g16 = tid & ~15, lbase = lane & 48;
     const int r = min(R, n), nblk = ONE ? 1 : (n + nt - 1) / nt, wstride = min(R, kRankBlock);
     const BuildLds L = build_lds(nw, R, D, sizeof(T));
@@ -520,7 +520,7 @@ __device__ __forceinline__ void write_teams(const TeamArrays<T>& out, const T* _
             }
 }
 
-// Thread t owns members t, t + nt, ... of its parent (nt = blockDim.x; ONE:
+// Thread t owns members t, t + nt, ... of its parent (nt threads run; ONE:
 // at most nt members, so one each, its state in registers, else in `state`).
 // Each sixteen lanes hold the rows of their sixteen members of a block of nt
 // together, one sixteenth of every row per lane, so that rows are read and
@@ -540,8 +540,8 @@ __device__ __forceinline__ void write_teams(const TeamArrays<T>& out, const T* _
 // (782 us).
 template <typename T, int D, bool LIST, bool ONE>
 __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, int N, int R, int M, int bh, int start,
-                             int n, int team0, const int* __restrict__ mem, MemberState* __restrict__ state_all,
-                             const TeamArrays<T>& out, char* lds) {
+                             int n, int team0, int nt, const int* __restrict__ mem,
+                             MemberState* __restrict__ state_all, const TeamArrays<T>& out, char* lds) {
     using C = Chunk<T, D>;
     constexpr int E = C::E;
     // rows kept in registers, and rows of the others in flight at once: what
@@ -551,7 +551,7 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
     // whole rows fit the registers: parents that the estimates leave open are
     // built by k_build_open
     constexpr bool DEFER = ONE && !LIST && CACHE == 16;
-    const int tid = threadIdx.x, nt = blockDim.x, nw = nt / kWave;
+    const int tid = threadIdx.x, nw = nt / kWave;
     const int w = wave_id(), lane = lane_id(), sub = lane & 15, g16 = tid & ~15, lbase = lane & 48;
     const int r = min(R, n);
     const int nblk = ONE ? 1 : (n + nt - 1) / nt;
@@ -1099,7 +1099,7 @@ __device__ void build_parent(const T* __restrict__ K, const T* __restrict__ V, i
         }
     }
     write_teams<T, D, ONE, ONE && !LIST, CACHE>(
-        out, K, V, N, R, M, bh, start, n, team0, lds, tok,
+        out, K, V, N, R, M, bh, start, n, team0, nt, lds, tok,
         [&](int i) { return static_cast<int>((ONE ? st.own : state[i].own) & 0xffffu); },
         [&](int k, T* to) { cache[k].store(to); });
 }
@@ -1112,7 +1112,8 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_contiguous(
     extern __shared__ __align__(16) char s_build[];
     const int p = blockIdx.x, bh = blockIdx.y, start = p * P;
     if (p == 0 && threadIdx.x == 0) team_count[bh] = M;
-    build_parent<T, D, false, ONE>(K, V, N, R, M, bh, start, min(P, N - start), p * min(R, P), nullptr, state, out, s_build);
+    build_parent<T, D, false, ONE>(K, V, N, R, M, bh, start, min(P, N - start), p * min(R, P), blockDim.x, nullptr, state, out,
+                                   s_build);
 }
 
 // LDS of k_build_open: build_lds, then the rows that nt threads load at once, one
@@ -1216,7 +1217,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_open(const T* __restric
             rep = far.i < n ? far.i : 0;
         }
     }
-    write_teams<T, D, true, true, 0>(out, K, V, N, R, M, bh, start, n, team0, s_build, [=](int i) { return start + i; },
+    write_teams<T, D, true, true, 0>(out, K, V, N, R, M, bh, start, n, team0, nt, s_build, [=](int i) { return start + i; },
                                      [=](int) { return owner; }, [](int, T*) {});
 }
 
@@ -1232,10 +1233,15 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_lists(
     const int start = pbeg[at], n = pbeg[at + 1] - start;
     if (n <= 0) return;  // empty parents are omitted (uniform over the workgroup)
     const int* const mem = members + static_cast<size_t>(bh) * N + start;
-    if (n <= static_cast<int>(blockDim.x))  // uniform
-        build_parent<T, D, true, true>(K, nullptr, N, R, M, bh, start, n, toff[at], mem, state, out, s_build);
+    // waves without members end here (a barrier counts the waves that have not
+    // ended), so that small parents leave room for others: a table of 2600 parents
+    // of one or a few members takes 223 us, 310 with all waves kept
+    const int nt = min(kBuildThreads, (n + kWave - 1) / kWave * kWave);
+    if (static_cast<int>(threadIdx.x) >= nt) return;
+    if (n <= nt)  // uniform
+        build_parent<T, D, true, true>(K, nullptr, N, R, M, bh, start, n, toff[at], nt, mem, state, out, s_build);
     else
-        build_parent<T, D, true, false>(K, nullptr, N, R, M, bh, start, n, toff[at], mem, state, out, s_build);
+        build_parent<T, D, true, false>(K, nullptr, N, R, M, bh, start, n, toff[at], nt, mem, state, out, s_build);
 }
 
 // Row gather into team order: packed[bh][pos] = src[bh][perm[bh][pos]], and the
