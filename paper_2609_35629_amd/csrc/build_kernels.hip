@@ -307,17 +307,6 @@ __device__ __forceinline__ float transpose_sum16(const float (&v)[16]) {
     return (h0 ? c[1] : c[0]) + dpp_f32<0xB1>(h0 ? c[0] : c[1]);                                      // quad [1,0,3,2]
 }
 
-// Maximum of a float over the wave (wave-uniform).
-__device__ __forceinline__ float wave_max_f32(float v) {
-    v = fmaxf(v, dpp_f32<0x128>(v));
-    v = fmaxf(v, dpp_f32<0x124>(v));
-    v = fmaxf(v, dpp_f32<0x122>(v));
-    v = fmaxf(v, dpp_f32<0x121>(v));
-    const int x = __float_as_int(v);
-    return fmaxf(fmaxf(__int_as_float(readlane(x, 0)), __int_as_float(readlane(x, 16))),
-                 fmaxf(__int_as_float(readlane(x, 32)), __int_as_float(readlane(x, 48))));
-}
-
 // A member's running minimum over the representatives so far: the three
 // smallest estimates and the representatives of the first two (own = first |
 // second << 16).  A chosen representative has m1 = -inf and owns itself.

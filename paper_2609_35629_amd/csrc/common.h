@@ -287,6 +287,31 @@ __device__ __forceinline__ int wave_sum(int x) {
     return readlane(x, 0) + readlane(x, 16) + readlane(x, 32) + readlane(x, 48);
 }
 
+// Maximum of a float over the wave (wave-uniform).
+__device__ __forceinline__ float wave_max_f32(float v) {
+    v = fmaxf(v, dpp_f32<0x128>(v));
+    v = fmaxf(v, dpp_f32<0x124>(v));
+    v = fmaxf(v, dpp_f32<0x122>(v));
+    v = fmaxf(v, dpp_f32<0x121>(v));
+    const int x = __float_as_int(v);
+    return fmaxf(fmaxf(__int_as_float(readlane(x, 0)), __int_as_float(readlane(x, 16))),
+                 fmaxf(__int_as_float(readlane(x, 32)), __int_as_float(readlane(x, 48))));
+}
+
+// Maximum of an unsigned value over the wave (wave-uniform).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#define SANTAPP_MAXSTEP(CTRL) \
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, false)));
+    SANTAPP_MAXSTEP(0x128)
+    SANTAPP_MAXSTEP(0x124)
+    SANTAPP_MAXSTEP(0x122)
+    SANTAPP_MAXSTEP(0x121)
+#undef SANTAPP_MAXSTEP
+    const int x = static_cast<int>(v);
+    return max(max(static_cast<uint32_t>(readlane(x, 0)), static_cast<uint32_t>(readlane(x, 16))),
+               max(static_cast<uint32_t>(readlane(x, 32)), static_cast<uint32_t>(readlane(x, 48))));
+}
+
 template <bool kAnd>
 __device__ __forceinline__ uint32_t wave_bits32(uint32_t x) {
     int v = static_cast<int>(x);

@@ -852,20 +852,6 @@ __device__ __forceinline__ KeyViews key_views(const DecodeArgs& a) {
                     reinterpret_cast<double*>(a.ws + a.key.phi), reinterpret_cast<uint64_t*>(a.ws + a.key.tokens)};
 }
 
-// Maximum of an unsigned value over the wave (wave-uniform).
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#define SANTAPP_MAXSTEP(CTRL) \
-    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, false)));
-    SANTAPP_MAXSTEP(0x128)
-    SANTAPP_MAXSTEP(0x124)
-    SANTAPP_MAXSTEP(0x122)
-    SANTAPP_MAXSTEP(0x121)
-#undef SANTAPP_MAXSTEP
-    const int x = static_cast<int>(v);
-    return max(max(static_cast<uint32_t>(readlane(x, 0)), static_cast<uint32_t>(readlane(x, 16))),
-               max(static_cast<uint32_t>(readlane(x, 32)), static_cast<uint32_t>(readlane(x, 48))));
-}
-
 // The value of rank `want` (0-based, descending) among x[0 .. R) of all lanes,
 // its lowest `drop` bits cleared (so at most that value): bit by bit below the
 // nonzero values' common prefix, counting the values at or above each
@@ -897,8 +883,7 @@ __device__ __forceinline__ uint32_t wave_kth(const uint32_t (&x)[R], int want, i
 }
 
 constexpr int kTopList = 256;
-constexpr int kRouteTeamsWg = kKeyTeamsWg;  // teams of a routing workgroup
-static_assert(kRouteTeamsWg == 16 * kWaves, "sixteen teams a wave");
+static_assert(kKeyTeamsWg == 16 * kWaves, "sixteen teams a wave");
 
 // LDS of the sampling launch: the workgroup's Philox words, or per head of the
 // selection the upper halves of its teams' fp32 keys, the sampled teams' bits
@@ -913,7 +898,7 @@ __host__ __device__ inline KeyLds key_lds(int M, int G) {
     L.bits = L.keys + G * Mr * 2;
     L.list = L.bits + G * (Mr / 32) * 4;
     L.total = L.list + G * kTopList * 2;
-    const int words = G * kRouteTeamsWg * 8;
+    const int words = G * kKeyTeamsWg * 8;
     if (L.total < words) L.total = words;
     return L;
 }
@@ -1279,7 +1264,7 @@ struct ArrivalSlots {
     }
 };
 
-// A workgroup takes kRouteTeamsWg teams of a pair, a wave 16 of them: phi of
+// A workgroup takes kKeyTeamsWg teams of a pair, a wave 16 of them: phi of
 // every head (16 x 16 tiles of v_mfma_f64_16x16x4_f64: A head i on lanes
 // 16 c + i, B team j on lanes 16 c + j, lane group c holding dims [c D / 4,
 // (c + 1) D / 4); result register q of lane 16 c + j is head 4 q + c of team
@@ -1298,11 +1283,11 @@ __global__ __launch_bounds__(kThreads, 1) void k_route_select(DecodeArgs a) {
     using Q = Quarter<T, D>;
     typedef double f64x4 __attribute__((ext_vector_type(4)));
     extern __shared__ __align__(16) char s_keys[];
-    uint64_t(*const s_word)[kRouteTeamsWg] = reinterpret_cast<uint64_t(*)[kRouteTeamsWg]>(s_keys);
+    uint64_t(*const s_word)[kKeyTeamsWg] = reinterpret_cast<uint64_t(*)[kKeyTeamsWg]>(s_keys);
     __shared__ int s_last;
     const int tid = threadIdx.x, lane = lane_id(), c = lane >> 4, j = lane & 15;
     const int p = blockIdx.y, b = p / a.Hkv, kv = p - b * a.Hkv, G = a.G, M = a.M;
-    const int g0 = blockIdx.x * kRouteTeamsWg, t = wave_id() * 16 + j;
+    const int g0 = blockIdx.x * kKeyTeamsWg, t = wave_id() * 16 + j;
     const int g = min(g0 + t, M - 1);
     const size_t tg = static_cast<size_t>(p) * M + g;
     Q row;
@@ -1320,7 +1305,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_route_select(DecodeArgs a) {
     const double ln = a.log_n[tg];
     // the Philox block at counter (g / 4, h, b, step), key (seed, 0), holds the
     // words of teams 4 (g / 4) .. + 3
-    constexpr int kBlocks = kRouteTeamsWg / 4;
+    constexpr int kBlocks = kKeyTeamsWg / 4;
     for (int i = tid; i < G * kBlocks; i += kThreads) {
         const int h = i / kBlocks, q = i - h * kBlocks;
         const u64x4 r = philox4x64_10(static_cast<uint64_t>(g0 / 4 + q), static_cast<uint64_t>(kv * G + h),

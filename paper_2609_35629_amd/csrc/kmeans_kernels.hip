@@ -388,17 +388,6 @@ struct Near3 {
     }
 };
 
-// Maximum of a float over the wave (wave-uniform).
-__device__ __forceinline__ float wave_fmax(float v) {
-    v = fmaxf(v, dpp_f32<0x128>(v));
-    v = fmaxf(v, dpp_f32<0x124>(v));
-    v = fmaxf(v, dpp_f32<0x122>(v));
-    v = fmaxf(v, dpp_f32<0x121>(v));
-    const int x = __float_as_int(v);
-    return fmaxf(fmaxf(__int_as_float(readlane(x, 0)), __int_as_float(readlane(x, 16))),
-                 fmaxf(__int_as_float(readlane(x, 32)), __int_as_float(readlane(x, 48))));
-}
-
 // Nearest center of 64 points per workgroup.  The centers are compared on fp32
 // estimates |c|^2 - 2 x.c, center tiles of 32 in LDS: a wave's 16 points
 // against 16 centers as one tile of v_mfma_f32_16x16x4_f32 (A point i on lanes
@@ -560,8 +549,8 @@ __global__ __launch_bounds__(kAsgThreads) void k_km_assign(
     }
     {
         const bool odd = __ballot(!(xn2 < INFINITY)) != 0;
-        const float x2 = odd ? INFINITY : wave_fmax(xn2), c2 = wave_fmax(cn2);
-        const bool zero = !odd && c2 < INFINITY && wave_fmax(fmaxf(xabs, cabs)) == 0.f;  // every distance is 0
+        const float x2 = odd ? INFINITY : wave_max_f32(xn2), c2 = wave_max_f32(cn2);
+        const bool zero = !odd && c2 < INFINITY && wave_max_f32(fmaxf(xabs, cabs)) == 0.f;  // every distance is 0
         const float size = __fsqrt_rn(x2) * __fsqrt_rn(c2) + c2;
         if (lane == 0) s_err[wv] = zero ? -1.f : c2 > 1e-30f && size < 1e30f && x2 < 1e30f ? 1400.f * 0x1.0p-24f * size : INFINITY;
     }
