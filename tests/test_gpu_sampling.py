@@ -2,8 +2,10 @@
 teams, budgets up to 144, at most half as many heads as compute units, and a
 workspace that holds the scores) against the oracle and against the
 sampling kernel that a smaller workspace takes: the same teams, tau and log c
-for budgets at the edges of its ranking (64 and 256 listed teams, nearly all
-teams), for the largest table, and where absent teams tie."""
+for budgets at the edges of its ranking (64 listed teams) and on both sides of
+its limit, for the largest table, where scores lie close for their size, and
+where absent teams tie.  (Larger budgets take the other kernel in either
+workspace.)"""
 import numpy as np
 import pytest
 import torch
@@ -38,6 +40,7 @@ def _small_workspace(teams, db, wl, K):
     ("fp32", 128, 5, 1, 2051, 4, 2, (31, 128, 700)),
     ("fp32", 64, 8, 1, 2561, 2, 1, (40, 1200)),
     ("bf16", 128, 8, 1, 8192, 1, 1, (33, 200, 4000)),
+    ("bf16", 64, 8, 1, 8192, 4, 2, (128, 144, 145)),
 ])
 def test_budgets_match_oracle_and_small_workspace(dtype, d, Hq, Hkv, N, P, R, budgets):
     wl = datagen.WORKLOADS["qwen8k" if dtype == "bf16" else "tiny"].with_(
